@@ -296,10 +296,12 @@ hyenand_status hyenand_fftconv_plan_name(int ndim, const int64_t* dims, hyenand_
  * (L - 1)] h[n] + D h[j], gk[i] = sum_n h[n] u[n - i + (L - 1)]) and
  * extents that are not powers of two: both are circular convolutions on
  * their transform grid once u is zero-padded and k placed at its
- * displacements.  Extents that are not powers of two run in one pass on the
+ * displacements.  Centred images of 16 to 64 power-of-two points per axis (at
+ * most 2:1) run in one pass, as the linear ones do.  Extents that are not
+ * powers of two run in one pass on the
  * forward's mixed-radix grid where it fits (about 3000 transform points per
  * image; the workspace holds the gD sums only).  The other shapes, and the
- * centred mode on power-of-two extents, are embedded: the library copies x1,
+ * centred mode on other power-of-two extents, are embedded: the library copies x1,
  * x2, v, gy and k into the transform grid (a power of two >= 2 L_d - 1 per
  * axis), runs the circular backward there and extracts the gradients.  The
  * workspace then starts with the nine embedded tensors (each B * C * prod P

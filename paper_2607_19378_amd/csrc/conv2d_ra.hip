@@ -1,0 +1,491 @@
+// Single-pass 2D kernels of the non-circular modes (linear and centered),
+// forward and backward, on right-angle row transforms (ra_device.hpp): the
+// whole image stays in LDS, HBM sees each tensor once.
+//
+// Rows (axis 1) are transformed in the ring x^N = -i, N = P1 / 2 complex points
+// for L1 = N reals; columns (axis 0) as ordinary zero-padded transforms of
+// P0 = 2 L0 points.  Every bin column is an ordinary complex column: products
+// are pointwise, and no pass untangles mirror bins.  One wavefront holds whole
+// rows, then whole columns, so a barrier is needed only where rows turn into
+// columns and back (two per image in the linear forward kernel).
+//
+// What bounds them (8 x 256 images of 64 x 64, fp32): the forward kernel issues
+// 25.5 M VALU instructions, 41.5 us, with 47 us of arithmetic without its
+// loads and stores and 33 us of traffic; two images per CU (74 KB of LDS
+// each, 110 VGPRs) overlap the two.  The packed real transforms that these
+// replace issued 29.0 M and met 21 barriers: linear forward 64.7 -> 58.1 us,
+// the operator on centered kernels 165 -> 118 us (bf16), linear backward 217
+// -> 200 us, and centered backward 1564 us (embedded in the circular 128 x 128
+// grid) -> 224 us.  The backward holds three spectra in registers (228 VGPRs):
+// one image per CU, its loads, arithmetic and stores in turn; at 128 VGPRs it
+// spills (360 us).  Keeping a workgroup resident and fetching the next image's
+// inputs during the inverse rows spilled too (80 us forward).
+#include "ra_device.hpp"
+
+namespace hyenand {
+
+namespace {
+
+template <int P0, int N>
+struct Ra2D {
+  using Row = RaRow<N>;
+  static constexpr int L0 = P0 / 2, L1 = N;
+  static constexpr int PITCH = Row::PITCH;
+  using Col = RaCol<P0, PITCH>;
+  static constexpr int NT = N * Col::T;         // one round of columns
+  static constexpr int RPR = NT / Row::T;       // rows per round
+  static constexpr int NR = (P0 + RPR - 1) / RPR;  // rounds of P0 rows (two for 128 columns points, else one)
+  static_assert(P0 % RPR == 0 && (NR == 1 || RPR == L0), "rounds hold whole signals or both");
+};
+
+// k of one line: kernel point of displacement (d0, d1)
+template <bool KC, int L0, int L1, typename TS>
+__device__ __forceinline__ float2 ra_kernel_point(const TS* kl, int g0, int n, float scale) {
+  if constexpr (!KC) {
+    return make_float2(ld1(kl + g0 * L1 + n) * scale, 0.f);
+  } else {
+    constexpr int K1 = 2 * L1 - 1;
+    float2 z = czero();
+    if (g0 != L0) {  // row L0 holds no displacement
+      const TS* kr = kl + (g0 < L0 ? g0 + L0 - 1 : g0 - L0 - 1) * K1;
+      z.x = ld1(kr + L1 - 1 + n) * scale;
+      if (n > 0) z.y = ld1(kr + n - 1) * scale;
+    }
+    return z;
+  }
+}
+
+// KH as in the circular kernel: 0 transforms each image's own k, 1 writes the
+// spectrum of each channel's k to khat[c][n][col] and stops, 2 reads it.
+template <int P0, int N, bool KC, typename TS, bool ACT, int KH>
+__global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves_per_eu(4)))
+    conv2d_ra(const TS* __restrict__ x1, const TS* __restrict__ x2, const TS* __restrict__ v,
+              const TS* __restrict__ k, const TS* __restrict__ Dp, TS* __restrict__ y, int C, int kC, ActIn ain,
+              float2* __restrict__ khat) {
+  static_assert(KH == 0 || (!KC && !ACT), "kept spectra: linear, plain gates");
+  using F = Ra2D<P0, N>;
+  using Row = typename F::Row;
+  using Col = typename F::Col;
+  constexpr int L0 = F::L0, L1 = F::L1, PITCH = F::PITCH, RPR = F::RPR, NR = F::NR, TR = Row::T;
+  constexpr int E = Col::E, TC = Col::T;
+  constexpr float scale = 1.f / ((float)P0 * (float)N);  // of the unnormalised inverses, a power of two
+  __shared__ float2 S[P0 * PITCH];
+  int img = blockIdx.x;
+  if constexpr (KH == 2) {
+    // the B images of a channel in consecutive slots of one XCD (workgroup j
+    // runs on XCD j mod 8): its spectrum comes into that L2 once
+    if ((C & 7) == 0) {
+      const int nb = (int)gridDim.x / C, x = img & 7, q = img >> 3;
+      img = (q % nb) * C + (q / nb) * 8 + x;
+    }
+  }
+  const int c = img % C;
+  const int tid = threadIdx.x;
+  const int rr = tid / TR, tr = tid % TR;                     // row of a round, lane of the row
+  const int lane = tid & 63;
+  const int col = (tid >> 6) * Col::CW + lane % Col::CW, tc = lane / Col::CW;  // column, lane of the column
+  float2* const cp = S + Col::slot(col);
+  const int r = rr % L0;                          // data row of this lane
+  const bool has_u = NR == 2 || rr < L0;          // with one round, lanes rr >= L0 take K's rows
+  const size_t rb = (size_t)img * L0 * L1 + r * L1 + tr;  // its first point
+  const TS* const kl = k + (size_t)k_line(img, kC) * (KC ? (2 * L0 - 1) * (2 * L1 - 1) : L0 * L1);
+  const Gates<ACT> G = line_gates<ACT, TS>(ain, img, C);
+
+  typename Row::FwdTw ftw;
+  ftw.load(tr);
+  auto load_u = [&](float (&a)[8], float (&b)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      a[e] = ld1(x1 + rb + TR * e);
+      b[e] = ld1(v + rb + TR * e);
+    }
+  };
+  auto gate_u = [&](const float (&a)[8], const float (&b)[8], float2 (&w)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) w[e] = Row::lead(G.u1(a[e], b[e], r * L1 + tr + TR * e), e);
+  };
+  auto load_k = [&](int g0, float2 (&w)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) w[e] = ra_kernel_point<KC, L0, L1>(kl, g0, tr + TR * e, scale);
+  };
+  auto lead_k = [&](float2 (&w)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) w[e] = KC ? Row::lead(w[e], e) : Row::lead(w[e].x, e);
+  };
+  auto row_fwd = [&](int slot_row, float2 (&w)[8]) {
+    float2* const row = S + slot_row * PITCH;
+    Row::forward(w, tr, row, ftw);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) row[tr + Row::off(e)] = w[e];
+  };
+
+  float2 wu[E], wk[E];
+  typename Col::Tw ctw;
+  if constexpr (KC) {
+    // U's rows first; each lane keeps the U values of its column while K's
+    // P0 rows take the region
+    if (has_u) {
+      float a[8], b[8];
+      float2 w[8];
+      load_u(a, b);
+      gate_u(a, b, w);
+      row_fwd(rr, w);
+    }
+    float2 wr[NR][8];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) load_k(q * RPR + rr, wr[q]);
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E / 2; ++e) wu[e] = cp[(tc + TC * e) * PITCH];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      lead_k(wr[q]);
+      row_fwd(q * RPR + rr, wr[q]);
+    }
+    __syncthreads();
+    ctw.load(tc);
+#pragma unroll
+    for (int e = 0; e < E; ++e) wk[e] = cp[(tc + TC * e) * PITCH];
+  } else {
+    // U in rows [0, L0) of the region, K in [L0, P0)
+    if constexpr (NR == 2) {
+      float a[8], b[8];
+      float2 wr[8];
+      if constexpr (KH != 2) load_k(rr, wr);
+      if constexpr (KH != 1) load_u(a, b);
+      if constexpr (KH != 2) {
+        lead_k(wr);
+        row_fwd(L0 + rr, wr);
+      }
+      if constexpr (KH != 1) {
+        gate_u(a, b, wr);
+        row_fwd(rr, wr);
+      }
+    } else if (KH == 0 || (KH == 1) == !has_u) {
+      float2 w[8];
+      if (!has_u) {
+        load_k(r, w);
+        lead_k(w);
+      } else {
+        float a[8], b[8];
+        load_u(a, b);
+        gate_u(a, b, w);
+      }
+      row_fwd(rr, w);
+    }
+    __syncthreads();
+    ctw.load(tc);
+    if constexpr (KH != 1) {
+#pragma unroll
+      for (int e = 0; e < E / 2; ++e) wu[e] = cp[(tc + TC * e) * PITCH];
+    }
+    if constexpr (KH != 2) {
+#pragma unroll
+      for (int e = 0; e < E / 2; ++e) wk[e] = cp[(L0 + tc + TC * e) * PITCH];
+#pragma unroll
+      for (int e = E / 2; e < E; ++e) wk[e] = czero();
+    }
+  }
+
+  // columns: forward, product with the folded shortcut, inverse, crop
+  float2* const kh = khat + ((size_t)c * P0 + tc) * N + col;
+  if constexpr (KH == 2) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) wk[e] = kh[TC * e * N];
+  } else {
+    Col::template run<false>(wk, tc, cp, ctw);
+  }
+  if constexpr (KH == 1) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) kh[TC * e * N] = wk[e];
+    return;
+  }
+#pragma unroll
+  for (int e = E / 2; e < E; ++e) wu[e] = czero();
+  Col::template run<false>(wu, tc, cp, ctw);
+  const float Ds = scale * ld1(Dp + c);
+#pragma unroll
+  for (int e = 0; e < E; ++e) wu[e] = gated_product(wu[e], wk[e], Ds);
+  // the outer gate and the inverse rows' twiddles arrive meanwhile
+  float g[8];
+  typename Row::InvTw itw;
+  if (has_u) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) g[e] = ld1(x2 + rb + TR * e);
+    itw.load(tr);
+  }
+  Col::template run<true>(wu, tc, cp, ctw);
+  wave_sync();
+#pragma unroll
+  for (int e = 0; e < E / 2; ++e) cp[(tc + TC * e) * PITCH] = wu[e];
+
+  // inverse rows, outer gate, store
+  __syncthreads();
+  if (!has_u) return;
+  float2* const row = S + rr * PITCH;
+  float2 w[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) w[e] = row[tr + Row::off(e)];
+  Row::inverse(w, tr, row, itw);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) st1(y + rb + TR * e, G.g1(g[e]) * Row::re(w[e], e));
+}
+
+// Backward (conv_backward.hip states the products): U and H take the region
+// side by side, then K; the three products' inverses return z and gu together,
+// then gk.  x1, v and gy stay in registers from staging to the epilogue (the
+// lane that stages row r of u and h stores row r of the gradients).
+template <int P0, int N, bool KC, typename TS>
+__global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves_per_eu(2)))
+    bwd2d_ra(const TS* __restrict__ x1, const TS* __restrict__ x2, const TS* __restrict__ v,
+             const TS* __restrict__ k, const TS* __restrict__ Dp, const TS* __restrict__ gy, TS* __restrict__ gx1,
+             TS* __restrict__ gx2, TS* __restrict__ gv, TS* __restrict__ gk, float* __restrict__ partial, int C) {
+  using F = Ra2D<P0, N>;
+  using Row = typename F::Row;
+  using Col = typename F::Col;
+  constexpr int L0 = F::L0, L1 = F::L1, PITCH = F::PITCH, RPR = F::RPR, NR = F::NR, TR = Row::T, NT = F::NT;
+  constexpr int E = Col::E, TC = Col::T;
+  constexpr float scale = 1.f / ((float)P0 * (float)N);
+  __shared__ float2 S[P0 * PITCH];
+  __shared__ float red[imax(1, NT / 64)];
+  const int img = blockIdx.x;
+  const int c = img % C;
+  const size_t base = (size_t)img * L0 * L1;
+  constexpr int KPTS = KC ? (2 * L0 - 1) * (2 * L1 - 1) : L0 * L1;
+  const TS* const kl = k + (size_t)img * KPTS;
+  TS* const gkl = gk + (size_t)img * KPTS;
+  const int tid = threadIdx.x;
+  const int rr = tid / TR, tr = tid % TR;
+  const int lane = tid & 63;
+  const int col = (tid >> 6) * Col::CW + lane % Col::CW, tc = lane / Col::CW;
+  float2* const cp = S + Col::slot(col);
+  const int r = rr % L0;                        // data row of this lane
+  const size_t rb = base + (size_t)r * L1 + tr;  // its first point
+
+  // rows of u [0, L0) and h [L0, P0)
+  float xa[8], xv[8], xg[8];
+  typename Row::FwdTw ftw;
+  ftw.load(tr);
+  auto row_fwd = [&](int slot_row, float2 (&w)[8]) {
+    float2* const row = S + slot_row * PITCH;
+    Row::forward(w, tr, row, ftw);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) row[tr + Row::off(e)] = w[e];
+  };
+  {
+    float xe[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      xa[e] = ld1(x1 + rb + TR * e);
+      xv[e] = ld1(v + rb + TR * e);
+      xg[e] = ld1(gy + rb + TR * e);
+      xe[e] = ld1(x2 + rb + TR * e);
+    }
+    float hu = 0.f;
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      const bool ish = q * RPR + rr >= L0;
+      float2 w[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) w[e] = Row::lead(ish ? xg[e] * xe[e] : xa[e] * xv[e], e);
+      row_fwd(q * RPR + rr, w);
+    }
+    if (rr < L0) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) hu += (xa[e] * xv[e]) * (xg[e] * xe[e]);
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) hu += __shfl_xor(hu, o, 64);
+    if (lane == 0) red[tid >> 6] = hu;
+  }
+  // K's rows are fetched while the columns of U and H are read
+  constexpr int NK = KC ? NR : 1;  // rounds of K's rows
+  float2 wr[NK][8];
+#pragma unroll
+  for (int q = 0; q < NK; ++q) {
+    const int g0 = q * RPR + rr;
+    if (KC || g0 < L0) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) wr[q][e] = ra_kernel_point<KC, L0, L1>(kl, g0, tr + TR * e, scale);
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < NT / 64; ++i) s += red[i];
+    partial[img] = s;
+  }
+  float2 wu[E], wh[E], wk[E];
+#pragma unroll
+  for (int e = 0; e < E / 2; ++e) {
+    wu[e] = cp[(tc + TC * e) * PITCH];
+    wh[e] = cp[(L0 + tc + TC * e) * PITCH];
+    wu[E / 2 + e] = wh[E / 2 + e] = czero();
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < NK; ++q) {
+    const int g0 = q * RPR + rr;
+    if (KC || g0 < L0) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) wr[q][e] = KC ? Row::lead(wr[q][e], e) : Row::lead(wr[q][e].x, e);
+      row_fwd(g0, wr[q]);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < E; ++e) wk[e] = (KC || e < E / 2) ? cp[(tc + TC * e) * PITCH] : czero();
+
+  // columns: three forward transforms, the products, inverse of z and gu
+  typename Col::Tw ctw;
+  ctw.load(tc);
+  Col::template run<false>(wk, tc, cp, ctw);
+  Col::template run<false>(wu, tc, cp, ctw);
+  Col::template run<false>(wh, tc, cp, ctw);
+  {
+    const float Ds = scale * ld1(Dp + c);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const float2 kd = make_float2(wk[e].x + Ds, wk[e].y);
+      wk[e] = c_scale(c_mulc(wh[e], wu[e]), scale);  // gk: H conj U
+      wu[e] = c_mul(wu[e], kd);                      // z: U (K + D)
+      wh[e] = c_mulc(wh[e], kd);                     // gu: H conj(K + D)
+    }
+  }
+  Col::template run<true>(wu, tc, cp, ctw);
+  Col::template run<true>(wh, tc, cp, ctw);
+  wave_sync();
+#pragma unroll
+  for (int e = 0; e < E / 2; ++e) {
+    cp[(tc + TC * e) * PITCH] = wu[e];
+    cp[(L0 + tc + TC * e) * PITCH] = wh[e];
+  }
+  typename Row::InvTw itw;
+  itw.load(tr);
+  __syncthreads();
+
+  // rows of z and gu; gx2 = gy z, gx1 = gu v, gv = gu x1
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    float2* const row = S + (q * RPR + rr) * PITCH;
+    const bool isgu = q * RPR + rr >= L0;
+    float2 w[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) w[e] = row[tr + Row::off(e)];
+    Row::inverse(w, tr, row, itw);
+    if (isgu) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float g = Row::re(w[e], e);
+        st1(gx1 + rb + TR * e, g * xv[e]);
+        st1(gv + rb + TR * e, g * xa[e]);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) st1(gx2 + rb + TR * e, Row::re(w[e], e) * xg[e]);
+    }
+  }
+  __syncthreads();
+
+  // gk: inverse columns (all P0 rows centered), rows, displacements
+  Col::template run<true>(wk, tc, cp, ctw);
+  wave_sync();
+#pragma unroll
+  for (int e = 0; e < (KC ? E : E / 2); ++e) cp[(tc + TC * e) * PITCH] = wk[e];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < NK; ++q) {
+    const int g0 = q * RPR + rr;
+    if (KC || g0 < L0) {
+      float2* const row = S + g0 * PITCH;
+      float2 w[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) w[e] = row[tr + Row::off(e)];
+      Row::inverse(w, tr, row, itw);
+      if constexpr (!KC) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) st1(gkl + g0 * L1 + tr + TR * e, Row::re(w[e], e));
+      } else if (g0 != L0) {
+        constexpr int K1 = 2 * L1 - 1;
+        TS* const kr = gkl + (g0 < L0 ? g0 + L0 - 1 : g0 - L0 - 1) * K1;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int n = tr + TR * e;
+          st1(kr + L1 - 1 + n, Row::re(w[e], e));
+          if (n > 0) st1(kr + n - 1, Row::im(w[e], e));
+        }
+      }
+    }
+  }
+}
+
+template <int P0, int N, typename TS>
+hipError_t launch_fwd_t(const FftConvArgs& a, hipStream_t s) {
+  constexpr int NT = Ra2D<P0, N>::NT;
+#define HY_RA(KC, ACT, KH, GRID)                                                                               \
+  hipLaunchKernelGGL((conv2d_ra<P0, N, KC, TS, ACT, KH>), dim3((unsigned)(GRID)), dim3(NT), 0, s,              \
+                     (const TS*)a.x1, (const TS*)a.x2, (const TS*)a.v, (const TS*)a.k, (const TS*)a.D,         \
+                     (TS*)a.y, (int)a.C, a.kC, a.act_in, a.khat)
+  if (a.centered) {
+    if (a.act) HY_RA(true, true, 0, a.lines);
+    else HY_RA(true, false, 0, a.lines);
+  } else if (a.act) {
+    HY_RA(false, true, 0, a.lines);
+  } else if (a.khat) {
+    if (a.khat_pass != 2) HY_RA(false, false, 1, a.C);
+    if (a.khat_pass != 1) HY_RA(false, false, 2, a.lines);
+  } else {
+    HY_RA(false, false, 0, a.lines);
+  }
+#undef HY_RA
+  return hipGetLastError();
+}
+
+template <int P0, int N, typename TS>
+hipError_t launch_bwd_t(const FftConvBwdArgs& b, hipStream_t s) {
+  const FftConvArgs& a = b.f;
+  constexpr int NT = Ra2D<P0, N>::NT;
+#define HY_RA(KC)                                                                                                 \
+  hipLaunchKernelGGL((bwd2d_ra<P0, N, KC, TS>), dim3((unsigned)a.lines), dim3(NT), 0, s, (const TS*)a.x1,         \
+                     (const TS*)a.x2, (const TS*)a.v, (const TS*)a.k, (const TS*)a.D, (const TS*)b.gy,            \
+                     (TS*)b.gx1, (TS*)b.gx2, (TS*)b.gv, (TS*)b.gk, b.partial, (int)a.C)
+  if (a.centered) HY_RA(true);
+  else HY_RA(false);
+#undef HY_RA
+  return hipGetLastError();
+}
+
+#define HY_RA2D_SIZES(X) X(32, 32) X(64, 64) X(128, 128) X(64, 128) X(128, 64) X(32, 64) X(64, 32)
+
+}  // namespace
+
+bool ra2d_supported(const FftConvArgs& a) {
+  if (a.ndim != 2 || a.circular || a.rl) return false;
+#define HY_CASE(p0, p1) if (a.P[0] == p0 && a.P[1] == p1) return true;
+  HY_RA2D_SIZES(HY_CASE)
+#undef HY_CASE
+  return false;
+}
+
+hipError_t launch_ra2d(const FftConvArgs& a, hipStream_t s) {
+#define HY_CASE(p0, p1)                   \
+  if (a.P[0] == p0 && a.P[1] == p1)       \
+    return a.bf16 ? launch_fwd_t<p0, p1 / 2, uint16_t>(a, s) : launch_fwd_t<p0, p1 / 2, float>(a, s);
+  HY_RA2D_SIZES(HY_CASE)
+#undef HY_CASE
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_ra2d_backward(const FftConvBwdArgs& b, hipStream_t s) {
+  const FftConvArgs& a = b.f;
+#define HY_CASE(p0, p1)                   \
+  if (a.P[0] == p0 && a.P[1] == p1)       \
+    return a.bf16 ? launch_bwd_t<p0, p1 / 2, uint16_t>(b, s) : launch_bwd_t<p0, p1 / 2, float>(b, s);
+  HY_RA2D_SIZES(HY_CASE)
+#undef HY_CASE
+  return hipErrorInvalidValue;
+}
+
+}  // namespace hyenand

@@ -509,6 +509,14 @@ hipError_t launch_bwd2d_t(const FftConvBwdArgs& b, hipStream_t s) {
   }
 }
 
+// linear images from 32 transform points per axis run in conv2d_ra.hip
+template <int P0, int P1, typename TS>
+hipError_t launch_bwd2d(const FftConvBwdArgs& b, hipStream_t s) {
+  if (b.f.circular) return launch_bwd2d_t<P0, P1, true, TS>(b, s);
+  if constexpr (P0 < 32) return launch_bwd2d_t<P0, P1, false, TS>(b, s);
+  return hipErrorInvalidValue;
+}
+
 template <typename TS>
 hipError_t launch_typed(const FftConvBwdArgs& b, hipStream_t s) {
   const FftConvArgs& a = b.f;
@@ -524,10 +532,12 @@ hipError_t launch_typed(const FftConvBwdArgs& b, hipStream_t s) {
   if (a.P[0] == p) e = a.circular ? launch_bwd1d_t<p, true, TS>(b, s) : launch_bwd1d_t<p, false, TS>(b, s);
     HY_BWD1D_SIZES(HY_CASE)
 #undef HY_CASE
+  } else if (ra2d_supported(a)) {
+    e = launch_ra2d_backward(b, s);
   } else if (a.ndim == 2) {
 #define HY_CASE(p0, p1)                                                                                          \
   if (a.P[0] == p0 && a.P[1] == p1)                                                                              \
-    e = a.circular ? launch_bwd2d_t<p0, p1, true, TS>(b, s) : launch_bwd2d_t<p0, p1, false, TS>(b, s);
+    e = launch_bwd2d<p0, p1, TS>(b, s);
     HY_BWD2D_SIZES(HY_CASE)
 #undef HY_CASE
   }
@@ -541,6 +551,8 @@ hipError_t launch_typed(const FftConvBwdArgs& b, hipStream_t s) {
 }  // namespace
 
 bool fused_backward_supported(const FftConvArgs& a) {
+  if (ra2d_supported(a)) return true;
+  if (a.centered) return false;
   if (a.ndim == 1) {
     if (a.L[0] == 1) return true;
 #define HY_CASE(p) \
@@ -551,7 +563,7 @@ bool fused_backward_supported(const FftConvArgs& a) {
   }
   if (a.ndim == 2) {
 #define HY_CASE(p0, p1) \
-  if (a.P[0] == p0 && a.P[1] == p1) return a.circular ? bwd2d_fits<p0, p1, true>() : bwd2d_fits<p0, p1, false>();
+  if (a.P[0] == p0 && a.P[1] == p1) return a.circular ? bwd2d_fits<p0, p1, true>() : p0 < 32;
     HY_BWD2D_SIZES(HY_CASE)
 #undef HY_CASE
   }

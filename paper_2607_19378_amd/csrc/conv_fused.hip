@@ -923,14 +923,18 @@ static hipError_t launch_2d_fused_t(const FftConvArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// linear and centered images from 32 transform points per axis run in
+// conv2d_ra.hip
 template <int P0, int P1>
 static hipError_t launch_2d_fused_p(const FftConvArgs& a, hipStream_t s) {
-  if (a.centered)
-    return a.bf16 ? launch_2d_fused_kc_t<P0, P1, uint16_t>(a, s) : launch_2d_fused_kc_t<P0, P1, float>(a, s);
-  if (a.circular) {
+  if (a.circular)
     return a.bf16 ? launch_2d_fused_t<P0, P1, true, uint16_t>(a, s) : launch_2d_fused_t<P0, P1, true, float>(a, s);
+  if constexpr (P0 < 32) {
+    if (a.centered)
+      return a.bf16 ? launch_2d_fused_kc_t<P0, P1, uint16_t>(a, s) : launch_2d_fused_kc_t<P0, P1, float>(a, s);
+    return a.bf16 ? launch_2d_fused_t<P0, P1, false, uint16_t>(a, s) : launch_2d_fused_t<P0, P1, false, float>(a, s);
   }
-  return a.bf16 ? launch_2d_fused_t<P0, P1, false, uint16_t>(a, s) : launch_2d_fused_t<P0, P1, false, float>(a, s);
+  return hipErrorInvalidValue;
 }
 
 // Instantiated sizes: squares 4..128 and the 2:1 shapes next to 64 and 128.
@@ -950,6 +954,7 @@ size_t fused2d_khat_bytes(const FftConvArgs& a) {
 }
 
 hipError_t launch_fused2d(const FftConvArgs& a, hipStream_t s) {
+  if (ra2d_supported(a)) return launch_ra2d(a, s);
 #define HY_CASE(p0, p1) if (a.P[0] == p0 && a.P[1] == p1) return launch_2d_fused_p<p0, p1>(a, s);
   HY_FUSED2D_SIZES(HY_CASE)
 #undef HY_CASE

@@ -359,13 +359,14 @@ hipError_t run_chunked(const FftConvArgs& a, size_t per, hipStream_t caller, Lau
 }
 
 // Backward plans: single pass per line where the three spectra fit in LDS,
-// else the multi-pass (2D/3D) or four-step (1D) structure of the forward
-// with three signals.  The workspace holds the gD sums (256-byte aligned
+// (conv2d_ra.hip takes the linear and centered images it supports), else the
+// multi-pass (2D/3D) or four-step (1D) structure of the forward with three
+// signals.  The workspace holds the gD sums (256-byte aligned
 // block) and then the spectra of a chunk of lines per side stream.
 //
 // Extents that are not powers of two run the mixed-radix single pass
 // (BWD_MIXED, conv_mixed.hip) where their grid fits; those beyond it and the
-// centred mode on power-of-two extents (BWD_EMBED) run the circular backward
+// centred mode on the other power-of-two extents (BWD_EMBED) run the circular backward
 // on their transform grid (P_d >= 2 L_d - 1, a power of two): the five
 // inputs are embedded in that grid and the four gradient
 // tensors extracted from it (conv_embed.hip); gD comes out directly.  Their
@@ -399,6 +400,7 @@ bool embedded_problem(const FftConvArgs& a, Embedded* m) {
 }
 
 BwdPlan choose_bwd_plan(const FftConvArgs& a) {
+  if (ra2d_supported(a)) return BWD_FUSED;
   if (a.centered || a.rl) {
     // extents that are not powers of two: the mixed-radix single pass on the
     // forward's grid where it fits (HYENAND_PLAN=nomixed avoids it)

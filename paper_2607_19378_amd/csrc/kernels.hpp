@@ -58,6 +58,11 @@ hipError_t launch_fused2d(const FftConvArgs& a, hipStream_t s);
 // per channel (C x P0 x P1/2 complex fp32); 0 where that path does not apply
 // (centered or non-power-of-two grids, the operator)
 size_t fused2d_khat_bytes(const FftConvArgs& a);
+// single-pass 2D kernels of the linear and centered modes (conv2d_ra.hip),
+// forward and backward; launch_fused2d and launch_backward take them where
+// they are supported
+bool ra2d_supported(const FftConvArgs& a);
+hipError_t launch_ra2d(const FftConvArgs& a, hipStream_t s);
 
 // single pass for grid extents that are not powers of two on power-of-two
 // transforms (P_d = the smallest power of two >= 2 L_d - 1; a circular axis
@@ -96,6 +101,7 @@ struct FftConvBwdArgs {
 // and h fit in LDS); one float of partial per line; launches the gD reduction
 bool fused_backward_supported(const FftConvArgs& a);
 hipError_t launch_backward(const FftConvBwdArgs& b, hipStream_t s);
+hipError_t launch_ra2d_backward(const FftConvBwdArgs& b, hipStream_t s);  // without the gD reduction
 // multi-pass 2D/3D and four-step 1D: one call per chunk of lines [line0,
 // line0 + nl) with their three spectra in ws; partial holds the given number
 // of sums per line; launch_backward_reduce adds them into gD afterwards

@@ -1,0 +1,48 @@
+"""Single-pass 2D kernels on right-angle row transforms (conv2d_ra.hip): every transform grid they are built for
+(one and two rounds of rows per signal), both modes, fp32 and bf16, forward and backward, an odd number of images,
+against the fp64 oracle, within the plans' tolerances (relative L2: fp32 1e-5, bf16 2e-2); lines of very different
+scales keep their own accuracy."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2607_19378_amd import workloads as W
+from gpu_util import TOL, from_device, log, per_line_worst, rel_l2, run_gpu, to_device
+
+pytestmark = pytest.mark.gpu
+
+GRIDS = [(16, 16), (16, 32), (32, 16), (32, 32), (32, 64), (64, 32), (64, 64)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("mode", ["linear", "centered"])
+@pytest.mark.parametrize("grid", GRIDS)
+def test_forward_and_backward(grid, mode, dtype):
+    import torch
+    from paper_2607_19378_amd import hyenand as H
+    inp = W.random_case(1, 3, grid, mode, dtype, seed=700 + sum(grid))
+    log(f"ra2d {grid} {mode} {dtype}")
+    assert H.plan_name(inp.workload.shape, mode, dtype) == "fused2d"
+    y = run_gpu(inp)
+    f = inp.as_f64()
+    assert per_line_worst(y, oracle.conv_fft(*f, mode), 3) <= TOL[dtype]
+    gy = W.quantise(np.random.default_rng(5).standard_normal(inp.workload.shape), dtype)
+    dev = [to_device(a, dtype) for a in (inp.x1, inp.x2, inp.v, inp.k, inp.D, gy)]
+    got = H.backward(*dev, pad_mode=mode)
+    torch.cuda.synchronize()
+    bwd = oracle.backward_direct if mode == "centered" else oracle.backward_fft
+    for name, g, r in zip(("gx1", "gx2", "gv", "gk", "gD"), got, bwd(*f, W.storage_to_f64(gy, dtype), mode)):
+        assert tuple(g.shape) == tuple(r.shape)
+        assert rel_l2(from_device(g), r) <= TOL[dtype], name
+
+
+@pytest.mark.parametrize("mode", ["linear", "centered"])
+def test_lines_of_different_scales(mode):
+    """u and k of a line are transformed apart, and lines never share a transform: scales 1e6 apart between lines
+    and 1e4 between u and k change no line's relative error."""
+    inp = W.random_case(1, 4, (32, 32), mode, "f32", seed=77)
+    scale = np.array([1e-3, 1e3, 1.0, 1e2], dtype=np.float32).reshape(1, 4, 1, 1)
+    inp.x1 *= scale
+    inp.k *= np.float32(1e-4)
+    inp.D *= np.float32(1e-4)
+    assert per_line_worst(run_gpu(inp), oracle.conv_fft(*inp.as_f64(), mode), 4) <= TOL["f32"]
