@@ -31,7 +31,7 @@ struct Ra2D {
   using Row = RaRow<N>;
   static constexpr int L0 = P0 / 2, L1 = N;
   static constexpr int PITCH = Row::PITCH;
-  using Col = RaCol<P0, PITCH>;
+  using Col = RaCol<P0, Row>;
   static constexpr int NT = N * Col::T;         // one round of columns
   static constexpr int RPR = NT / Row::T;       // rows per round
   static constexpr int NR = (P0 + RPR - 1) / RPR;  // rounds of P0 rows (two for 128 columns points, else one)
@@ -84,7 +84,7 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
   const int rr = tid / TR, tr = tid % TR;                     // row of a round, lane of the row
   const int lane = tid & 63;
   const int col = (tid >> 6) * Col::CW + lane % Col::CW, tc = lane / Col::CW;  // column, lane of the column
-  float2* const cp = S + Col::slot(col);
+  float2* const cp = S + Row::slot(col);
   const int r = rr % L0;                          // data row of this lane
   const bool has_u = NR == 2 || rr < L0;          // with one round, lanes rr >= L0 take K's rows
   const size_t rb = (size_t)img * L0 * L1 + r * L1 + tr;  // its first point
@@ -259,7 +259,7 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
   const int rr = tid / TR, tr = tid % TR;
   const int lane = tid & 63;
   const int col = (tid >> 6) * Col::CW + lane % Col::CW, tc = lane / Col::CW;
-  float2* const cp = S + Col::slot(col);
+  float2* const cp = S + Row::slot(col);
   const int r = rr % L0;                        // data row of this lane
   const size_t rb = base + (size_t)r * L1 + tr;  // its first point
 

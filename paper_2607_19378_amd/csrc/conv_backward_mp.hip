@@ -1,6 +1,6 @@
 // Backward of the gated long convolution for 2D/3D grids whose spectra do
-// not fit in LDS: the multi-pass structure of the forward plan carried over
-// to three signals.
+// not fit in LDS, circular mode: the multi-pass structure of the forward plan
+// carried over to three signals (the other modes: conv_ra_mp.hip).
 //
 // With gy = dLoss/dy, u = x1 v and h = gy x2, the gradients are gx2 = gy z,
 // gu = k (*)^T h + D h, gk[m] = sum_n h[n] u[n - m], gx1 = gu v, gv = gu x1
@@ -13,7 +13,7 @@
 //              last axis; per-workgroup sums of h u for gD.
 //   axis1_fwd  (3D) forward along axis 1 for the three signals.
 //   core       along axis 0: forward transforms of U, K, H, the three
-//              products, inverse transforms, keep the L0 cropped rows; Z, GU,
+//              products, inverse transforms; Z, GU,
 //              GK overwrite U, K, H.
 //   axis1_inv  (3D) inverse along axis 1 for the three signals.
 //   rows_inv   inverse along the last axis, two real rows per complex
@@ -65,7 +65,7 @@ struct In5 {
   float4 a, b, k, g, e;
 };
 
-template <int PL, bool CIRC, typename TS>
+template <int PL, typename TS>
 __global__ void __launch_bounds__(256)
     mpb_rows_fwd(const TS* __restrict__ x1, const TS* __restrict__ v, const TS* __restrict__ k,
                  const TS* __restrict__ gy, const TS* __restrict__ x2, float2* __restrict__ ws,
@@ -73,9 +73,8 @@ __global__ void __launch_bounds__(256)
                  int64_t half, int64_t per_line) {
   using Cf = BRowsCfg<PL>;
   constexpr int ML = Cf::ML, HP = Cf::HP, E = Cf::E, T = Cf::T, NT = Cf::NT, RPW = Cf::RPW;
-  constexpr int LL = CIRC ? PL : PL / 2;
+  constexpr int LL = PL;
   constexpr int H = ML + 1;
-  constexpr int MNZ = (LL + 1) / 2;
   __shared__ float2 S[3][RPW * HP];  // u, k, h rows
   __shared__ float2 twl[imax(1, PassTw<ML, E>::kCount)];
   __shared__ float red[NT / 64];
@@ -154,7 +153,7 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int m = t + T * e;
-      w[e] = (act && (CIRC || m < MNZ)) ? row[m] : czero();
+      w[e] = act ? row[m] : czero();
     }
     BlockFFT<ML, E, false>::run(w, t, ScrS<1>{row}, act, twl);
     if (act) {
@@ -211,22 +210,21 @@ __global__ void __launch_bounds__(256)
 // three column lines of a lane stay in registers; the LDS tile is only the
 // exchange scratch.
 // ---------------------------------------------------------------------------
-template <int P0, bool CIRC>
+template <int P0>
 struct BCoreCfg {
   static constexpr int NT = kTileNT;
   static constexpr int TL = mp_tl(P0, 1, kTileKB);
   static constexpr int E = mp_e(P0, TL, NT);
   static constexpr int T = P0 / E;
   static constexpr int TLP = TL + 1;
-  static constexpr int L0 = CIRC ? P0 : P0 / 2;
 };
 
-template <int P0, bool CIRC>
+template <int P0>
 __global__ void __launch_bounds__(kTileNT)
     mpb_core(float2* __restrict__ ws, const void* __restrict__ Dp, int dbf16, int64_t line0, int C, int ncols,
              int HS, int H, int64_t half, int64_t per_line, float scale) {
-  using Cf = BCoreCfg<P0, CIRC>;
-  constexpr int TL = Cf::TL, TLP = Cf::TLP, E = Cf::E, T = Cf::T, NT = Cf::NT, L0 = Cf::L0;
+  using Cf = BCoreCfg<P0>;
+  constexpr int TL = Cf::TL, TLP = Cf::TLP, E = Cf::E, T = Cf::T, NT = Cf::NT;
   __shared__ float2 tile[P0 * TLP];
   __shared__ float2 twl[imax(1, PassTw<P0, E>::kCount)];
   const int ntile = (ncols + TL - 1) / TL;
@@ -248,10 +246,9 @@ __global__ void __launch_bounds__(kTileNT)
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int n = t + T * e;
-    const bool ld = cv && (CIRC || n < L0);
-    wu[e] = ld ? uc[(int64_t)n * ncols] : czero();
-    wk[e] = ld ? uc[half + (int64_t)n * ncols] : czero();
-    wh[e] = ld ? uc[2 * half + (int64_t)n * ncols] : czero();
+    wu[e] = cv ? uc[(int64_t)n * ncols] : czero();
+    wk[e] = cv ? uc[half + (int64_t)n * ncols] : czero();
+    wh[e] = cv ? uc[2 * half + (int64_t)n * ncols] : czero();
   }
   BlockFFT<P0, E, false>::run(wu, t, sc, act, twl);
   BlockFFT<P0, E, false>::run(wk, t, sc, act, twl);
@@ -271,11 +268,9 @@ __global__ void __launch_bounds__(kTileNT)
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int n = t + T * e;
-      if (CIRC || n < L0) {
-        uc[(int64_t)n * ncols] = wu[e];
-        uc[half + (int64_t)n * ncols] = wk[e];
-        uc[2 * half + (int64_t)n * ncols] = wh[e];
-      }
+      uc[(int64_t)n * ncols] = wu[e];
+      uc[half + (int64_t)n * ncols] = wk[e];
+      uc[2 * half + (int64_t)n * ncols] = wh[e];
     }
   }
 }
@@ -294,7 +289,7 @@ struct BRowsInvCfg {
   static constexpr int PPW = imax(1, imin(NT / T, (48 * 1024) / (3 * PRP * 8)));  // pairs per workgroup
 };
 
-template <int PL, bool CIRC, typename TS>
+template <int PL, typename TS>
 __global__ void __launch_bounds__(256)
     mpb_rows_inv(const float2* __restrict__ ws, const TS* __restrict__ x1, const TS* __restrict__ v,
                  const TS* __restrict__ gy, TS* __restrict__ gx1, TS* __restrict__ gx2, TS* __restrict__ gv,
@@ -302,7 +297,7 @@ __global__ void __launch_bounds__(256)
                  int64_t per_line) {
   using Cf = BRowsInvCfg<PL>;
   constexpr int H = Cf::H, PRP = Cf::PRP, E = Cf::E, T = Cf::T, NT = Cf::NT, PPW = Cf::PPW;
-  constexpr int LL = CIRC ? PL : PL / 2;
+  constexpr int LL = PL;
   constexpr int ML = PL / 2;
   __shared__ float2 reg[3][PPW * PRP];  // z, gu, gk pair regions
   __shared__ float2 twl[imax(1, PassTw<PL, E>::kCount)];
@@ -371,7 +366,7 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const int n = t + T * e;
-        if (CIRC || n < LL) R[n] = w[e];
+        R[n] = w[e];
       }
     }
   }
@@ -474,11 +469,9 @@ hipError_t b_rows_fwd(const MpbLaunch& L) {
   (const TS*)a.x1, (const TS*)a.v, (const TS*)a.k, (const TS*)L.b->gy, (const TS*)a.x2, L.ws, L.b->partial, \
       L.line0, L.g.rows, rpw, L.g.L1, L.g.P1, L.g.HS, L.g.half, L.per
   if (a.bf16) {
-    if (a.circular) hipLaunchKernelGGL((mpb_rows_fwd<PL, true, uint16_t>), grid, dim3(256), 0, L.s, HY_ARGS(uint16_t));
-    else hipLaunchKernelGGL((mpb_rows_fwd<PL, false, uint16_t>), grid, dim3(256), 0, L.s, HY_ARGS(uint16_t));
+    hipLaunchKernelGGL((mpb_rows_fwd<PL, uint16_t>), grid, dim3(256), 0, L.s, HY_ARGS(uint16_t));
   } else {
-    if (a.circular) hipLaunchKernelGGL((mpb_rows_fwd<PL, true, float>), grid, dim3(256), 0, L.s, HY_ARGS(float));
-    else hipLaunchKernelGGL((mpb_rows_fwd<PL, false, float>), grid, dim3(256), 0, L.s, HY_ARGS(float));
+    hipLaunchKernelGGL((mpb_rows_fwd<PL, float>), grid, dim3(256), 0, L.s, HY_ARGS(float));
   }
 #undef HY_ARGS
   return hipGetLastError();
@@ -489,13 +482,8 @@ hipError_t b_axis1(const MpbLaunch& L) {
   constexpr int TL = TileCfg<P1, 3>::TL;
   const int ntile = (L.g.H + TL - 1) / TL;
   const dim3 grid((unsigned)((int64_t)L.nl * L.g.L0 * ntile));
-  const int nload = INV ? P1 : L.g.L1;
-  if (L.b->f.circular)
-    hipLaunchKernelGGL((mp_axis1<P1, true, INV, 3>), grid, dim3(kTileNT), 0, L.s, L.ws, L.g.H, L.g.HS, L.g.L0,
-                       L.g.half, L.per, nload, (int64_t)0);
-  else
-    hipLaunchKernelGGL((mp_axis1<P1, false, INV, 3>), grid, dim3(kTileNT), 0, L.s, L.ws, L.g.H, L.g.HS, L.g.L0,
-                       L.g.half, L.per, nload, (int64_t)0);
+  hipLaunchKernelGGL((mp_axis1<P1, INV, 3>), grid, dim3(kTileNT), 0, L.s, L.ws, L.g.H, L.g.HS, L.g.L0, L.g.half,
+                     L.per, (int64_t)0);
   return hipGetLastError();
 }
 template <int P1>
@@ -507,17 +495,10 @@ template <int P0>
 hipError_t b_core(const MpbLaunch& L) {
   const FftConvArgs& a = L.b->f;
   const int ncols = L.g.P1 * L.g.HS;
-  if (a.circular) {
-    constexpr int TL = BCoreCfg<P0, true>::TL;
-    const dim3 grid((unsigned)((int64_t)L.nl * ((ncols + TL - 1) / TL)));
-    hipLaunchKernelGGL((mpb_core<P0, true>), grid, dim3(kTileNT), 0, L.s, L.ws, a.D, (int)a.bf16, L.line0,
-                       (int)a.C, ncols, L.g.HS, L.g.H, L.g.half, L.per, L.scale);
-  } else {
-    constexpr int TL = BCoreCfg<P0, false>::TL;
-    const dim3 grid((unsigned)((int64_t)L.nl * ((ncols + TL - 1) / TL)));
-    hipLaunchKernelGGL((mpb_core<P0, false>), grid, dim3(kTileNT), 0, L.s, L.ws, a.D, (int)a.bf16, L.line0,
-                       (int)a.C, ncols, L.g.HS, L.g.H, L.g.half, L.per, L.scale);
-  }
+  constexpr int TL = BCoreCfg<P0>::TL;
+  const dim3 grid((unsigned)((int64_t)L.nl * ((ncols + TL - 1) / TL)));
+  hipLaunchKernelGGL((mpb_core<P0>), grid, dim3(kTileNT), 0, L.s, L.ws, a.D, (int)a.bf16, L.line0, (int)a.C, ncols,
+                     L.g.HS, L.g.H, L.g.half, L.per, L.scale);
   return hipGetLastError();
 }
 
@@ -530,11 +511,9 @@ hipError_t b_rows_inv(const MpbLaunch& L) {
   L.ws, (const TS*)a.x1, (const TS*)a.v, (const TS*)L.b->gy, (TS*)L.b->gx1, (TS*)L.b->gx2, (TS*)L.b->gv, \
       (TS*)L.b->gk, L.line0, L.nl, L.g.rows, L.g.L1, L.g.P1, L.g.HS, L.g.half, L.per
   if (a.bf16) {
-    if (a.circular) hipLaunchKernelGGL((mpb_rows_inv<PL, true, uint16_t>), grid, dim3(256), 0, L.s, HY_ARGS(uint16_t));
-    else hipLaunchKernelGGL((mpb_rows_inv<PL, false, uint16_t>), grid, dim3(256), 0, L.s, HY_ARGS(uint16_t));
+    hipLaunchKernelGGL((mpb_rows_inv<PL, uint16_t>), grid, dim3(256), 0, L.s, HY_ARGS(uint16_t));
   } else {
-    if (a.circular) hipLaunchKernelGGL((mpb_rows_inv<PL, true, float>), grid, dim3(256), 0, L.s, HY_ARGS(float));
-    else hipLaunchKernelGGL((mpb_rows_inv<PL, false, float>), grid, dim3(256), 0, L.s, HY_ARGS(float));
+    hipLaunchKernelGGL((mpb_rows_inv<PL, float>), grid, dim3(256), 0, L.s, HY_ARGS(float));
   }
 #undef HY_ARGS
   return hipGetLastError();
@@ -585,7 +564,7 @@ int64_t backward_mp_partials_per_line(const FftConvArgs& a) {
 
 hipError_t launch_backward_mp(const FftConvBwdArgs& b, int64_t line0, int64_t nl, void* ws, hipStream_t s) {
   const FftConvArgs& a = b.f;
-  if (!multipass_supported(a) || nl < 1 || line0 < 0 || line0 + nl > a.lines) return hipErrorInvalidValue;
+  if (!multipass_supported(a) || !a.circular || nl < 1 || line0 < 0 || line0 + nl > a.lines) return hipErrorInvalidValue;
   MpbLaunch L;
   L.b = &b;
   L.g = mp_geom(a);

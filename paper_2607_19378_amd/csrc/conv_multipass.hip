@@ -21,8 +21,6 @@
 // contiguous run of TL complex values and no explicit transpose is stored.
 // Tiles are sized so that two 512-lane (core pass: up to four 256-lane)
 // workgroups share a CU.
-#include <type_traits>
-
 #include "multipass.hpp"
 
 namespace hyenand {
@@ -42,16 +40,15 @@ struct RowsCfg {
   static constexpr int RPW = imax(1, imin(NT / (2 * T), (36 * 1024) / (2 * HP * 8)));  // rows per workgroup
 };
 
-template <int PL, bool CIRC, typename TS, bool ACT = false>
+template <int PL, typename TS, bool ACT = false>
 __global__ void __launch_bounds__(256)
     mp_rows_fwd(const TS* __restrict__ x1, const TS* __restrict__ v, const TS* __restrict__ k,
                 float2* __restrict__ ws, int64_t line0, int nlines, int rows, int L1, int P1, int HS,
-                int64_t half, int64_t per_line, int kC, int nsig, ActIn ain, int C) {
+                int64_t half, int64_t per_line, int kC, ActIn ain, int C) {
   using Cf = RowsCfg<PL>;
   constexpr int ML = Cf::ML, HP = Cf::HP, E = Cf::E, T = Cf::T, NT = Cf::NT, RPW = Cf::RPW;
-  constexpr int LL = CIRC ? PL : PL / 2;
+  constexpr int LL = PL;
   constexpr int H = ML + 1;
-  constexpr int MNZ = (LL + 1) / 2;
   __shared__ float2 Ur[RPW * HP];
   __shared__ float2 Kr[RPW * HP];
   __shared__ float2 twl[imax(1, PassTw<ML, E>::kCount)];
@@ -85,7 +82,7 @@ __global__ void __launch_bounds__(256)
             if (i / LL < nrow) {
               z.a = ld4(x1 + gbase + i);
               z.b = ld4(v + gbase + i);
-              z.k = nsig > 1 ? ld4(k + kidx(gbase + i)) : make_float4(0.f, 0.f, 0.f, 0.f);
+              z.k = ld4(k + kidx(gbase + i));
               if constexpr (ACT) {  // the operator's inner gate; a line's points are contiguous
                 const size_t e = gbase + i;
                 const int64_t line = (int64_t)(e / per);
@@ -118,7 +115,7 @@ __global__ void __launch_bounds__(256)
               const size_t e = gbase + i;
               const int64_t line = (int64_t)(e / per);
               const float u = line_gates<ACT, TS>(ain, line, C).u1(ld1(x1 + e), ld1(v + e), (int64_t)(e - (size_t)line * per));
-              z = make_float2(u, nsig > 1 ? ld1(k + kidx(e)) : 0.f);
+              z = make_float2(u, ld1(k + kidx(e)));
             }
             return z;
           },
@@ -138,13 +135,13 @@ __global__ void __launch_bounds__(256)
   for (int l0 = 0; l0 < NLINE; l0 += NT / T) {
     const int l = l0 + tid % (NT / T), t = tid / (NT / T);
     const int r = l >> 1;
-    const bool act = l < NLINE && r < nrow && (l & 1) < nsig;
+    const bool act = l < NLINE && r < nrow;
     float2* row = ((l & 1) ? Kr : Ur) + (act ? r : 0) * HP;
     float2 w[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int m = t + T * e;
-      w[e] = (act && (CIRC || m < MNZ)) ? row[m] : czero();
+      w[e] = act ? row[m] : czero();
     }
     BlockFFT<ML, E, false>::run(w, t, ScrS<1>{row}, act, twl);
     if (act) {
@@ -159,7 +156,7 @@ __global__ void __launch_bounds__(256)
   constexpr int NPOST = NLINE * (ML / 2 + 1);
   for (int it = tid; it < NPOST; it += NT) {
     const int l = it % NLINE, g = it / NLINE;
-    if ((l >> 1) < nrow && (l & 1) < nsig) {
+    if ((l >> 1) < nrow) {
       float2* row = ((l & 1) ? Kr : Ur) + (l >> 1) * HP;
       float2 xa, xb;
       r2c_pair(row[g], row[(ML - g) & (ML - 1)], twiddle<ilog2(PL), false>(g), xa, xb);
@@ -181,99 +178,7 @@ __global__ void __launch_bounds__(256)
         if (r < nrow) {
           float2* U = ws + roff[r] + f;
           U[0] = make_float2(z.x, z.y);
-          if (nsig > 1) U[half] = make_float2(z.z, z.w);
-        }
-      });
-}
-
-// ---------------------------------------------------------------------------
-// rows of a centered kernel: K holds all P0 x P1 grid rows, each a full real
-// row of PL points gathered from the (2 L0 - 1) x (2 L1 - 1) x (2 LL - 1)
-// centered points (grid index g of an axis holds displacement g or g - 2L);
-// real-to-complex along the last axis, stored at koff + row * HS.
-// ---------------------------------------------------------------------------
-template <int PL, typename TS>
-__global__ void __launch_bounds__(256)
-    mp_rows_kc(const TS* __restrict__ k, float2* __restrict__ ws, int64_t line0, int nlines, int krows, int L0,
-               int L1, int P1, int HS, int64_t koff, int64_t per_line, int kC) {
-  using Cf = RowsCfg<PL>;
-  constexpr int ML = Cf::ML, HP = Cf::HP, E = Cf::E, T = Cf::T, NT = Cf::NT;
-  constexpr int RPW = 2 * Cf::RPW;  // one signal: the two-signal pass's LDS holds twice the rows
-  constexpr int LL = PL / 2;
-  constexpr int H = ML + 1;
-  __shared__ float2 Kr[RPW * HP];
-  __shared__ float2 twl[imax(1, PassTw<ML, E>::kCount)];
-  const int64_t total_rows = (int64_t)nlines * krows;
-  const int64_t row0 = (int64_t)blockIdx.x * RPW;
-  const int nrow = (int)((total_rows - row0) < RPW ? (total_rows - row0) : RPW);
-  const int tid = threadIdx.x;
-  PassTw<ML, E>::fill(twl, tid, NT);
-  const int K1 = 2 * L1 - 1;
-  constexpr int K2 = 2 * LL - 1;
-  const int64_t kpts = (int64_t)(2 * L0 - 1) * K1 * K2;
-
-  // gather the grid points 2m, 2m + 1 of every row
-  batched_copy<RPW * ML, NT, 8>(
-      tid,
-      [&](int i) {
-        const int r = i / ML, m = i - r * ML;
-        float2 z = czero();
-        if (r < nrow) {
-          const int64_t gr = row0 + r;
-          const int64_t line = gr / krows;
-          const int rr = (int)(gr - line * krows);
-          const int j0 = centered_index(rr / P1, L0, 2 * L0), j1 = centered_index(rr % P1, L1, 2 * L1);
-          if (j0 >= 0 && j1 >= 0) {
-            const TS* kr = k + (size_t)k_line(line0 + line, kC) * kpts + ((size_t)j0 * K1 + j1) * K2;
-            const int ja = centered_index(2 * m, LL, PL), jb = centered_index(2 * m + 1, LL, PL);
-            z = make_float2(ja >= 0 ? ld1(kr + ja) : 0.f, jb >= 0 ? ld1(kr + jb) : 0.f);
-          }
-        }
-        return z;
-      },
-      [&](int i, float2 z) {
-        const int r = i / ML, m = i - r * ML;
-        Kr[r * HP + m] = z;
-      });
-  __syncthreads();
-
-  for (int l0 = 0; l0 < RPW; l0 += NT / T) {
-    const int l = l0 + tid % (NT / T), t = tid / (NT / T);
-    const bool act = l < RPW && l < nrow;
-    float2* row = Kr + (act ? l : 0) * HP;
-    float2 w[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) w[e] = act ? row[t + T * e] : czero();
-    BlockFFT<ML, E, false>::run(w, t, ScrS<1>{row}, act, twl);
-    if (act) {
-#pragma unroll
-      for (int e = 0; e < E; ++e) row[t + T * e] = w[e];
-    }
-  }
-  __syncthreads();
-
-  constexpr int NPOST = RPW * (ML / 2 + 1);
-  for (int it = tid; it < NPOST; it += NT) {
-    const int l = it % RPW, g = it / RPW;
-    if (l < nrow) {
-      float2* row = Kr + l * HP;
-      float2 xa, xb;
-      r2c_pair(row[g], row[(ML - g) & (ML - 1)], twiddle<ilog2(PL), false>(g), xa, xb);
-      row[g] = xa;
-      row[ML - g] = xb;
-    }
-  }
-  __syncthreads();
-
-  batched_copy<RPW * H, NT, 8>(
-      tid, [&](int i) { return Kr[(i / H) * HP + (i % H)]; },
-      [&](int i, float2 z) {
-        const int r = i / H, f = i - r * H;
-        if (r < nrow) {
-          const int64_t gr = row0 + r;
-          const int64_t line = gr / krows;
-          const int rr = (int)(gr - line * krows);
-          ws[line * per_line + koff + (int64_t)rr * HS + f] = z;
+          U[half] = make_float2(z.z, z.w);
         }
       });
 }
@@ -290,22 +195,21 @@ __global__ void __launch_bounds__(256)
 // lane transforms the padding slots; else tiles run over every slot and the
 // padding lanes idle.
 // ---------------------------------------------------------------------------
-template <int P0, bool CIRC>
+template <int P0>
 struct CoreCfg {
   static constexpr int NT = mp_core_nt(P0);
   static constexpr int TL = mp_tl(P0, 1, mp_core_small(P0) ? kTileKB / 2 : kTileKB);
   static constexpr int E = mp_e(P0, TL, NT);
   static constexpr int T = P0 / E;
   static constexpr int TLP = TL + 1;
-  static constexpr int L0 = CIRC ? P0 : P0 / 2;
 };
 
-template <int P0, bool CIRC>
+template <int P0>
 __global__ void __launch_bounds__(mp_core_nt(P0))
     mp_core(float2* __restrict__ ws, const void* __restrict__ Dp, int dbf16, int64_t line0, int C,
-            int ncols, int HS, int H, int64_t half, int64_t per_line, float scale, int krows, int nyq) {
-  using Cf = CoreCfg<P0, CIRC>;
-  constexpr int TL = Cf::TL, TLP = Cf::TLP, E = Cf::E, T = Cf::T, NT = Cf::NT, L0 = Cf::L0;
+            int ncols, int HS, int H, int64_t half, int64_t per_line, float scale, int nyq) {
+  using Cf = CoreCfg<P0>;
+  constexpr int TL = Cf::TL, TLP = Cf::TLP, E = Cf::E, T = Cf::T, NT = Cf::NT;
   __shared__ float2 tile[P0 * TLP];
   __shared__ float2 twl[imax(1, PassTw<P0, E>::kCount)];
   const int vrows = ncols / HS;
@@ -349,12 +253,12 @@ __global__ void __launch_bounds__(mp_core_nt(P0))
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int n = t + T * e;
-    wu[e] = (cv && (CIRC || n < L0)) ? uc[(int64_t)n * ncols] : czero();
+    wu[e] = cv ? uc[(int64_t)n * ncols] : czero();
   }
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int n = t + T * e;
-    wk[e] = (cv && (CIRC || n < krows)) ? kc[(int64_t)n * ncols] : czero();
+    wk[e] = cv ? kc[(int64_t)n * ncols] : czero();
   }
   BlockFFT<P0, E, false>::run(wu, t, sc, act, twl);
   BlockFFT<P0, E, false>::run(wk, t, sc, act, twl);
@@ -365,7 +269,7 @@ __global__ void __launch_bounds__(mp_core_nt(P0))
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int n = t + T * e;
-      if (CIRC || n < L0) uc[(int64_t)n * ncols] = wu[e];
+      uc[(int64_t)n * ncols] = wu[e];
     }
   }
 }
@@ -386,13 +290,13 @@ struct RowsInvCfg {
   static constexpr int PPW = imax(1, imin(NT / T, (48 * 1024) / (PRP * 8)));  // pairs per workgroup
 };
 
-template <int PL, bool CIRC, typename TS, bool ACT = false>
+template <int PL, typename TS, bool ACT = false>
 __global__ void __launch_bounds__(256)
     mp_rows_inv(const float2* __restrict__ ws, const TS* __restrict__ x2, TS* __restrict__ y, int64_t line0,
                 int nlines, int rows, int L1, int P1, int HS, int64_t per_line) {
   using Cf = RowsInvCfg<PL>;
   constexpr int H = Cf::H, PRP = Cf::PRP, E = Cf::E, T = Cf::T, NT = Cf::NT, PPW = Cf::PPW;
-  constexpr int LL = CIRC ? PL : PL / 2;
+  constexpr int LL = PL;
   constexpr int ML = PL / 2;
   __shared__ float2 reg[PPW * PRP];
   __shared__ float2 twl[imax(1, PassTw<PL, E>::kCount)];
@@ -451,7 +355,7 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const int n = t + T * e;
-        if (CIRC || n < LL) *sc(n) = w[e];
+        *sc(n) = w[e];
       }
     }
   }
@@ -508,61 +412,35 @@ hipError_t rows_fwd(const MpLaunch& L) {
   const int64_t total = (int64_t)L.nl * L.g.rows;
   const dim3 grid((unsigned)((total + RowsCfg<PL>::RPW - 1) / RowsCfg<PL>::RPW));
   const FftConvArgs& a = *L.a;
-  const int nsig = L.g.kc ? 1 : 2;  // a centered K has rows of its own (rows_kc)
 #define HY_ARGS(TS) (const TS*)a.x1, (const TS*)a.v, (const TS*)a.k, L.ws, L.line0, L.nl, L.g.rows, L.g.L1, L.g.P1, \
-                    L.g.HS, L.g.half, L.per, a.kC, nsig, a.act_in, (int)a.C
-#define HY_LAUNCH(CI, TS)                                                                                     \
-  if (a.act) hipLaunchKernelGGL((mp_rows_fwd<PL, CI, TS, true>), grid, dim3(256), 0, L.s, HY_ARGS(TS)); \
-  else hipLaunchKernelGGL((mp_rows_fwd<PL, CI, TS, false>), grid, dim3(256), 0, L.s, HY_ARGS(TS));
+                    L.g.HS, L.g.half, L.per, a.kC, a.act_in, (int)a.C
+#define HY_LAUNCH(TS)                                                                                     \
+  if (a.act) hipLaunchKernelGGL((mp_rows_fwd<PL, TS, true>), grid, dim3(256), 0, L.s, HY_ARGS(TS)); \
+  else hipLaunchKernelGGL((mp_rows_fwd<PL, TS, false>), grid, dim3(256), 0, L.s, HY_ARGS(TS));
   if (a.bf16) {
-    if (a.circular) { HY_LAUNCH(true, uint16_t) } else { HY_LAUNCH(false, uint16_t) }
+    HY_LAUNCH(uint16_t)
   } else {
-    if (a.circular) { HY_LAUNCH(true, float) } else { HY_LAUNCH(false, float) }
+    HY_LAUNCH(float)
   }
 #undef HY_LAUNCH
 #undef HY_ARGS
   return hipGetLastError();
 }
 
-template <int PL>
-hipError_t rows_kc(const MpLaunch& L) {
-  const FftConvArgs& a = *L.a;
-  constexpr int RPW = 2 * RowsCfg<PL>::RPW;
-  const int krows = L.g.P0 * L.g.P1;
-  const int64_t total = (int64_t)L.nl * krows;
-  const dim3 grid((unsigned)((total + RPW - 1) / RPW));
-  if (a.bf16)
-    hipLaunchKernelGGL((mp_rows_kc<PL, uint16_t>), grid, dim3(256), 0, L.s, (const uint16_t*)a.k, L.ws, L.line0, L.nl,
-                       krows, L.g.L0, L.g.L1, L.g.P1, L.g.HS, L.g.half, L.per, a.kC);
-  else
-    hipLaunchKernelGGL((mp_rows_kc<PL, float>), grid, dim3(256), 0, L.s, (const float*)a.k, L.ws, L.line0, L.nl,
-                       krows, L.g.L0, L.g.L1, L.g.P1, L.g.HS, L.g.half, L.per, a.kC);
-  return hipGetLastError();
-}
-
 template <int P1, bool INV, int NS>
-hipError_t axis1_sig(const MpLaunch& L, int planes, int nload, int64_t sig_off) {
+hipError_t axis1_sig(const MpLaunch& L, int planes, int64_t sig_off) {
   constexpr int TL = TileCfg<P1, NS>::TL;
   const int ntile = (L.g.H + TL - 1) / TL;
   const dim3 grid((unsigned)((int64_t)L.nl * planes * ntile));
-  if (L.a->circular)
-    hipLaunchKernelGGL((mp_axis1<P1, true, INV, NS>), grid, dim3(kTileNT), 0, L.s, L.ws, L.g.H, L.g.HS, planes,
-                       L.g.half, L.per, nload, sig_off);
-  else
-    hipLaunchKernelGGL((mp_axis1<P1, false, INV, NS>), grid, dim3(kTileNT), 0, L.s, L.ws, L.g.H, L.g.HS, planes,
-                       L.g.half, L.per, nload, sig_off);
+  hipLaunchKernelGGL((mp_axis1<P1, INV, NS>), grid, dim3(kTileNT), 0, L.s, L.ws, L.g.H, L.g.HS, planes,
+                       L.g.half, L.per, sig_off);
   return hipGetLastError();
 }
 
-// forward: U and K in one pass (a centered K, with P0 planes of P1 nonzero
-// rows, in a pass of its own); inverse: Y
+// forward: U and K in one pass; inverse: Y
 template <int P1, bool INV>
 hipError_t axis1(const MpLaunch& L) {
-  if (INV) return axis1_sig<P1, true, 1>(L, L.g.L0, P1, 0);
-  if (!L.g.kc) return axis1_sig<P1, false, 2>(L, L.g.L0, L.g.L1, 0);
-  hipError_t e = axis1_sig<P1, false, 1>(L, L.g.L0, L.g.L1, 0);
-  if (e != hipSuccess) return e;
-  return axis1_sig<P1, false, 1>(L, L.g.P0, P1, L.g.half);
+  return INV ? axis1_sig<P1, true, 1>(L, L.g.L0, 0) : axis1_sig<P1, false, 2>(L, L.g.L0, 0);
 }
 template <int P1>
 hipError_t axis1_fwd(const MpLaunch& L) { return axis1<P1, false>(L); }
@@ -573,18 +451,12 @@ template <int P0>
 hipError_t core(const MpLaunch& L) {
   const FftConvArgs& a = *L.a;
   const int ncols = L.g.P1 * L.g.HS;
-  auto launch = [&](auto circ) {
-    constexpr bool CI = decltype(circ)::value;
-    constexpr int TL = CoreCfg<P0, CI>::TL;
-    const int rows = ncols / L.g.HS;
-    const int nyq = rows > 1 && (L.g.H - 1) % TL == 0 && L.g.H - 1 >= TL;
-    const int64_t ntile = nyq ? (int64_t)rows * ((L.g.H - 1) / TL) + (rows + TL - 1) / TL : (ncols + TL - 1) / TL;
-    hipLaunchKernelGGL((mp_core<P0, CI>), dim3((unsigned)(L.nl * ntile)), dim3(CoreCfg<P0, CI>::NT), 0, L.s, L.ws,
-                       a.D, (int)a.bf16, L.line0, (int)a.C, ncols, L.g.HS, L.g.H, L.g.half, L.per, L.scale,
-                       L.g.krows0, nyq);
-  };
-  if (a.circular) launch(std::true_type{});
-  else launch(std::false_type{});
+  constexpr int TL = CoreCfg<P0>::TL;
+  const int rows = ncols / L.g.HS;
+  const int nyq = rows > 1 && (L.g.H - 1) % TL == 0 && L.g.H - 1 >= TL;
+  const int64_t ntile = nyq ? (int64_t)rows * ((L.g.H - 1) / TL) + (rows + TL - 1) / TL : (ncols + TL - 1) / TL;
+  hipLaunchKernelGGL((mp_core<P0>), dim3((unsigned)(L.nl * ntile)), dim3(CoreCfg<P0>::NT), 0, L.s, L.ws, a.D,
+                     (int)a.bf16, L.line0, (int)a.C, ncols, L.g.HS, L.g.H, L.g.half, L.per, L.scale, nyq);
   return hipGetLastError();
 }
 
@@ -594,13 +466,13 @@ hipError_t rows_inv(const MpLaunch& L) {
   const dim3 grid((unsigned)((pairs + RowsInvCfg<PL>::PPW - 1) / RowsInvCfg<PL>::PPW));
   const FftConvArgs& a = *L.a;
 #define HY_ARGS(TS) L.ws, (const TS*)a.x2, (TS*)a.y, L.line0, L.nl, L.g.rows, L.g.L1, L.g.P1, L.g.HS, L.per
-#define HY_LAUNCH(CI, TS)                                                                                     \
-  if (a.act) hipLaunchKernelGGL((mp_rows_inv<PL, CI, TS, true>), grid, dim3(256), 0, L.s, HY_ARGS(TS)); \
-  else hipLaunchKernelGGL((mp_rows_inv<PL, CI, TS, false>), grid, dim3(256), 0, L.s, HY_ARGS(TS));
+#define HY_LAUNCH(TS)                                                                                     \
+  if (a.act) hipLaunchKernelGGL((mp_rows_inv<PL, TS, true>), grid, dim3(256), 0, L.s, HY_ARGS(TS)); \
+  else hipLaunchKernelGGL((mp_rows_inv<PL, TS, false>), grid, dim3(256), 0, L.s, HY_ARGS(TS));
   if (a.bf16) {
-    if (a.circular) { HY_LAUNCH(true, uint16_t) } else { HY_LAUNCH(false, uint16_t) }
+    HY_LAUNCH(uint16_t)
   } else {
-    if (a.circular) { HY_LAUNCH(true, float) } else { HY_LAUNCH(false, float) }
+    HY_LAUNCH(float)
   }
 #undef HY_LAUNCH
 #undef HY_ARGS
@@ -623,7 +495,6 @@ hipError_t rows_inv(const MpLaunch& L) {
   }
 
 hipError_t d_rows_fwd(int P, const MpLaunch& L) { HY_SIZE_SWITCH(P, rows_fwd, L) }
-hipError_t d_rows_kc(int P, const MpLaunch& L) { HY_SIZE_SWITCH(P, rows_kc, L) }
 hipError_t d_axis1_fwd(int P, const MpLaunch& L) { HY_SIZE_SWITCH(P, axis1_fwd, L) }
 hipError_t d_core(int P, const MpLaunch& L) { HY_SIZE_SWITCH(P, core, L) }
 hipError_t d_axis1_inv(int P, const MpLaunch& L) { HY_SIZE_SWITCH(P, axis1_inv, L) }
@@ -631,6 +502,8 @@ hipError_t d_rows_inv(int P, const MpLaunch& L) { HY_SIZE_SWITCH(P, rows_inv, L)
 
 }  // namespace
 
+// the circular grids run here, and the sizes that the workspace queries of the
+// others report are these passes'
 bool multipass_supported(const FftConvArgs& a) {
   if (a.ndim != 2 && a.ndim != 3) return false;
   for (int d = 0; d < a.ndim; ++d)
@@ -644,7 +517,7 @@ size_t multipass_bytes_per_line(const FftConvArgs& a) {
 }
 
 hipError_t launch_multipass(const FftConvArgs& a, int64_t line0, int64_t nl, void* ws, hipStream_t s) {
-  if (!multipass_supported(a) || nl < 1 || line0 < 0 || line0 + nl > a.lines) return hipErrorInvalidValue;
+  if (!multipass_supported(a) || !a.circular || nl < 1 || line0 < 0 || line0 + nl > a.lines) return hipErrorInvalidValue;
   MpLaunch L;
   L.a = &a;
   L.g = mp_geom(a);
@@ -662,7 +535,6 @@ hipError_t launch_multipass(const FftConvArgs& a, int64_t line0, int64_t nl, voi
     return launch_slab3d(a, line0, nl, ws, true, s);
   }
   if ((e = d_rows_fwd(L.g.PL, L)) != hipSuccess) return e;
-  if (L.g.kc && (e = d_rows_kc(L.g.PL, L)) != hipSuccess) return e;
   if (three && (e = d_axis1_fwd(L.g.P1, L)) != hipSuccess) return e;
   if ((e = d_core(L.g.P0, L)) != hipSuccess) return e;
   if (three && (e = d_axis1_inv(L.g.P1, L)) != hipSuccess) return e;

@@ -1,4 +1,4 @@
-// Three-pass plan for 3D grids whose planes fit in LDS (plan "slab3d"):
+// Three-pass plan for circular 3D grids whose planes fit in LDS (plan "slab3d"):
 //
 //   slab_fwd   one workgroup per (line, plane n0 < L0, signal u or k): stage
 //              the plane's L1 real rows, real-to-complex transform of every
@@ -7,10 +7,9 @@
 //              [L0][P1][HS] of the workspace;
 //   core       along axis 0 (the multi-pass core, conv_multipass.hip):
 //              forward U and K, gated product with the folded shortcut,
-//              inverse, keep the L0 cropped planes; Y overwrites U;
+//              inverse; Y overwrites U;
 //   slab_inv   one workgroup per (line, plane n0 < L0): axis-1 inverse of
-//              every bin column with the crop to n1 < L1, complex-to-real
-//              rows, crop, outer gate x2, store y.
+//              every bin column, complex-to-real rows, outer gate x2, store y.
 //
 // The two transforms of a plane stay on chip, so the spectra make one round
 // trip through the workspace per pass pair (the five-pass plan writes and
@@ -19,15 +18,9 @@
 // bins of every row, both real, share column 0 as DC + i Nyquist, so the
 // bin columns are P/2 complex columns.
 //
-// In linear mode the axis-1 transform of length P1 = 2 L1 has L1 nonzero
-// inputs: its even outputs are the length-L1 transform of the column and its
-// odd outputs the length-L1 transform of the column times exp(-2 pi i n /
-// P1) (the first radix-2 step of a zero-padded input), so both run in place
-// in the column's own L1 slots.  The inverse keeps the outputs n1 < L1 = P1/2
-// only: x[n] = E[n] + exp(2 pi i n / P1) O[n] with E, O the length-L1
-// inverses of the even and odd bins.  The axis-0 (core) transform is the
-// paper's middle kernel of its three-kernel 2D structure (appendix "2D FFT
-// Convolution"), carried to the third axis.
+// The axis-0 (core) transform is the paper's middle kernel of its three-kernel
+// 2D structure (appendix "2D FFT Convolution"), carried to the third axis.  The
+// non-circular volumes run on right-angle rows (conv_ra_slab.hip).
 #include <stdlib.h>
 #include <string.h>
 
@@ -37,36 +30,30 @@ namespace hyenand {
 
 namespace {
 
-template <int P, bool CIRC>
+template <int P>
 struct SlabCfg {
   static constexpr int ML = P / 2;             // packed row length (complex)
   static constexpr int HP = ML + 1;            // LDS row pitch (odd)
-  static constexpr int L1 = CIRC ? P : P / 2;  // nonzero rows of a plane
-  static constexpr int LL = L1;                // nonzero reals of a row
-  static constexpr int MNZ = (LL + 1) / 2;     // nonzero packed points of a row
+  static constexpr int L1 = P;                 // rows of a plane
+  static constexpr int LL = P;                 // reals of a row
   static constexpr int ER = imin(16, ML), TR = ML / ER;  // row transforms
-  static constexpr int NC = CIRC ? P : P / 2;            // column transform length
+  static constexpr int NC = P;                           // column transform length
   static constexpr int EC = imin(16, NC), TC = NC / EC;  // column transforms
   static constexpr int NT = imin(1024, imax(64, imax(L1 * TR, ML * TC)));
   static constexpr int kLdsBytes = L1 * HP * 8 + P * 8;
 };
 
-template <int P, bool CIRC>
-constexpr bool slab_fits() {
-  return SlabCfg<P, CIRC>::kLdsBytes <= 150 * 1024;
-}
-
 // the packed DC + i Nyquist bin pair of a row from its two bins
 __device__ __forceinline__ float2 pack_dc_nyq(float2 dc, float2 nyq) { return make_float2(dc.x - nyq.y, dc.y + nyq.x); }
 
 // ACT: the HyenaND operator's gates (x1, v, x2 hold q, kin, vin; see Gates)
-template <int P, bool CIRC, typename TS, bool ACT>
-__global__ void __launch_bounds__((SlabCfg<P, CIRC>::NT))
+template <int P, typename TS, bool ACT>
+__global__ void __launch_bounds__((SlabCfg<P>::NT))
     mp_slab_fwd(const TS* __restrict__ x1, const TS* __restrict__ v, const TS* __restrict__ k,
                 float2* __restrict__ ws, int64_t line0, int L0, int HS, int64_t half, int64_t per_line, int kC,
                 ActIn ain, int C) {
-  using Cf = SlabCfg<P, CIRC>;
-  constexpr int ML = Cf::ML, HP = Cf::HP, L1 = Cf::L1, LL = Cf::LL, MNZ = Cf::MNZ, NT = Cf::NT;
+  using Cf = SlabCfg<P>;
+  constexpr int ML = Cf::ML, HP = Cf::HP, L1 = Cf::L1, LL = Cf::LL, NT = Cf::NT;
   __shared__ float2 pl[L1 * HP];
   __shared__ float2 nq[P];  // column 0's spectrum (DC + i Nyquist)
   const int tid = threadIdx.x;
@@ -110,7 +97,7 @@ __global__ void __launch_bounds__((SlabCfg<P, CIRC>::NT))
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const int m = t + T * e;
-        w[e] = (act && (CIRC || m < MNZ)) ? row[m] : czero();
+        w[e] = act ? row[m] : czero();
       }
       BlockFFT<ML, E, false>::run(w, t, ScrS<1>{row}, act);
       if (act) {
@@ -173,39 +160,13 @@ __global__ void __launch_bounds__((SlabCfg<P, CIRC>::NT))
         if constexpr (kColUntangle) x[e] = act ? untangle_bin(row, cc, mc, twc) : czero();
         else x[e] = act ? row[cc] : czero();
       }
-      if constexpr (CIRC) {
-        BlockFFT<NC, E, false>::run(x, t, sc, act);
-        if (act) {
+      BlockFFT<NC, E, false>::run(x, t, sc, act);
+      if (act) {
 #pragma unroll
-          for (int e = 0; e < E; ++e) {
-            const int f1 = t + T * e;
-            if (cc == 0) nq[f1] = x[e];
-            else S[(int64_t)f1 * HS + cc] = x[e];
-          }
-        }
-      } else {
-        float2 xs[E];
-#pragma unroll
-        for (int e = 0; e < E; ++e) xs[e] = x[e];
-        BlockFFT<NC, E, false>::run(x, t, sc, act);  // even bins f1 = 2j
-        if (act) {
-#pragma unroll
-          for (int e = 0; e < E; ++e) {
-            const int f1 = 2 * (t + T * e);
-            if (cc == 0) nq[f1] = x[e];
-            else S[(int64_t)f1 * HS + cc] = x[e];
-          }
-        }
-#pragma unroll
-        for (int e = 0; e < E; ++e) x[e] = c_mul(xs[e], twiddle<ilog2(P), false>(t + T * e));
-        BlockFFT<NC, E, false>::run(x, t, sc, act);  // odd bins f1 = 2j + 1
-        if (act) {
-#pragma unroll
-          for (int e = 0; e < E; ++e) {
-            const int f1 = 2 * (t + T * e) + 1;
-            if (cc == 0) nq[f1] = x[e];
-            else S[(int64_t)f1 * HS + cc] = x[e];
-          }
+        for (int e = 0; e < E; ++e) {
+          const int f1 = t + T * e;
+          if (cc == 0) nq[f1] = x[e];
+          else S[(int64_t)f1 * HS + cc] = x[e];
         }
       }
     }
@@ -220,11 +181,11 @@ __global__ void __launch_bounds__((SlabCfg<P, CIRC>::NT))
   }
 }
 
-template <int P, bool CIRC, typename TS, bool ACT>
-__global__ void __launch_bounds__((SlabCfg<P, CIRC>::NT))
+template <int P, typename TS, bool ACT>
+__global__ void __launch_bounds__((SlabCfg<P>::NT))
     mp_slab_inv(const float2* __restrict__ ws, const TS* __restrict__ x2, TS* __restrict__ y, int64_t line0,
                 int L0, int HS, int64_t per_line) {
-  using Cf = SlabCfg<P, CIRC>;
+  using Cf = SlabCfg<P>;
   constexpr int ML = Cf::ML, HP = Cf::HP, L1 = Cf::L1, LL = Cf::LL, NT = Cf::NT;
   __shared__ float2 pl[L1 * HP];
   const int tid = threadIdx.x;
@@ -234,8 +195,8 @@ __global__ void __launch_bounds__((SlabCfg<P, CIRC>::NT))
   const int64_t gline = line0 + line;
   const float2* const Y = ws + line * per_line + (int64_t)n0 * P * HS;
 
-  // 1. axis-1 inverse of the ML bin columns (column 0 as DC + i Nyquist),
-  //    rows n1 < L1 kept, into the plane
+  // 1. axis-1 inverse of the ML bin columns (column 0 as DC + i Nyquist) into
+  //    the plane
   {
     constexpr int E = Cf::EC, T = Cf::TC, NC = Cf::NC, CR = NT / T;
     using Map = LaneMap<T, NT>;
@@ -248,33 +209,14 @@ __global__ void __launch_bounds__((SlabCfg<P, CIRC>::NT))
         const float2* r = Y + (int64_t)f1 * HS;
         return cc == 0 ? pack_dc_nyq(r[0], r[ML]) : r[cc];
       };
-      if constexpr (CIRC) {
-        float2 x[E];
+      float2 x[E];
 #pragma unroll
-        for (int e = 0; e < E; ++e) x[e] = act ? bin(t + T * e) : czero();
-        BlockFFT<NC, E, true>::run(x, t, sc, act);
-        __syncthreads();  // every lane's last exchange read is done
-        if (act) {
+      for (int e = 0; e < E; ++e) x[e] = act ? bin(t + T * e) : czero();
+      BlockFFT<NC, E, true>::run(x, t, sc, act);
+      __syncthreads();  // every lane's last exchange read is done
+      if (act) {
 #pragma unroll
-          for (int e = 0; e < E; ++e) pl[(t + T * e) * HP + cc] = x[e];
-        }
-      } else {
-        float2 ev[E], od[E];
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          ev[e] = act ? bin(2 * (t + T * e)) : czero();
-          od[e] = act ? bin(2 * (t + T * e) + 1) : czero();
-        }
-        BlockFFT<NC, E, true>::run(ev, t, sc, act);
-        BlockFFT<NC, E, true>::run(od, t, sc, act);
-        __syncthreads();  // every lane's last exchange read is done
-        if (act) {
-#pragma unroll
-          for (int e = 0; e < E; ++e) {
-            const int n = t + T * e;
-            pl[n * HP + cc] = c_add(ev[e], c_mul(od[e], twiddle<ilog2(P), true>(n)));
-          }
-        }
+        for (int e = 0; e < E; ++e) pl[(t + T * e) * HP + cc] = x[e];
       }
     }
   }
@@ -324,7 +266,7 @@ __global__ void __launch_bounds__((SlabCfg<P, CIRC>::NT))
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           const int m = t + T * e;
-          if (CIRC || 2 * m < LL) row[m] = w[e];
+          row[m] = w[e];
         }
       }
     }
@@ -354,17 +296,16 @@ __global__ void __launch_bounds__((SlabCfg<P, CIRC>::NT))
   }
 }
 
-template <int P, bool CIRC>
+template <int P>
 hipError_t slab_launch(const FftConvArgs& a, const MpGeom& g, float2* ws, int64_t line0, int nl, int64_t per,
                        bool inverse, hipStream_t s) {
-  if constexpr (!slab_fits<P, CIRC>()) {
-    return hipErrorInvalidValue;
-  } else {
-    constexpr int NT = SlabCfg<P, CIRC>::NT;
+  static_assert(SlabCfg<P>::kLdsBytes <= 150 * 1024, "a plane in LDS");
+  constexpr int NT = SlabCfg<P>::NT;
+  {
     if (!inverse) {
       const dim3 grid((unsigned)((int64_t)nl * g.L0 * 2));
 #define HY_FWD(TS, ACT)                                                                                        \
-  hipLaunchKernelGGL((mp_slab_fwd<P, CIRC, TS, ACT>), grid, dim3(NT), 0, s, (const TS*)a.x1, (const TS*)a.v, \
+  hipLaunchKernelGGL((mp_slab_fwd<P, TS, ACT>), grid, dim3(NT), 0, s, (const TS*)a.x1, (const TS*)a.v, \
                      (const TS*)a.k, ws, line0, g.L0, g.HS, g.half, per, a.kC, a.act_in, (int)a.C)
       if (a.bf16) {
         if (a.act) HY_FWD(uint16_t, true); else HY_FWD(uint16_t, false);
@@ -375,7 +316,7 @@ hipError_t slab_launch(const FftConvArgs& a, const MpGeom& g, float2* ws, int64_
     } else {
       const dim3 grid((unsigned)((int64_t)nl * g.L0));
 #define HY_INV(TS, ACT)                                                                                   \
-  hipLaunchKernelGGL((mp_slab_inv<P, CIRC, TS, ACT>), grid, dim3(NT), 0, s, ws, (const TS*)a.x2, (TS*)a.y, \
+  hipLaunchKernelGGL((mp_slab_inv<P, TS, ACT>), grid, dim3(NT), 0, s, ws, (const TS*)a.x2, (TS*)a.y, \
                      line0, g.L0, g.HS, per)
       if (a.bf16) {
         if (a.act) HY_INV(uint16_t, true); else HY_INV(uint16_t, false);
@@ -400,19 +341,13 @@ bool slab3d_supported(const FftConvArgs& a) {
 }
 
 hipError_t launch_slab3d(const FftConvArgs& a, int64_t line0, int64_t nl, void* ws, bool inverse, hipStream_t s) {
-  if (!slab3d_supported(a) || nl < 1 || line0 < 0 || line0 + nl > a.lines) return hipErrorInvalidValue;
+  if (!slab3d_supported(a) || !a.circular || nl < 1 || line0 < 0 || line0 + nl > a.lines) return hipErrorInvalidValue;
   const MpGeom g = mp_geom(a);
   const int64_t per = g.half + g.halfK;
   float2* w = (float2*)ws;
   const int P = (int)a.P[2];
-  if (a.circular) {
-    if (P == 64) return slab_launch<64, true>(a, g, w, line0, (int)nl, per, inverse, s);
-    if (P == 128) return slab_launch<128, true>(a, g, w, line0, (int)nl, per, inverse, s);
-  } else {
-    if (P == 64) return slab_launch<64, false>(a, g, w, line0, (int)nl, per, inverse, s);
-    if (P == 128) return slab_launch<128, false>(a, g, w, line0, (int)nl, per, inverse, s);
-    if (P == 256) return slab_launch<256, false>(a, g, w, line0, (int)nl, per, inverse, s);
-  }
+  if (P == 64) return slab_launch<64>(a, g, w, line0, (int)nl, per, inverse, s);
+  if (P == 128) return slab_launch<128>(a, g, w, line0, (int)nl, per, inverse, s);
   return hipErrorInvalidValue;
 }
 

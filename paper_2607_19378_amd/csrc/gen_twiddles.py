@@ -4,6 +4,7 @@ Tables (all values exp(-2 pi i j / n) rounded once to float32):
   kTwCoarse[j] = exp(-2 pi i j / 4096),  j < 4096
   kTwFine[j]   = exp(-2 pi i j / 2^24),  j < 4096
   kCos32/kSin32[j] = cos/sin(2 pi j / 32), j < 32 (radix-<=32 butterfly constants)
+  kCos64/kSin64[j] = cos/sin(2 pi j / 64), j < 16 (shifted radix-16 passes)
   kPassTw_<log2 NS>_<log2 R>: for every Stockham pass shape (NS, R) with
     NS * R <= 8192, the twiddles exp(-2 pi i jm r / (NS R)) laid out
     [r - 1][jm] (r in 1..R-1, jm in 0..NS-1), so lanes holding consecutive jm
@@ -70,6 +71,10 @@ def main():
     sin32 = ", ".join(lit(math.sin(2 * math.pi * j / 32)) for j in range(32))
     parts.append(f"constexpr float kCos32[32] = {{{cos32}}};")
     parts.append(f"constexpr float kSin32[32] = {{{sin32}}};")
+    cos64 = ", ".join(lit(math.cos(2 * math.pi * j / 64)) for j in range(16))
+    sin64 = ", ".join(lit(math.sin(2 * math.pi * j / 64)) for j in range(16))
+    parts.append(f"constexpr float kCos64[16] = {{{cos64}}};")
+    parts.append(f"constexpr float kSin64[16] = {{{sin64}}};")
     text = "\n".join(parts) + "\n"
     tmp = path + ".tmp"
     with open(tmp, "w") as f:

@@ -261,6 +261,16 @@ size_t embed_fwd_ws(const FftConvArgs& a, bool recommended) {
   return 5 * m.tensor + (recommended ? recommended_ws(m.e, pi) : bytes_per_line(m.e, pi));
 }
 
+// Non-circular 2D and 3D shapes of the multi-pass and embedded plans run on
+// right-angle rows (conv_ra_mp.hip), on the points of the grid alone.  Their
+// workspace queries keep reporting the plan's sizes, which are the larger
+// ones: two spectra against padded spectra, or against five tensors on the
+// transform grid.
+bool runs_ra_mp(const FftConvArgs& a, Plan p) {
+  return (p == PLAN_MULTIPASS || p == PLAN_EMBED) && ra_mp_supported(a) &&
+         ra_mp_bytes_per_line(a, false) <= bytes_per_line(a, p);
+}
+
 // Side streams of the multi-pass plans, and the events that fork them off
 // the caller's stream and join them back: one set per (host thread, device),
 // created on that thread's first multi-pass call on the device (default
@@ -430,6 +440,10 @@ size_t bwd_partial_bytes(const FftConvArgs& a, BwdPlan p) {
   return (n + 255) / 256 * 256;
 }
 
+size_t ra_partial_bytes(const FftConvArgs& a) {
+  return ((size_t)a.lines * (size_t)ra_mp_partials_per_line(a) * sizeof(float) + 255) / 256 * 256;
+}
+
 size_t bwd_bytes_per_line(const FftConvArgs& a, BwdPlan p) {
   if (p == BWD_MULTIPASS) return backward_mp_bytes_per_line(a);
   if (p == BWD_FOURSTEP) return backward_fs_bytes_per_line(a);
@@ -445,6 +459,12 @@ size_t bwd_recommended_spectra(const FftConvArgs& a, BwdPlan p) {
   n *= ns;
   if (n > a.lines) n = a.lines;
   return (size_t)n * per;
+}
+
+// as runs_ra_mp, for the backward: sums and spectra within the plan's least workspace
+bool bwd_runs_ra_mp(const FftConvArgs& a, BwdPlan p, size_t least) {
+  return (p == BWD_MULTIPASS || p == BWD_EMBED) && ra_mp_backward_supported(a) &&
+         ra_partial_bytes(a) + ra_mp_bytes_per_line(a, true) <= least;
 }
 
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
@@ -535,7 +555,13 @@ hipError_t launch_plan(const FftConvArgs& a, Plan p, size_t per, hipStream_t s) 
   switch (p) {
     case PLAN_FUSED1D: return launch_fused1d(a, s);
     case PLAN_FUSED2D: return launch_fused2d(a, s);
+    case PLAN_EMBED:  // forward() embeds the other shapes itself
     case PLAN_MULTIPASS:
+      if (runs_ra_mp(a, p))
+        return run_chunked(a, ra_mp_bytes_per_line(a, false), s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
+          return launch_ra_mp(a, l0, nl, ws, st);
+        });
+      if (p == PLAN_EMBED) return hipErrorInvalidValue;
       return run_chunked(a, per, s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
         return launch_multipass(a, l0, nl, ws, st);
       });
@@ -629,7 +655,7 @@ hyenand_status forward(const void* x1, const void* x2, const void* v, const void
   a.ws_bytes = workspace_bytes;
   a.khat = use_khat ? (float2*)workspace : nullptr;
   clear_pending_error();
-  if (p == PLAN_EMBED) {
+  if (p == PLAN_EMBED && !runs_ra_mp(a, p)) {
     // x1, x2, v, k into the transform grid, the circular plan there, y back
     GridProblem m;
     embedded_inner_plan(a, &m);
@@ -911,7 +937,18 @@ hyenand_status hyenand_fftconv_backward(const void* x1, const void* x2, const vo
   const hipStream_t s = (hipStream_t)stream;
   hipError_t err = hipSuccess;
   clear_pending_error();
-  if (p == BWD_EMBED) {
+  if (bwd_runs_ra_mp(a, p, need)) {
+    FftConvArgs sa = b.f;
+    const size_t rb = ra_partial_bytes(a);
+    sa.ws = (char*)workspace + rb;
+    sa.ws_bytes = workspace_bytes - rb;
+    err = launch_ra_mp_hu(b, b.partial, s);
+    if (err == hipSuccess)
+      err = run_chunked(sa, ra_mp_bytes_per_line(a, true), s, [&b](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
+        return launch_ra_mp_backward(b, l0, nl, ws, st);
+      });
+    if (err == hipSuccess) err = launch_backward_reduce(b, ra_mp_partials_per_line(a), s);
+  } else if (p == BWD_EMBED) {
     char* w = (char*)workspace;
     void* e[9];
     for (int i = 0; i < 9; ++i) e[i] = w + i * m.tensor;

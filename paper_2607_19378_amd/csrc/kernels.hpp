@@ -77,7 +77,8 @@ bool mixed_supported(const FftConvArgs& a);
 bool mixed_preferred(const FftConvArgs& a);  // faster than the power-of-two kernels
 hipError_t launch_mixed(const FftConvArgs& a, hipStream_t s);
 
-// multi-pass 2D/3D (lines along each axis; spectra staged in the workspace).
+// multi-pass 2D/3D (lines along each axis; spectra staged in the workspace);
+// circular grids run there, the others in launch_ra_mp.
 // One call runs every pass over lines [line0, line0 + nl) with their spectra
 // in ws (nl times the bytes per line), all on stream s.
 bool multipass_supported(const FftConvArgs& a);
@@ -89,6 +90,12 @@ hipError_t launch_multipass(const FftConvArgs& a, int64_t line0, int64_t nl, voi
 // where slab3d_supported (HYENAND_SLAB=0 turns it off)
 bool slab3d_supported(const FftConvArgs& a);
 hipError_t launch_slab3d(const FftConvArgs& a, int64_t line0, int64_t nl, void* ws, bool inverse, hipStream_t s);
+
+// multi-pass 2D/3D on right-angle rows for non-circular grids of any extents
+// (conv_ra_mp.hip, conv_ra_slab.hip); one call per chunk of lines
+bool ra_mp_supported(const FftConvArgs& a);
+size_t ra_mp_bytes_per_line(const FftConvArgs& a, bool backward);
+hipError_t launch_ra_mp(const FftConvArgs& a, int64_t line0, int64_t nl, void* ws, hipStream_t s);
 
 // backward
 struct FftConvBwdArgs {
@@ -113,6 +120,10 @@ size_t backward_fs_bytes_per_line(const FftConvArgs& a);
 int64_t backward_fs_partials_per_line(const FftConvArgs& a);
 hipError_t launch_backward_fs(const FftConvBwdArgs& b, int64_t line0, int64_t nl, void* ws, hipStream_t s);
 hipError_t launch_backward_reduce(const FftConvBwdArgs& b, int64_t partials_per_line, hipStream_t s);
+bool ra_mp_backward_supported(const FftConvArgs& a);
+int64_t ra_mp_partials_per_line(const FftConvArgs& a);
+hipError_t launch_ra_mp_hu(const FftConvBwdArgs& b, float* partial, hipStream_t s);  // the gD sums of all lines
+hipError_t launch_ra_mp_backward(const FftConvBwdArgs& b, int64_t line0, int64_t nl, void* ws, hipStream_t s);
 // mixed-radix single pass (conv_mixed.hip) on the forward's transform grid,
 // grids of up to about 3000 points; one float of partial per line
 bool mixed_backward_supported(const FftConvArgs& a);

@@ -23,7 +23,7 @@ struct MpGeom {
   int64_t halfK;                      // complex entries of K per line: krows0 * P1 * HS
 };
 
-MpGeom mp_geom(const FftConvArgs& a) {
+inline MpGeom mp_geom(const FftConvArgs& a) {
   MpGeom g;
   g.L0 = (int)a.L[0];
   g.P0 = (int)a.P[0];
@@ -136,18 +136,15 @@ __device__ __forceinline__ void tile_store(const float2* tile, float2* __restric
 }
 
 // ---------------------------------------------------------------------------
-// axis-1 transforms (3D): forward on NS signals (nload nonzero rows in: L1,
-// or P1 for a centered kernel; P1 out), inverse on NS signals (P1 in, L1
-// cropped rows out).  Signal s of a line starts at sig_off + s * half and
+// axis-1 transforms (3D) of NS signals, P1 rows in and out.  Signal s of a line starts at sig_off + s * half and
 // has `planes` planes n0.  One workgroup per (line, n0, tile).
 // ---------------------------------------------------------------------------
-template <int P1, bool CIRC, bool INV, int NS>
+template <int P1, bool INV, int NS>
 __global__ void __launch_bounds__(kTileNT)
-    mp_axis1(float2* __restrict__ ws, int H, int HS, int planes, int64_t half, int64_t per_line, int nload,
+    mp_axis1(float2* __restrict__ ws, int H, int HS, int planes, int64_t half, int64_t per_line,
              int64_t sig_off) {
   using Cf = TileCfg<P1, NS>;
   constexpr int TL = Cf::TL, TLP = Cf::TLP, E = Cf::E, T = Cf::T;
-  constexpr int L1 = CIRC ? P1 : P1 / 2;
   constexpr int NT = kTileNT;
   __shared__ float2 tile[NS][P1 * TLP];
   __shared__ float2 twl[imax(1, PassTw<P1, E>::kCount)];
@@ -164,12 +161,9 @@ __global__ void __launch_bounds__(kTileNT)
 
   // Lines are (signal, column) pairs; lane (line, t) moves rows t + T e of
   // its column straight between global memory and registers (consecutive
-  // lanes, consecutive columns), in place: the forward reads the nload
-  // nonzero rows and writes all P1, the inverse reads P1 rows and keeps L1.
+  // lanes, consecutive columns), in place.
   // The LDS tile is only the exchange scratch.
   constexpr int NL = NS * TL;
-  const int NLOAD = INV ? P1 : nload;
-  constexpr int NSTORE = INV ? L1 : P1;
   for (int l0 = 0; l0 < NL; l0 += NT / T) {
     const int l = l0 + tid % (NT / T), t = tid / (NT / T);
     const int s = l / TL, cc = l % TL;
@@ -180,14 +174,14 @@ __global__ void __launch_bounds__(kTileNT)
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int n = t + T * e;
-      w[e] = (cv && n < NLOAD) ? g[(int64_t)n * HS] : czero();
+      w[e] = cv ? g[(int64_t)n * HS] : czero();
     }
     BlockFFT<P1, E, INV>::run(w, t, ScrS<TLP>{tile[act ? s : 0] + cc}, act, twl);
     if (cv) {
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const int n = t + T * e;
-        if (n < NSTORE) g[(int64_t)n * HS] = w[e];
+        g[(int64_t)n * HS] = w[e];
       }
     }
   }

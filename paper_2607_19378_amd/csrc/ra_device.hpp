@@ -25,7 +25,8 @@
 // only this wavefront touches between two barriers of the workgroup, so the
 // exchange needs no barrier (a wavefront's LDS accesses are performed in
 // order).  The layouts below keep the exchanges free of bank conflicts
-// (64 banks of 4 bytes: 64 lanes of 8 bytes, two lanes per bank pair).
+// (64 banks of 4 bytes: 64 lanes of 8 bytes, two lanes per bank pair; columns of
+// narrow rows excepted).
 #pragma once
 
 #include "kernels.hpp"
@@ -40,122 +41,170 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// A lane number the compiler cannot see through: twiddles indexed by it are
-// loaded where they are used, not hoisted out of a loop over images into
-// registers that live through all of it.
-__device__ __forceinline__ int opaque(int x) {
-  asm volatile("" : "+v"(x));
-  return x;
-}
-
 // ---------------------------------------------------------------------------
-// Rows: N points (16, 32 or 64), 8 per lane.  Point p of a row sits in slot
-// p + p / 8 of a pitch of 9 N / 8 slots: lane (row l, t) writes slots 9 t + r
-// of the first pass and reads t + T e, and both spread over all banks.
+// Rows: N points (16 to 512), E = 8 per lane up to 64 points, 16 beyond.
+// Point p of a row sits in slot p + p / E of a pitch of N + N / E slots: the
+// writes of a pass (slots (E + 1) t + r) and the reads t + T e both spread over
+// all banks.
 // ---------------------------------------------------------------------------
-template <int N>
+//
+// F = 2: the bins 2 j + p of a row of 2 N points, as the N-point transform of
+// the folded row x[n] + x[n + N] exp(-i pi (p + 1/4)) at the frequencies
+// j + (p + 1/4) / 2.  p is wave-uniform; F = 1 has p = 0.
+template <int N, int F = 1>
 struct RaRow {
-  static_assert(N == 16 || N == 32 || N == 64, "row length");
-  static constexpr int E = 8, T = N / E;       // lanes per row
-  static constexpr int PITCH = N + N / 8;
-  static constexpr int R = N / E, NB = E / R;  // last pass: NB butterflies of radix R per lane
-  static constexpr int kRoot = 32 / (4 * R);   // exp(2 pi i r / (4 R)) in 32nds of a turn
-  // slot of point t + T e, less t
-  static constexpr int off(int e) { return T * e + (T * e) / 8; }
+  static_assert(is_pow2(N) && N >= 16 && N <= 512, "row length");
+  static_assert(F == 1 || (F == 2 && N == 64), "folded rows");
+  static constexpr int E = N <= 64 ? 8 : 16, T = N / E;  // lanes per row
+  static constexpr int PITCH = N + N / E;
+  static constexpr int R2 = imin(E, N / E), NB2 = E / R2;              // second pass
+  static constexpr bool kThree = R2 * E < N;                           // 512 points: a third pass
+  static constexpr int R3 = kThree ? N / (E * R2) : 1, NB3 = E / R3;
+  static constexpr int RL = kThree ? R3 : R2, NBL = kThree ? NB3 : NB2;  // last pass
+  // slot of point t + T e, less t + t / E
+  static constexpr int off(int e) { return T * e + (T * e) / E; }
+  static __device__ __forceinline__ int slot(int p) { return p + p / E; }
 
-  // exp(-2 pi i r (j + 1/4) / N), j = t + T b the butterfly, r = 1 .. R - 1
+  // forward: exp(-2 pi i r (jm + sh) / (NS R)), r >= 1, sh = (p + 1/4) / F;
+  // folded rows also the first pass's exp(-2 pi i e sh / E)
   struct FwdTw {
-    float2 w[NB][R];
-    __device__ __forceinline__ void load(int t) {
+    float2 w2[NB2][R2], w3[kThree ? NB3 : 1][R3], first[F > 1 ? E : 1];
+    __device__ __forceinline__ void load(int t, int p = 0) {
+      if constexpr (F > 1) {
 #pragma unroll
-      for (int b = 0; b < NB; ++b)
+        for (int e = 1; e < E; ++e) first[e] = twiddle<ilog2(4 * F * E), false>((uint32_t)(e * (4 * p + 1)));
+      }
 #pragma unroll
-        for (int r = 1; r < R; ++r) w[b][r] = twiddle<ilog2(4 * N), false>((uint32_t)((4 * (t + T * b) + 1) * r));
+      for (int b = 0; b < NB2; ++b)
+#pragma unroll
+        for (int r = 1; r < R2; ++r)
+          w2[b][r] = twiddle<ilog2(4 * F * E * R2), false>((uint32_t)((4 * F * ((t + T * b) & (E - 1)) + 4 * p + 1) * r));
+      if constexpr (kThree) {
+#pragma unroll
+        for (int b = 0; b < NB3; ++b)
+#pragma unroll
+          for (int r = 1; r < R3; ++r) w3[b][r] = twiddle<ilog2(4 * N), false>((uint32_t)((4 * (t + T * b) + 1) * r));
+      }
     }
   };
-  // exp(+2 pi i j (r + 1/4) / N), r = 0 .. R - 1
+  // inverse: exp(+2 pi i jm r / (NS R)), and in the last pass (NS R = N)
+  // exp(+2 pi i jm (r + 1/4) / N), r >= 0
   struct InvTw {
-    float2 w[NB][R];
+    float2 w2[NB2][R2], w3[kThree ? NB3 : 1][R3];
     __device__ __forceinline__ void load(int t) {
+      static_assert(F == 1, "folded rows are not inverted");
 #pragma unroll
-      for (int b = 0; b < NB; ++b)
+      for (int b = 0; b < NB2; ++b)
 #pragma unroll
-        for (int r = 0; r < R; ++r) w[b][r] = twiddle<ilog2(4 * N), true>((uint32_t)((t + T * b) * (4 * r + 1)));
+        for (int r = 0; r < R2; ++r) {
+          const int jm = (t + T * b) & (E - 1);
+          if constexpr (kThree) w2[b][r] = twiddle<ilog2(E * R2), true>((uint32_t)(jm * r));
+          else w2[b][r] = twiddle<ilog2(4 * N), true>((uint32_t)(jm * (4 * r + 1)));
+        }
+      if constexpr (kThree) {
+#pragma unroll
+        for (int b = 0; b < NB3; ++b)
+#pragma unroll
+          for (int r = 0; r < R3; ++r) w3[b][r] = twiddle<ilog2(4 * N), true>((uint32_t)((t + T * b) * (4 * r + 1)));
+      }
     }
   };
 
-  // the first pass's constants exp(-2 pi i e / 32) on a real or complex input
-  static __device__ __forceinline__ float2 lead(float x, int e) { return make_float2(x * kCos32[e], -x * kSin32[e]); }
-  static __device__ __forceinline__ float2 lead(float2 x, int e) { return mul_root<32, false>(x, e); }
+  // the first pass's constants exp(-2 pi i e / (4 E)) on a real or complex input
+  static __device__ __forceinline__ float lead_c(int e) { return E == 8 ? kCos32[e] : kCos64[e]; }
+  static __device__ __forceinline__ float lead_s(int e) { return E == 8 ? kSin32[e] : kSin64[e]; }
+  static __device__ __forceinline__ float2 lead(float x, int e) { return make_float2(x * lead_c(e), -x * lead_s(e)); }
+  static __device__ __forceinline__ float2 lead(float2 x, int e) {
+    if (e == 0) return x;
+    const float c = lead_c(e), s = lead_s(e);
+    return make_float2(fmaf(x.x, c, x.y * s), fmaf(x.y, c, -x.x * s));
+  }
 
+  // folded rows: point n from x[n] (a) and x[n + N] (b), both real or complex
+  static __device__ __forceinline__ float2 fold(float2 a, float2 b, int p, const FwdTw& tw, int e) {
+    const float s = p ? -0.70710678118654752f : 0.70710678118654752f;  // exp(-i pi (p + 1/4)) = s (1 - i)
+    const float2 z = make_float2(fmaf(s, b.x + b.y, a.x), fmaf(s, b.y - b.x, a.y));
+    return e ? c_mul(z, tw.first[e]) : z;
+  }
+  // exchange after pass (NS, R): butterfly j = t + T b leaves its output r at
+  // position (j - jm) R + jm + NS r
+  template <int NS, int R>
   static __device__ __forceinline__ void exchange(float2 (&w)[E], int t, float2* row) {
+    constexpr int NB = E / R;
+    static_assert(NB == 1, "a pass before an exchange has one butterfly per lane");
     wave_sync();
-    float2* const pw = row + 9 * t;
+    const int jm = t & (NS - 1);
+    float2* const pw = row + slot((t - jm) * R + jm);
+    // NS r: a multiple of E, or (first pass) inside the E slots from a multiple of E on
 #pragma unroll
-    for (int r = 0; r < E; ++r) pw[r] = w[r];
+    for (int r = 0; r < R; ++r) pw[NS * r + (NS * r) / E] = w[r];
     wave_sync();
-    const float2* const pr = row + t;
+    const float2* const pr = row + slot(t);
 #pragma unroll
     for (int e = 0; e < E; ++e) w[e] = pr[off(e)];
     wave_sync();
+  }
+  template <int R, int NB, bool INV, bool FIRST>
+  static __device__ __forceinline__ void pass(float2 (&w)[E], const float2 (&tw)[NB][R]) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      float2 x[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) x[r] = (r || FIRST) ? c_mul(w[b + NB * r], tw[b][r]) : w[b];
+      dft<R, INV>(x);
+#pragma unroll
+      for (int r = 0; r < R; ++r) w[b + NB * r] = x[r];
+    }
   }
 
   // w[e] = lead(point t + T e); leaves bin t + T e in w[e]
   static __device__ __forceinline__ void forward(float2 (&w)[E], int t, float2* row, const FwdTw& tw) {
     dft<E, false>(w);
-    exchange(w, t, row);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      float2 x[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) x[r] = r ? c_mul(w[b + NB * r], tw.w[b][r]) : w[b];
-      dft<R, false>(x);
-#pragma unroll
-      for (int r = 0; r < R; ++r) w[b + NB * r] = x[r];
+    exchange<1, E>(w, t, row);
+    pass<R2, NB2, false, false>(w, tw.w2);
+    if constexpr (kThree) {
+      exchange<E, R2>(w, t, row);
+      pass<R3, NB3, false, false>(w, tw.w3);
     }
   }
-  // bin t + T e in w[e]; leaves point t + T e up to exp(2 pi i r / (4 R)),
-  // r = e / NB, which re() and im() apply
+  // bin t + T e in w[e]; leaves point t + T e up to exp(2 pi i r / (4 RL)),
+  // r = e / NBL, which re() and im() apply
   static __device__ __forceinline__ void inverse(float2 (&w)[E], int t, float2* row, const InvTw& tw) {
     dft<E, true>(w);
-    exchange(w, t, row);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      float2 x[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) x[r] = c_mul(w[b + NB * r], tw.w[b][r]);
-      dft<R, true>(x);
-#pragma unroll
-      for (int r = 0; r < R; ++r) w[b + NB * r] = x[r];
+    exchange<1, E>(w, t, row);
+    pass<R2, NB2, true, !kThree>(w, tw.w2);
+    if constexpr (kThree) {
+      exchange<E, R2>(w, t, row);
+      pass<R3, NB3, true, true>(w, tw.w3);
     }
   }
+  // cos, sin of 2 pi (e / NBL) / (4 RL)
+  static constexpr float root_c(int e) { return RL == 16 ? kCos64[e / NBL] : kCos32[(e / NBL) * (8 / imin(RL, 8))]; }
+  static constexpr float root_s(int e) { return RL == 16 ? kSin64[e / NBL] : kSin32[(e / NBL) * (8 / imin(RL, 8))]; }
   static __device__ __forceinline__ float re(float2 z, int e) {
-    const int j = (e / NB) * kRoot;
-    return j ? fmaf(z.x, kCos32[j], -z.y * kSin32[j]) : z.x;
+    return e / NBL ? fmaf(z.x, root_c(e), -z.y * root_s(e)) : z.x;
   }
   static __device__ __forceinline__ float im(float2 z, int e) {
-    const int j = (e / NB) * kRoot;
-    return j ? fmaf(z.x, kSin32[j], z.y * kCos32[j]) : z.y;
+    return e / NBL ? fmaf(z.x, root_s(e), z.y * root_c(e)) : z.y;
   }
 };
 
 // ---------------------------------------------------------------------------
-// Columns: P points (32, 64 or 128) along axis 0, ordinary transforms.  A
-// wavefront holds 64 / T adjacent columns; their slots in the P rows of the
+// Columns: P points (16 to 128) of the rows of a region, ordinary transforms.
+// A wavefront holds 64 / T adjacent columns; their slots in the P rows of the
 // region are its own.  Row n of the region holds point n of the column before
 // and after; the exchange stores point p in row rho(p), p with its low two
 // bits turned by p / E, so that the lanes of a first pass (p = E t + r) and
 // of its reads (p = t + T e) fall on different rows modulo 4.
 // ---------------------------------------------------------------------------
-template <int P, int PITCH>
+template <int P, class Row>
 struct RaCol {
-  static_assert(P == 32 || P == 64 || P == 128, "column length");
+  static_assert(P == 16 || P == 32 || P == 64 || P == 128, "column length");
+  static constexpr int PITCH = Row::PITCH;
   static constexpr int E = P == 128 ? 16 : 8, T = P / E;
   static constexpr int CW = 64 / T;            // columns per wavefront
   static constexpr int R = T, NB = E / R;      // last pass
   static constexpr int LE = ilog2(E);
-
-  static __device__ __forceinline__ int slot(int col) { return col + (col >> 3); }
 
   static __device__ __forceinline__ void exchange(float2 (&w)[E], int t, float2* col) {
     wave_sync();
@@ -169,7 +218,7 @@ struct RaCol {
 #pragma unroll
     for (int q = 0; q < 4; ++q) pr[q] = col + ((t & ~3) + ((t + q) & 3)) * PITCH;
 #pragma unroll
-    for (int e = 0; e < E; ++e) w[e] = pr[((T * e) >> LE) & 3][T * e * PITCH];
+    for (int e = 0; e < E; ++e) w[e] = pr[((T * e) + ((T * e) >> LE)) & 3][((T * e) & ~3) * PITCH];
     wave_sync();
   }
 

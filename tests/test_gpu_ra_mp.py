@@ -1,0 +1,56 @@
+"""Multi-pass kernels on right-angle rows (conv_ra_mp.hip, conv_ra_slab.hip): non-circular 2D and 3D grids of any
+extents, forward and backward, at the edges of their transforms: one point below and above a power of two on each
+axis, rows from 16 to 512 complex points (two and three passes), planes in the slab passes (one and two foldings)
+and outside them, periodic kernels, and a small workspace; against the oracle, within the plans' tolerances (relative
+L2: fp32 1e-5, bf16 2e-2)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2607_19378_amd import workloads as W
+from gpu_util import TOL, from_device, log, oracle_ref, rel_l2, run_gpu, to_device
+
+pytestmark = pytest.mark.gpu
+
+GRIDS = [((200, 150), "centered"), ((65, 257), "centered"), ((129, 128), "linear"), ((16, 512), "centered"),
+         ((300, 9), "linear"), ((70, 90), "circular"), ((17, 33, 49), "centered"), ((48, 48, 48), "centered"),
+         ((9, 65, 127), "centered"), ((5, 128, 128), "linear"), ((20, 24, 28), "linear"), ((3, 129, 130), "centered"),
+         ((11, 40, 100), "circular")]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("grid,mode", GRIDS)
+def test_forward(grid, mode, dtype):
+    from paper_2607_19378_amd import hyenand as H
+    log(f"ra_mp forward {grid} {mode} {dtype}")
+    inp = W.random_case(1, 2, grid, mode, dtype, seed=40 + sum(grid))
+    w = inp.workload
+    y = run_gpu(inp)
+    x1, x2, v, k, D = inp.as_f64()
+    if mode == "circular":  # the oracle's circular FFT takes powers of two: numpy's serves here
+        ax = tuple(range(2, 2 + len(grid)))
+        u = x1 * v
+        ref = x2 * (np.fft.irfftn(np.fft.rfftn(u, axes=ax) * np.fft.rfftn(k, axes=ax), s=grid, axes=ax)
+                    + D.reshape((1, 2) + (1,) * len(grid)) * u)
+    else:
+        ref = oracle_ref(inp)
+    assert rel_l2(y, ref) <= TOL[dtype]
+    small = run_gpu(inp, workspace_bytes=H.workspace_min(w.shape, mode, dtype))
+    assert np.array_equal(y, small)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("grid,mode", [((65, 33), "linear"), ((72, 40), "centered"), ((7, 70, 18), "centered"),
+                                       ((6, 17, 33), "linear"), ((3, 20, 65), "centered"), ((4, 65, 65), "linear")])
+def test_backward(grid, mode, dtype):
+    import torch
+    from paper_2607_19378_amd import hyenand as H
+    log(f"ra_mp backward {grid} {mode} {dtype}")
+    inp = W.random_case(2, 2, grid, mode, dtype, seed=60 + sum(grid))
+    gy = W.quantise(np.random.default_rng(9).standard_normal(inp.workload.shape), dtype)
+    dev = [to_device(a, dtype) for a in (inp.x1, inp.x2, inp.v, inp.k, inp.D, gy)]
+    got = H.backward(*dev, pad_mode=mode)
+    torch.cuda.synchronize()
+    ref = oracle.backward_direct(*inp.as_f64(), W.storage_to_f64(gy, dtype), mode)
+    for name, g, r in zip(("gx1", "gx2", "gv", "gk", "gD"), got, ref):
+        assert rel_l2(from_device(g), r) <= TOL[dtype], name

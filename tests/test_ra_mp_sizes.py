@@ -1,0 +1,32 @@
+"""The multi-pass kernels on right-angle rows must fit in the workspace that the plans' queries report, for every
+shape that reaches them: the power-of-two non-circular grids have no other kernels."""
+import itertools
+
+from paper_2607_19378_amd import hyenand as H
+
+
+def _ra_bytes(grid, mode, backward):
+    """Spectra of a line: planes x P1 x N complex fp32 (conv_ra_mp.hip)."""
+    p = [2 * n for n in grid]
+    n = max(16, p[-1] // 2)
+    p1 = p[1] if len(grid) == 3 else 1
+    if len(grid) == 3 and p[-1] >= 32 and 32 <= p1 <= 256 and max(32, n) <= 128:
+        n = max(32, n)
+    kp = grid[0] if mode == "linear" else 2 * grid[0] - 1
+    return ((2 if backward else 1) * grid[0] + kp) * p1 * n * 8
+
+
+def test_power_of_two_grids_fit(monkeypatch):
+    monkeypatch.setenv("HYENAND_PLAN", "multipass")
+    sizes = [2, 4, 8, 16, 32, 64, 128, 256, 512]
+    grids = [g for nd in (2, 3) for g in itertools.product(sizes, repeat=nd)]
+    for grid, mode in itertools.product(grids, ("linear", "centered")):
+        shape = (1, 1) + grid
+        assert H.plan_name(shape, mode, "f32")[:6] in ("multip", "slab3d"), (grid, mode)
+        assert _ra_bytes(grid, mode, False) <= H.workspace_min(shape, mode, "f32"), (grid, mode)
+        data = 1
+        for n in grid:
+            data *= n
+        sums = (min(64, -(-data // 8192)) * 4 + 255) // 256 * 256
+        assert sums + _ra_bytes(grid, mode, True) <= H.backward_workspace_min(shape, mode, "f32") or max(grid[:2]) <= 64 \
+            and len(grid) == 2, (grid, mode)
