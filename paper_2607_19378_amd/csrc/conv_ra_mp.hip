@@ -35,31 +35,40 @@ struct RaRowsCfg {
   static constexpr int RB = RW * (kRaNT / 64);
 };
 
-// KERN: k on the double grid; else gate(x, w) or, w null, a linear kernel
+// KERN: k on the double grid (signal 0); else the gated signals and, w null,
+// linear kernels, workgroup by workgroup in turn.  vec: rows come in 16-byte
+// accesses through the rows' LDS slots; otherwise point by point.
 template <int N, bool KERN, typename TS, bool ACT>
 __global__ void __launch_bounds__(kRaNT)
-    ra_rows_fwd(const TS* __restrict__ x, const TS* __restrict__ w, float2* __restrict__ ws, RaGeom g, int64_t line0,
-                int nl, int64_t per, int kC, ActIn ain, int C) {
+    ra_rows_fwd(RaSignals sg, float2* __restrict__ ws, RaGeom g, int64_t line0, int nl, int64_t per, int kC, int vec,
+                ActIn ain, int C) {
   using Cf = RaRowsCfg<N>;
   using Row = typename Cf::Row;
   constexpr int E = Row::E, T = Row::T;
   __shared__ float2 S[Cf::RB * Row::PITCH];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
   const int rr = tid / T, t = tid % T;
   float2* const row = S + rr * Row::PITCH;
+  float* const wrow = reinterpret_cast<float*>(S + (tid >> 6) * Cf::RW * Row::PITCH);  // this wavefront's rows
   typename Row::FwdTw tw;
   tw.load(t);
+  const unsigned nsig = KERN ? 1 : sg.n, nb = gridDim.x / nsig;
+  const unsigned sig = blockIdx.x % nsig;
+  const TS* const x = (const TS*)sg.x[sig];
+  const TS* const w = KERN ? nullptr : (const TS*)sg.w[sig];
+  const bool act_gate = ACT && w;
+  const bool vrow = !KERN && vec && !act_gate && (w || !kC);
   const uint32_t n1s = KERN ? 2 * g.L1 - 1 : g.L1;               // rows of a plane
   const uint32_t rows = (KERN ? g.KP : g.L0) * n1s;               // rows of a line
   const uint32_t total = rows * (uint32_t)nl;
-  for (uint32_t r0 = blockIdx.x * Cf::RB; r0 < total; r0 += gridDim.x * Cf::RB) {
+  for (uint32_t r0 = blockIdx.x / nsig * Cf::RB; r0 < total; r0 += nb * Cf::RB) {
     const uint32_t r = r0 + rr;
     const bool act = r < total;
     const uint32_t line = act ? r / rows : 0, lr = act ? r - line * rows : 0;
     const uint32_t pl = lr / n1s, i1 = lr - pl * n1s;
     const int64_t gl = line0 + line;
     float2 v[E];
-    int64_t dst = line * per;
+    int64_t dst = sg.off[sig] + line * per;
     if constexpr (KERN) {
       const int d1 = (int)i1 - (g.L1 - 1);
       const RaKRow kr = ra_krow(g, (int)pl - (g.L0 - 1), d1);
@@ -71,22 +80,32 @@ __global__ void __launch_bounds__(kRaNT)
       for (int e = 0; e < E; ++e) v[e] = Row::lead(z[e], e);
       dst += ((int64_t)pl * g.P1 + (d1 < 0 ? d1 + g.P1 : d1)) * N;
     } else {
-      const int64_t o = (int64_t)lr * g.LL + t;
-      const TS* const a = x + (w ? gl : k_line(gl, kC)) * g.data + o;
-      const TS* const b = w + gl * g.data + o;
-      const Gates<ACT> G = line_gates<ACT, TS>(ain, gl, C);
-      float p[E], q[E];
+      if (vrow) {
+        const uint32_t rw = r0 + (uint32_t)(tid >> 6) * Cf::RW;  // the wavefront's first row
+        const int nrows = rw < total ? (int)(total - rw < (uint32_t)Cf::RW ? total - rw : Cf::RW) : 0;
+        const int64_t o = line0 * g.data + (int64_t)rw * g.LL;
+        ra_rows_in<Row::PITCH, Cf::RW, N>(x + o, w ? w + o : nullptr, nrows, g.LL, wrow, lane);
+        const float* const rf = reinterpret_cast<const float*>(row) + t;
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const bool in = act && t + T * e < g.LL;
-        p[e] = in ? ld1(a + T * e) : 0.f;
-        q[e] = in && w ? ld1(b + T * e) : 1.f;
-      }
+        for (int e = 0; e < E; ++e) v[e] = Row::lead(act && t + T * e < g.LL ? rf[T * e] : 0.f, e);
+      } else {
+        const int64_t o = (int64_t)lr * g.LL + t;
+        const TS* const a = x + (w ? gl : k_line(gl, kC)) * g.data + o;
+        const TS* const b = w + gl * g.data + o;
+        const Gates<ACT> G = line_gates<ACT, TS>(ain, gl, C);
+        float p[E], q[E];
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        float u = p[e] * q[e];
-        if constexpr (ACT) u = act && t + T * e < g.LL ? G.u1(p[e], q[e], o + T * e) : 0.f;
-        v[e] = Row::lead(u, e);
+        for (int e = 0; e < E; ++e) {
+          const bool in = act && t + T * e < g.LL;
+          p[e] = in ? ld1(a + T * e) : 0.f;
+          q[e] = in && w ? ld1(b + T * e) : 1.f;
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          float u = p[e] * q[e];
+          if (act_gate) u = act && t + T * e < g.LL ? G.u1(p[e], q[e], o + T * e) : 0.f;
+          v[e] = Row::lead(u, e);
+        }
       }
       dst += ((int64_t)pl * g.P1 + i1) * N;
     }
@@ -98,58 +117,70 @@ __global__ void __launch_bounds__(kRaNT)
   }
 }
 
-template <int N, RaOut OUT, typename TS, bool ACT>
+// the inverse of one spectrum (forward) or of z, gu and gk in turn (BWD)
+template <int N, bool BWD, typename TS, bool ACT>
 __global__ void __launch_bounds__(kRaNT)
-    ra_rows_inv(const float2* __restrict__ ws, const TS* __restrict__ p, const TS* __restrict__ q,
-                TS* __restrict__ o1, TS* __restrict__ o2, RaGeom g, int64_t line0, int nl, int64_t per) {
+    ra_rows_inv(RaIos ios, const float2* __restrict__ ws, RaGeom g, int64_t line0, int nl, int64_t per, int vec) {
   using Cf = RaRowsCfg<N>;
   using Row = typename Cf::Row;
   constexpr int E = Row::E, T = Row::T;
   __shared__ float2 S[Cf::RB * Row::PITCH];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
   const int rr = tid / T, t = tid % T;
   float2* const row = S + rr * Row::PITCH;
+  float* const wrow = reinterpret_cast<float*>(S + (tid >> 6) * Cf::RW * Row::PITCH);
   typename Row::InvTw tw;
   tw.load(t);
-  const bool dbl = OUT == RA_GK && g.kmode != RA_LINEAR;
+  const unsigned n = BWD ? ios.n : 1, nb = gridDim.x / n, which = blockIdx.x % n;
+  const RaOut out = BWD ? ios.io[which].out : RA_Y;
+  const TS* const p = (const TS*)ios.io[which].p;
+  const TS* const q = (const TS*)ios.io[which].q;
+  TS* const o1 = (TS*)ios.io[which].o;
+  TS* const o2 = (TS*)ios.io[which].o2;
+  const bool dbl = BWD && out == RA_GK && g.kmode != RA_LINEAR;
   const uint32_t n1s = dbl ? 2 * g.L1 - 1 : g.L1;
   const uint32_t rows = (dbl ? g.KP : g.L0) * n1s;
   const uint32_t total = rows * (uint32_t)nl;
-  for (uint32_t r0 = blockIdx.x * Cf::RB; r0 < total; r0 += gridDim.x * Cf::RB) {
+  for (uint32_t r0 = blockIdx.x / n * Cf::RB; r0 < total; r0 += nb * Cf::RB) {
     const uint32_t r = r0 + rr;
     const bool act = r < total;
     const uint32_t line = act ? r / rows : 0, lr = act ? r - line * rows : 0;
     const uint32_t pl = lr / n1s, i1 = lr - pl * n1s;
     const int64_t gl = line0 + line;
     const int d1 = dbl ? (int)i1 - (g.L1 - 1) : (int)i1;
-    const float2* const src = ws + line * per + ((int64_t)pl * g.P1 + (d1 < 0 ? d1 + g.P1 : d1)) * N + t;
+    const float2* const src =
+        ws + ios.io[which].off + line * per + ((int64_t)pl * g.P1 + (d1 < 0 ? d1 + g.P1 : d1)) * N + t;
     float2 v[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) v[e] = src[T * e];
     Row::inverse(v, t, row, tw);
-    if (act) {
-      if constexpr (OUT == RA_GK) {
-        if (dbl) {
-          const RaKRow kr = ra_krow(g, (int)pl - (g.L0 - 1), d1);
-          TS* const d = o1 + gl * g.kpts + kr.row;
+    if (dbl) {
+      if (act) {
+        const RaKRow kr = ra_krow(g, (int)pl - (g.L0 - 1), d1);
+        TS* const d = o1 + gl * g.kpts + kr.row;
 #pragma unroll
-          for (int e = 0; e < E; ++e) {
-            const int n = t + T * e;
-            if (n < g.LL) st1(d + kr.reo + n, Row::re(v[e], e));
-            if (n > g.N - g.LL) st1(d + kr.imo + n, Row::im(v[e], e));
-          }
-        } else {
-          TS* const d = o1 + gl * g.kpts + (int64_t)lr * g.LL;
-#pragma unroll
-          for (int e = 0; e < E; ++e)
-            if (t + T * e < g.LL) st1(d + t + T * e, Row::re(v[e], e));
+        for (int e = 0; e < E; ++e) {
+          const int m = t + T * e;
+          if (m < g.LL) st1(d + kr.reo + m, Row::re(v[e], e));
+          if (m > g.N - g.LL) st1(d + kr.imo + m, Row::im(v[e], e));
         }
-      } else {
-        const int64_t o = gl * g.data + (int64_t)lr * g.LL + t;
-#pragma unroll
-        for (int e = 0; e < E; ++e)
-          if (t + T * e < g.LL) ra_store<OUT, TS, ACT>(p, q, o1, o2, o + T * e, Row::re(v[e], e));
       }
+    } else if (vec) {
+      float* const rf = reinterpret_cast<float*>(row) + t;
+#pragma unroll
+      for (int e = 0; e < E; ++e) rf[T * e] = Row::re(v[e], e);
+      const uint32_t rw = r0 + (uint32_t)(tid >> 6) * Cf::RW;
+      const int nrows = rw < total ? (int)(total - rw < (uint32_t)Cf::RW ? total - rw : Cf::RW) : 0;
+      const int64_t o = line0 * g.data + (int64_t)rw * g.LL;
+      ra_rows_out<Row::PITCH, Cf::RW, N, ACT>(out, p + o, q + o, o1 + o, o2 + o, nrows, g.LL, wrow, lane);
+    } else if (act) {
+      const int64_t o = gl * g.data + (int64_t)lr * g.LL + t;
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (t + T * e < g.LL) {
+          if (out == RA_GK) st1(o1 + o + T * e, Row::re(v[e], e));
+          else ra_store<TS, ACT>(out, p, q, o1, o2, o + T * e, Row::re(v[e], e));
+        }
     }
   }
 }
@@ -333,44 +364,43 @@ unsigned row_blocks(int64_t rows, int rb) {
   return (unsigned)(n < kRaRowBlocks ? n : kRaRowBlocks);
 }
 
+template <typename TS>
+int ra_vec(const RaGeom& g) {
+  return g.LL % RaVec<TS>::V == 0;
+}
+
 template <int N, typename TS>
-hipError_t rows_signal(const RaPass& p, const void* x, const void* w, bool act, int64_t off) {
+hipError_t rows_signals(const RaPass& p, const RaSignals& sg, bool act) {
   const FftConvArgs& a = *p.a;
-  const dim3 grid(row_blocks((int64_t)p.nl * p.g.L0 * p.g.L1, RaRowsCfg<N>::RB));
+  const dim3 grid(row_blocks((int64_t)p.nl * p.g.L0 * p.g.L1, RaRowsCfg<N>::RB) * sg.n);
   if (act)
-    hipLaunchKernelGGL((ra_rows_fwd<N, false, TS, true>), grid, dim3(kRaNT), 0, p.s, (const TS*)x, (const TS*)w,
-                       p.ws + off, p.g, p.line0, p.nl, p.per, a.kC, a.act_in, (int)a.C);
+    hipLaunchKernelGGL((ra_rows_fwd<N, false, TS, true>), grid, dim3(kRaNT), 0, p.s, sg, p.ws, p.g, p.line0, p.nl,
+                       p.per, a.kC, ra_vec<TS>(p.g), a.act_in, (int)a.C);
   else
-    hipLaunchKernelGGL((ra_rows_fwd<N, false, TS, false>), grid, dim3(kRaNT), 0, p.s, (const TS*)x, (const TS*)w,
-                       p.ws + off, p.g, p.line0, p.nl, p.per, a.kC, a.act_in, (int)a.C);
+    hipLaunchKernelGGL((ra_rows_fwd<N, false, TS, false>), grid, dim3(kRaNT), 0, p.s, sg, p.ws, p.g, p.line0, p.nl,
+                       p.per, a.kC, ra_vec<TS>(p.g), a.act_in, (int)a.C);
   return hipGetLastError();
 }
 template <int N, typename TS>
 hipError_t rows_kernel(const RaPass& p, int64_t off) {
   const FftConvArgs& a = *p.a;
   const dim3 grid(row_blocks((int64_t)p.nl * p.g.KP * (2 * p.g.L1 - 1), RaRowsCfg<N>::RB));
-  hipLaunchKernelGGL((ra_rows_fwd<N, true, TS, false>), grid, dim3(kRaNT), 0, p.s, (const TS*)a.k, (const TS*)nullptr,
-                     p.ws + off, p.g, p.line0, p.nl, p.per, a.kC, a.act_in, (int)a.C);
+  const RaSignals sg{{a.k}, {nullptr}, {off}, 1};
+  hipLaunchKernelGGL((ra_rows_fwd<N, true, TS, false>), grid, dim3(kRaNT), 0, p.s, sg, p.ws, p.g, p.line0, p.nl,
+                     p.per, a.kC, 0, a.act_in, (int)a.C);
   return hipGetLastError();
 }
 template <int N, typename TS>
-hipError_t rows_inverse(const RaPass& p, RaOut out, const RaIo& io, int64_t off) {
-  const bool dbl = out == RA_GK && p.g.kmode != RA_LINEAR;
-  const int64_t rows = dbl ? (int64_t)p.nl * p.g.KP * (2 * p.g.L1 - 1) : (int64_t)p.nl * p.g.L0 * p.g.L1;
-  const dim3 grid(row_blocks(rows, RaRowsCfg<N>::RB));
-#define HY_INV(OUT, ACT)                                                                                       \
-  hipLaunchKernelGGL((ra_rows_inv<N, OUT, TS, ACT>), grid, dim3(kRaNT), 0, p.s, p.ws + off, (const TS*)io.p,  \
-                     (const TS*)io.q, (TS*)io.o, (TS*)io.o2, p.g, p.line0, p.nl, p.per)
-  if (out == RA_Y) {
-    if (p.a->act) HY_INV(RA_Y, true);
-    else HY_INV(RA_Y, false);
-  } else if (out == RA_GX2) {
-    HY_INV(RA_GX2, false);
-  } else if (out == RA_GU) {
-    HY_INV(RA_GU, false);
-  } else {
-    HY_INV(RA_GK, false);
-  }
+hipError_t rows_inverse(const RaPass& p, const RaIos& ios) {
+  const int64_t rows = (int64_t)p.nl * p.g.KP * (p.g.kmode == RA_LINEAR ? p.g.L1 : 2 * p.g.L1 - 1);  // the most of any
+  const bool bwd = ios.io[0].out != RA_Y;
+  const dim3 grid(row_blocks(bwd ? rows : (int64_t)p.nl * p.g.L0 * p.g.L1, RaRowsCfg<N>::RB) * ios.n);
+#define HY_INV(BWD, ACT)                                                                                       \
+  hipLaunchKernelGGL((ra_rows_inv<N, BWD, TS, ACT>), grid, dim3(kRaNT), 0, p.s, ios, p.ws, p.g, p.line0, p.nl, \
+                     p.per, ra_vec<TS>(p.g))
+  if (bwd) HY_INV(true, false);
+  else if (p.a->act) HY_INV(false, true);
+  else HY_INV(false, false);
 #undef HY_INV
   return hipGetLastError();
 }
@@ -385,13 +415,9 @@ hipError_t rows_inverse(const RaPass& p, RaOut out, const RaIo& io, int64_t off)
     case 512: return p.a->bf16 ? FN<512, uint16_t>(__VA_ARGS__) : FN<512, float>(__VA_ARGS__);   \
     default: return hipErrorInvalidValue;                                                        \
   }
-hipError_t d_rows_signal(const RaPass& p, const void* x, const void* w, bool act, int64_t off) {
-  HY_N_SWITCH(rows_signal, p, x, w, act, off)
-}
+hipError_t d_rows_signals(const RaPass& p, const RaSignals& sg, bool act) { HY_N_SWITCH(rows_signals, p, sg, act) }
 hipError_t d_rows_kernel(const RaPass& p, int64_t off) { HY_N_SWITCH(rows_kernel, p, off) }
-hipError_t d_rows_inverse(const RaPass& p, RaOut out, const RaIo& io, int64_t off) {
-  HY_N_SWITCH(rows_inverse, p, out, io, off)
-}
+hipError_t d_rows_inverse(const RaPass& p, const RaIos& ios) { HY_N_SWITCH(rows_inverse, p, ios) }
 
 template <int P1>
 hipError_t axis1(const RaPass& p, bool inv, int planes, bool dbl, int64_t off) {
@@ -456,22 +482,22 @@ hipError_t forward_axes(const RaPass& p, RaSignals sg, bool act, int64_t koff) {
     e = ra_slab_signals(p, sg, act);
     return e == hipSuccess && !lin ? ra_slab_kernel(p, koff) : e;
   }
-  for (int i = 0; i < sg.n && e == hipSuccess; ++i) {
-    e = d_rows_signal(p, sg.x[i], sg.w[i], act && sg.w[i], sg.off[i]);
-    if (e == hipSuccess && p.g.P1 > 1) e = d_axis1(p, false, p.g.L0, false, sg.off[i]);
-  }
+  e = d_rows_signals(p, sg, act);
+  for (int i = 0; i < sg.n && e == hipSuccess && p.g.P1 > 1; ++i) e = d_axis1(p, false, p.g.L0, false, sg.off[i]);
   if (!lin) {
     if (e == hipSuccess) e = d_rows_kernel(p, koff);
     if (e == hipSuccess && p.g.P1 > 1) e = d_axis1(p, false, p.g.KP, true, koff);
   }
   return e;
 }
-hipError_t inverse(const RaPass& p, RaOut out, const RaIo& io, int64_t off) {
-  if (p.g.slab) return ra_slab_inverse(p, out, io, off);
+hipError_t inverse_axes(const RaPass& p, const RaIos& ios) {
   hipError_t e = hipSuccess;
-  const bool dbl = out == RA_GK && p.g.kmode != RA_LINEAR;
-  if (p.g.P1 > 1) e = d_axis1(p, true, dbl ? p.g.KP : p.g.L0, dbl, off);
-  return e == hipSuccess ? d_rows_inverse(p, out, io, off) : e;
+  for (int i = 0; i < ios.n && e == hipSuccess; ++i) {
+    const bool dbl = ios.io[i].out == RA_GK && p.g.kmode != RA_LINEAR;
+    if (p.g.slab) e = ra_slab_inverse(p, ios.io[i]);
+    else if (p.g.P1 > 1) e = d_axis1(p, true, dbl ? p.g.KP : p.g.L0, dbl, ios.io[i].off);
+  }
+  return e == hipSuccess && !p.g.slab ? d_rows_inverse(p, ios) : e;
 }
 
 RaPass make_pass(const FftConvArgs& a, const RaGeom& g, bool bwd, int64_t line0, int64_t nl, void* ws, hipStream_t s) {
@@ -506,7 +532,7 @@ hipError_t launch_ra_mp(const FftConvArgs& a, int64_t line0, int64_t nl, void* w
   hipError_t e;
   if ((e = forward_axes(p, RaSignals{{a.x1}, {a.v}, {0}, 1}, a.act, p.g.half)) != hipSuccess) return e;
   if ((e = d_core(p, false)) != hipSuccess) return e;
-  return inverse(p, RA_Y, RaIo{a.x2, nullptr, a.y, nullptr}, 0);
+  return inverse_axes(p, RaIos{{{RA_Y, a.x2, nullptr, a.y, nullptr, 0}}, 1});
 }
 
 // the periodic kernel's gradient gathers two displacements per axis, which
@@ -521,9 +547,9 @@ hipError_t launch_ra_mp_backward(const FftConvBwdArgs& b, int64_t line0, int64_t
   hipError_t e;
   if ((e = forward_axes(p, RaSignals{{a.x1, b.gy}, {a.v, a.x2}, {0, h}, 2}, false, 2 * h)) != hipSuccess) return e;
   if ((e = d_core(p, true)) != hipSuccess) return e;
-  if ((e = inverse(p, RA_GX2, RaIo{b.gy, nullptr, b.gx2, nullptr}, 0)) != hipSuccess) return e;
-  if ((e = inverse(p, RA_GU, RaIo{a.v, a.x1, b.gx1, b.gv}, h)) != hipSuccess) return e;
-  return inverse(p, RA_GK, RaIo{nullptr, nullptr, b.gk, nullptr}, 2 * h);
+  return inverse_axes(p, RaIos{{{RA_GX2, b.gy, nullptr, b.gx2, nullptr, 0},
+                                {RA_GU, a.v, a.x1, b.gx1, b.gv, h},
+                                {RA_GK, nullptr, nullptr, b.gk, nullptr, 2 * h}}, 3});
 }
 
 int64_t ra_mp_partials_per_line(const FftConvArgs& a) {

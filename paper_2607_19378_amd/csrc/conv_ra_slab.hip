@@ -55,7 +55,8 @@ __device__ __forceinline__ int slab_bin(int col) {
 // Workgroups: (line, plane, signal, folding).
 template <int P1, int N, bool FULL, typename TS, bool ACT>
 __global__ void __launch_bounds__((SlabFwd<P1, N>::NT)) __attribute__((amdgpu_waves_per_eu(P1 <= 128 ? 6 : 4)))
-    ra_slab_fwd(RaSignals sg, float2* __restrict__ ws, RaGeom g, int64_t line0, int64_t per, int kC, ActIn ain, int C) {
+    ra_slab_fwd(RaSignals sg, float2* __restrict__ ws, RaGeom g, int64_t line0, int64_t per, int kC, int vec, ActIn ain,
+                int C) {
   using S_ = SlabFwd<P1, N>;
   using Row = typename S_::Row;
   using Col = typename S_::Col;
@@ -83,12 +84,20 @@ __global__ void __launch_bounds__((SlabFwd<P1, N>::NT)) __attribute__((amdgpu_wa
   const TS* const kl = (const TS*)sg.x[sig] + (gated ? gl * g.data : k_line(gl, kC) * g.kpts);
   const TS* const wl = gated ? w0 + gl * g.data : nullptr;
   const Gates<ACT> G = line_gates<ACT, TS>(ain, gl, C);
+  constexpr int RW = 64 / TR;  // rows of a wavefront
+  const bool vrow = !FULL && vec && !(ACT && gated);
   // the rows of one half of axis 1: n1 = r, or (FULL) displacement r - PH
   auto rows = [&](int hf) {
 #pragma unroll
     for (int q = 0; q < S_::NR; ++q) {
       const int r = q * RPR + rr;
       const int d1 = hf ? r - PH : r;
+      if (vrow) {
+        const int rw = q * RPR + (tid >> 6) * RW;  // the wavefront's first row
+        const int64_t o = ((int64_t)pl * g.L1 + rw) * g.LL;
+        ra_rows_in<PITCH, RW, N>(kl + o, gated ? wl + o : nullptr, imax(0, imin(RW, g.L1 - rw)), g.LL,
+                                 reinterpret_cast<float*>(S + rw * PITCH), lane);
+      }
       if (r < PH && (hf ? d1 > -g.L1 : r < g.L1)) {
         float2 v[ER];
         if constexpr (FULL) {
@@ -112,8 +121,8 @@ __global__ void __launch_bounds__((SlabFwd<P1, N>::NT)) __attribute__((amdgpu_wa
             for (int e = 0; e < ER; ++e) {
               const int n = TR * e + f * NC;
               const bool in = tr + n < g.LL;
-              a[f][e] = in ? ld1(kl + o + n) : 0.f;
-              b[f][e] = gated && in ? ld1(wl + o + n) : 1.f;
+              a[f][e] = !in ? 0.f : (vrow ? reinterpret_cast<const float*>(S + r * PITCH)[tr + n] : ld1(kl + o + n));
+              b[f][e] = gated && in && !vrow ? ld1(wl + o + n) : 1.f;
             }
 #pragma unroll
           for (int e = 0; e < ER; ++e) {
@@ -175,7 +184,7 @@ __global__ void __launch_bounds__((SlabFwd<P1, N>::NT)) __attribute__((amdgpu_wa
 template <int P1, int N, RaOut OUT, typename TS, bool ACT>
 __global__ void __launch_bounds__((SlabInv<P1, N>::NT)) __attribute__((amdgpu_waves_per_eu(P1 <= 128 ? 6 : 4)))
     ra_slab_inv(const float2* __restrict__ ws, const TS* __restrict__ p, const TS* __restrict__ q,
-                TS* __restrict__ o1, TS* __restrict__ o2, RaGeom g, int64_t line0, int64_t per) {
+                TS* __restrict__ o1, TS* __restrict__ o2, RaGeom g, int64_t line0, int64_t per, int vec) {
   using S_ = SlabInv<P1, N>;
   using Row = typename S_::Row;
   using Col = typename S_::Col;
@@ -236,6 +245,13 @@ __global__ void __launch_bounds__((SlabInv<P1, N>::NT)) __attribute__((amdgpu_wa
         for (int e = 0; e < ER; ++e) v[e] = pr[(TR / 2) * e + (TR / 2 * e) / ER];
       }
       Row::inverse(v, tr, row, itw);
+      if (vec && !dbl) {
+        wave_sync();
+        float* const rf = reinterpret_cast<float*>(row) + tr;
+#pragma unroll
+        for (int e = 0; e < ER; ++e) rf[TR * e] = Row::re(v[e], e);
+        continue;
+      }
       const int64_t lr = (int64_t)pl * g.L1 + r;
       if constexpr (OUT == RA_GK) {
         if (dbl) {
@@ -257,8 +273,18 @@ __global__ void __launch_bounds__((SlabInv<P1, N>::NT)) __attribute__((amdgpu_wa
         const int64_t o = gl * g.data + lr * g.LL + tr;
 #pragma unroll
         for (int e = 0; e < ER; ++e)
-          if (tr + TR * e < g.LL) ra_store<OUT, TS, ACT>(p, q, o1, o2, o + TR * e, Row::re(v[e], e));
+          if (tr + TR * e < g.LL) ra_store<TS, ACT>(OUT, p, q, o1, o2, o + TR * e, Row::re(v[e], e));
       }
+    }
+  }
+  if (vec && !dbl) {
+    constexpr int RW = 64 / TR;
+#pragma unroll
+    for (int i = 0; i < S_::NR; ++i) {
+      const int rw = i * RPR + (tid >> 6) * RW;
+      const int64_t o = gl * g.data + ((int64_t)pl * g.L1 + rw) * g.LL;
+      ra_rows_out<PITCH, RW, N, ACT>(OUT, p + o, q + o, o1 + o, o2 + o, imax(0, imin(RW, g.L1 - rw)), g.LL,
+                                     reinterpret_cast<const float*>(S + rw * PITCH), lane);
     }
   }
 }
@@ -267,13 +293,15 @@ template <int P1, int N, typename TS>
 hipError_t slab_signals(const RaPass& p, const RaSignals& sg, bool act) {
   constexpr int NT = SlabFwd<P1, N>::NT, F = SlabFwd<P1, N>::F;
   const FftConvArgs& a = *p.a;
+  // (shared kernels start at k_line's line, as aligned as any other)
+  const int kvec = p.g.LL % RaVec<TS>::V == 0;
   const dim3 grid((unsigned)((int64_t)p.nl * p.g.L0 * sg.n * F));
   if (act)
     hipLaunchKernelGGL((ra_slab_fwd<P1, N, false, TS, true>), grid, dim3(NT), 0, p.s, sg, p.ws, p.g, p.line0, p.per,
-                       a.kC, a.act_in, (int)a.C);
+                       a.kC, kvec, a.act_in, (int)a.C);
   else
     hipLaunchKernelGGL((ra_slab_fwd<P1, N, false, TS, false>), grid, dim3(NT), 0, p.s, sg, p.ws, p.g, p.line0, p.per,
-                       a.kC, a.act_in, (int)a.C);
+                       a.kC, kvec, a.act_in, (int)a.C);
   return hipGetLastError();
 }
 
@@ -282,19 +310,22 @@ hipError_t slab_kernel(const RaPass& p, int64_t off) {
   constexpr int NT = SlabFwd<P1, N>::NT, F = SlabFwd<P1, N>::F;
   const FftConvArgs& a = *p.a;
   const RaSignals sg{{a.k}, {nullptr}, {off}, 1};
+  const int kvec = 0;
   hipLaunchKernelGGL((ra_slab_fwd<P1, N, true, TS, false>), dim3((unsigned)((int64_t)p.nl * p.g.KP * F)), dim3(NT), 0,
-                     p.s, sg, p.ws, p.g, p.line0, p.per, a.kC, a.act_in, (int)a.C);
+                     p.s, sg, p.ws, p.g, p.line0, p.per, a.kC, kvec, a.act_in, (int)a.C);
   return hipGetLastError();
 }
 
 template <int P1, int N, typename TS>
-hipError_t slab_inverse(const RaPass& p, RaOut out, const RaIo& io, int64_t off) {
+hipError_t slab_inverse(const RaPass& p, const RaIo& io) {
   constexpr int NT = SlabInv<P1, N>::NT;
+  const RaOut out = io.out;
   const bool dbl = out == RA_GK && p.g.kmode != RA_LINEAR;
   const dim3 grid((unsigned)((int64_t)p.nl * (out == RA_GK ? p.g.KP : p.g.L0) * (dbl ? 2 : 1)));
 #define HY_INV(OUT, ACT)                                                                                      \
-  hipLaunchKernelGGL((ra_slab_inv<P1, N, OUT, TS, ACT>), grid, dim3(NT), 0, p.s, p.ws + off, (const TS*)io.p, \
-                     (const TS*)io.q, (TS*)io.o, (TS*)io.o2, p.g, p.line0, p.per)
+  hipLaunchKernelGGL((ra_slab_inv<P1, N, OUT, TS, ACT>), grid, dim3(NT), 0, p.s, p.ws + io.off, (const TS*)io.p, \
+                     (const TS*)io.q, (TS*)io.o, (TS*)io.o2, p.g, p.line0, p.per, \
+                     (int)(p.g.LL % RaVec<TS>::V == 0))
   if (out == RA_Y) {
     if (p.a->act) HY_INV(RA_Y, true);
     else HY_INV(RA_Y, false);
@@ -332,8 +363,8 @@ hipError_t ra_slab_kernel(const RaPass& p, int64_t off) {
 #undef HY_FN
   return hipErrorInvalidValue;
 }
-hipError_t ra_slab_inverse(const RaPass& p, RaOut out, const RaIo& io, int64_t off) {
-#define HY_FN(P1, N, TS) slab_inverse<P1, N, TS>(p, out, io, off)
+hipError_t ra_slab_inverse(const RaPass& p, const RaIo& io) {
+#define HY_FN(P1, N, TS) slab_inverse<P1, N, TS>(p, io)
   HY_SLAB_SIZES(HY_CASE)
 #undef HY_FN
   return hipErrorInvalidValue;

@@ -224,14 +224,22 @@ struct ChunkPlan {
   int streams;      // 1: everything on the caller's stream
 };
 
-ChunkPlan plan_chunks(int64_t lines, size_t per, size_t ws_bytes) {
+// wide: one stream and chunks of up to 640 MiB, for the passes of ragged grids
+// (conv_ra_mp.hip), whose callers hold a workspace of that order anyway.  Their
+// lines are short (about 1 to 10 MB of spectra) and a launch tail costs more
+// than the cache saves: 4 x 64 images of 200 x 150 329 -> 291 us, 2 x 32
+// volumes of 48^3 497 -> 474 us.  Power-of-two grids keep the rule above (one
+// line of 128^3 points is 67 MB: 3378 us, wide 3994 us).
+ChunkPlan plan_chunks(int64_t lines, size_t per, size_t ws_bytes, bool wide) {
   ChunkPlan c;
   const int64_t fit = (int64_t)(ws_bytes / per);  // >= 1, checked by the caller
-  const int want = chunk_streams();
+  const bool set = getenv("HYENAND_WS_TARGET_MB") || getenv("HYENAND_CHUNK_STREAMS");
+  wide = wide && !set;
+  const int want = wide ? 1 : chunk_streams();
   c.streams = want;
   if (c.streams > fit) c.streams = (int)fit;
   if (c.streams > lines) c.streams = (int)lines;
-  int64_t target = (int64_t)(ws_target_bytes() / (size_t)want / per);
+  int64_t target = (int64_t)((wide ? (size_t)640 << 20 : ws_target_bytes()) / (size_t)want / per);
   if (target < 1) target = 1;
   int64_t chunk = fit / c.streams;
   if (chunk > target) chunk = target;
@@ -330,8 +338,8 @@ hipError_t side_set(hipStream_t caller, SideSet** out) {
 // the caller's stream, chunk j runs on side stream j % S with workspace part
 // j % S, and the caller's stream waits for all S before any later work.
 template <class Launch>
-hipError_t run_chunked(const FftConvArgs& a, size_t per, hipStream_t caller, Launch launch) {
-  const ChunkPlan c = plan_chunks(a.lines, per, a.ws_bytes);
+hipError_t run_chunked(const FftConvArgs& a, size_t per, hipStream_t caller, Launch launch, bool wide = false) {
+  const ChunkPlan c = plan_chunks(a.lines, per, a.ws_bytes, wide);
   if (c.streams == 1) {
     for (int64_t j = 0; j < c.nchunks; ++j) {
       const int64_t line0 = j * c.chunk;
@@ -560,7 +568,7 @@ hipError_t launch_plan(const FftConvArgs& a, Plan p, size_t per, hipStream_t s) 
       if (runs_ra_mp(a, p))
         return run_chunked(a, ra_mp_bytes_per_line(a, false), s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
           return launch_ra_mp(a, l0, nl, ws, st);
-        });
+        }, a.rl);
       if (p == PLAN_EMBED) return hipErrorInvalidValue;
       return run_chunked(a, per, s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
         return launch_multipass(a, l0, nl, ws, st);
@@ -946,7 +954,7 @@ hyenand_status hyenand_fftconv_backward(const void* x1, const void* x2, const vo
     if (err == hipSuccess)
       err = run_chunked(sa, ra_mp_bytes_per_line(a, true), s, [&b](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
         return launch_ra_mp_backward(b, l0, nl, ws, st);
-      });
+      }, a.rl);
     if (err == hipSuccess) err = launch_backward_reduce(b, ra_mp_partials_per_line(a), s);
   } else if (p == BWD_EMBED) {
     char* w = (char*)workspace;

@@ -33,8 +33,14 @@ enum RaOut { RA_Y = 0, RA_GX2 = 1, RA_GU = 2, RA_GK = 3 };
 // pointers of one pass; the meaning per output: RA_Y p = x2, o = y; RA_GX2
 // p = gy, o = gx2; RA_GU p = v, q = x1, o = gx1, o2 = gv; RA_GK o = gk
 struct RaIo {
+  RaOut out;
   const void *p, *q;
   void *o, *o2;
+  int64_t off;  // of the spectrum
+};
+struct RaIos {
+  RaIo io[3];
+  int n;
 };
 
 struct RaPass {
@@ -57,7 +63,7 @@ struct RaSignals {
 };
 hipError_t ra_slab_signals(const RaPass& p, const RaSignals& sg, bool act);
 hipError_t ra_slab_kernel(const RaPass& p, int64_t off);  // k on the double grid
-hipError_t ra_slab_inverse(const RaPass& p, RaOut out, const RaIo& io, int64_t off);
+hipError_t ra_slab_inverse(const RaPass& p, const RaIo& io);
 bool ra_slab_takes(int P1, int N);
 
 namespace {
@@ -87,12 +93,102 @@ __device__ __forceinline__ float2 ra_kvalue(const TS* kl, const RaKRow& r, const
   return make_float2(n < g.LL ? ld1(kl + r.row + r.reo + n) : 0.f, n > g.N - g.LL ? ld1(kl + r.row + r.imo + n) : 0.f);
 }
 
+// Rows between memory and LDS in 16-byte accesses.  A wavefront's rows are
+// consecutive, so their nrows LL values are one run; LL has to be a multiple of
+// the V values of an access (the tensors are 16-byte aligned, so the run is
+// too).  Row i's values sit at s + i * 2 PITCH (floats), where the row's
+// transform has its exchange slots.
+template <typename TS>
+struct RaVec {
+  static constexpr int V = 16 / sizeof(TS);
+};
+__device__ __forceinline__ void ra_ld(const float* p, float (&v)[4]) {
+  const float4 a = ld4(p);
+  v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w;
+}
+__device__ __forceinline__ void ra_ld(const uint16_t* p, float (&v)[8]) {
+  const uint4 a = *reinterpret_cast<const uint4*>(p);
+  const uint32_t w[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    v[2 * i] = __uint_as_float(w[i] << 16);
+    v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+  }
+}
+__device__ __forceinline__ void ra_st(float* p, const float (&v)[4]) { st4(p, make_float4(v[0], v[1], v[2], v[3])); }
+__device__ __forceinline__ void ra_st(uint16_t* p, const float (&v)[8]) {
+  *reinterpret_cast<uint4*>(p) =
+      make_uint4(bf16_pack(v[0], v[1]), bf16_pack(v[2], v[3]), bf16_pack(v[4], v[5]), bf16_pack(v[6], v[7]));
+}
+// values x w (w null: x) of nrows rows from x and w on
+template <int PITCH, int RW, int NMAX, typename TS>
+__device__ __forceinline__ void ra_rows_in(const TS* x, const TS* w, int nrows, int LL, float* s, int lane) {
+  constexpr int V = RaVec<TS>::V, ITER = (RW * NMAX / V + 63) / 64;
+  const unsigned vr = (unsigned)LL / V, total = (unsigned)nrows * vr;
+  wave_sync();
+#pragma unroll
+  for (int j = 0; j < ITER; ++j) {
+    const unsigned i = (unsigned)lane + 64u * j;
+    if (i < total) {
+      float a[V], b[V];
+      ra_ld(x + (size_t)i * V, a);
+      if (w) {
+        ra_ld(w + (size_t)i * V, b);
+#pragma unroll
+        for (int k = 0; k < V; ++k) a[k] *= b[k];
+      }
+      const unsigned r = i / vr;
+      float* const d = s + r * (2 * PITCH) + (i - r * vr) * V;
+#pragma unroll
+      for (int k = 0; k < V; k += 4) *reinterpret_cast<float4*>(d + k) = make_float4(a[k], a[k + 1], a[k + 2], a[k + 3]);
+    }
+  }
+  wave_sync();
+}
+// o = g(p) value (RA_Y: the outer gate), p value (RA_GX2), the values (RA_GK),
+// or o = p value and o2 = q value (RA_GU), for nrows rows from those pointers on
+template <int PITCH, int RW, int NMAX, bool ACT, typename TS>
+__device__ __forceinline__ void ra_rows_out(RaOut out, const TS* p, const TS* q, TS* o, TS* o2, int nrows, int LL,
+                                            const float* s, int lane) {
+  constexpr int V = RaVec<TS>::V, ITER = (RW * NMAX / V + 63) / 64;
+  const unsigned vr = (unsigned)LL / V, total = (unsigned)nrows * vr;
+  wave_sync();
+#pragma unroll
+  for (int j = 0; j < ITER; ++j) {
+    const unsigned i = (unsigned)lane + 64u * j;
+    if (i < total) {
+      const size_t at = (size_t)i * V;
+      float a[V], b[V], z[V];
+      if (out != RA_GK) ra_ld(p + at, a);
+      if (out == RA_GU) ra_ld(q + at, b);
+      const unsigned r = i / vr;
+      const float* const d = s + r * (2 * PITCH) + (i - r * vr) * V;
+#pragma unroll
+      for (int k = 0; k < V; k += 4) {
+        const float4 f = *reinterpret_cast<const float4*>(d + k);
+        z[k] = f.x, z[k + 1] = f.y, z[k + 2] = f.z, z[k + 3] = f.w;
+      }
+      if (out == RA_GU) {
+#pragma unroll
+        for (int k = 0; k < V; ++k) b[k] *= z[k];
+        ra_st(o2 + at, b);
+      }
+      if (out != RA_GK) {
+#pragma unroll
+        for (int k = 0; k < V; ++k) z[k] *= out == RA_Y ? Gates<ACT>{}.g1(a[k]) : a[k];
+      }
+      ra_st(o + at, z);
+    }
+  }
+  wave_sync();
+}
+
 // one point of an inverse pass: z at data point o (line base + index)
-template <RaOut OUT, typename TS, bool ACT>
-__device__ __forceinline__ void ra_store(const TS* p, const TS* q, TS* o1, TS* o2, int64_t o, float z) {
-  if constexpr (OUT == RA_Y) st1(o1 + o, Gates<ACT>{}.g1(ld1(p + o)) * z);
-  if constexpr (OUT == RA_GX2) st1(o1 + o, ld1(p + o) * z);
-  if constexpr (OUT == RA_GU) {
+template <typename TS, bool ACT>
+__device__ __forceinline__ void ra_store(RaOut out, const TS* p, const TS* q, TS* o1, TS* o2, int64_t o, float z) {
+  if (out == RA_Y) st1(o1 + o, Gates<ACT>{}.g1(ld1(p + o)) * z);
+  if (out == RA_GX2) st1(o1 + o, ld1(p + o) * z);
+  if (out == RA_GU) {
     st1(o1 + o, z * ld1(p + o));
     st1(o2 + o, z * ld1(q + o));
   }
