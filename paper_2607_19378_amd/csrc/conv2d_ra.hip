@@ -14,8 +14,8 @@
 // loads and stores and 33 us of traffic; two images per CU (74 KB of LDS
 // each, 110 VGPRs) overlap the two.  The packed real transforms that these
 // replace issued 29.0 M and met 21 barriers: linear forward 64.7 -> 58.1 us,
-// the operator on centered kernels 165 -> 118 us (bf16), linear backward 217
-// -> 200 us, and centered backward 1564 us (embedded in the circular 128 x 128
+// the operator on centered kernels 165 -> 118 us (bf16), linear backward 220
+// -> 158 us, and centered backward 1566 us (embedded in the circular 128 x 128
 // grid) -> 224 us.  The backward holds three spectra in registers (228 VGPRs):
 // one image per CU, its loads, arithmetic and stores in turn; at 128 VGPRs it
 // spills (360 us).  Keeping a workgroup resident and fetching the next image's

@@ -509,6 +509,14 @@ hipError_t launch_bwd2d_t(const FftConvBwdArgs& b, hipStream_t s) {
   }
 }
 
+// linear lines from 1024 transform points on run in conv1d_ra.hip
+template <int P, typename TS>
+hipError_t launch_bwd1d(const FftConvBwdArgs& b, hipStream_t s) {
+  if (b.f.circular) return launch_bwd1d_t<P, true, TS>(b, s);
+  if constexpr (P < 1024) return launch_bwd1d_t<P, false, TS>(b, s);
+  return hipErrorInvalidValue;
+}
+
 // linear images from 32 transform points per axis run in conv2d_ra.hip
 template <int P0, int P1, typename TS>
 hipError_t launch_bwd2d(const FftConvBwdArgs& b, hipStream_t s) {
@@ -529,7 +537,7 @@ hipError_t launch_typed(const FftConvBwdArgs& b, hipStream_t s) {
     e = hipGetLastError();
   } else if (a.ndim == 1) {
 #define HY_CASE(p) \
-  if (a.P[0] == p) e = a.circular ? launch_bwd1d_t<p, true, TS>(b, s) : launch_bwd1d_t<p, false, TS>(b, s);
+  if (a.P[0] == p) e = launch_bwd1d<p, TS>(b, s);
     HY_BWD1D_SIZES(HY_CASE)
 #undef HY_CASE
   } else if (ra2d_supported(a)) {

@@ -1,5 +1,6 @@
-// Backward of the gated long convolution for 1D lines beyond the single-pass
-// limit (2^14 to 2^22 transform points): the four-step structure of the
+// Backward of the gated long convolution for circular 1D lines beyond the
+// single-pass limit (2^14 to 2^22 transform points; the other modes:
+// conv1d_ra.hip): the four-step structure of the
 // forward plan (M = P/2 = N1 x N2, m = m1 N2 + m2, f = f1 + N1 f2) carried
 // over to three signals.
 //
@@ -15,7 +16,7 @@
 //             half-length inverses; inverse transforms over f2, twiddle
 //             exp(+2 pi i f1 m2 / M); Z, GU, GK overwrite A_u, A_k, A_h.
 //   cols_inv  per column m2: inverse transforms over f1 of Z, GU and GK
-//             (one exchange tile in turn), keep m1 < N1/2 (linear), unpack,
+//             (one exchange tile in turn), unpack,
 //             write gx2, gx1, gv, gk; per-workgroup sums of h u for gD.
 #include "fourstep.hpp"
 
@@ -37,14 +38,13 @@ __device__ __forceinline__ float fs_wg_sum(float x, float* red, int tid) {
   return s;
 }
 
-template <int N1, bool CIRC, typename TS>
+template <int N1, typename TS>
 __global__ void __launch_bounds__(ColCfgFwd<N1>::NT) __attribute__((amdgpu_waves_per_eu(ColCfgFwd<N1>::kWaves)))
     fsb_cols_fwd(const TS* __restrict__ x1, const TS* __restrict__ v, const TS* __restrict__ k,
                  const TS* __restrict__ gy, const TS* __restrict__ x2, float2* __restrict__ ws, int64_t line0,
                  int N2, int log2M, int64_t per_line) {
   using Cf = ColCfgFwd<N1>;
   constexpr int E = Cf::E, T = Cf::T, NT = Cf::NT, TL = Cf::TL, TLP = Cf::TLP;
-  constexpr int NZ = CIRC ? N1 : N1 / 2;  // nonzero rows m1
   static_assert(NT / T >= TL, "one round covers the tile");
   __shared__ float2 tile[N1 * TLP];
   __shared__ float2 twl[imax(1, PassTw<N1, E>::kCount)];
@@ -55,7 +55,7 @@ __global__ void __launch_bounds__(ColCfgFwd<N1>::NT) __attribute__((amdgpu_waves
   const int64_t line = rest / ntile;
   const int c0 = (int)(rest % ntile) * TL;
   const int64_t M = (int64_t)N1 * N2;
-  const int64_t L = CIRC ? 2 * M : M;
+  const int64_t L = 2 * M;
   const size_t gbase = (size_t)(line0 + line) * L;
   const int tid = threadIdx.x;
   const int cc = tid % (NT / T), t = tid / (NT / T);
@@ -66,7 +66,7 @@ __global__ void __launch_bounds__(ColCfgFwd<N1>::NT) __attribute__((amdgpu_waves
   for (int e = 0; e < E; ++e) {
     const int m1 = t + T * e;
     w[e] = czero();
-    if (act && (CIRC || m1 < NZ)) {
+    if (act) {
       const size_t n = gbase + 2 * ((size_t)m1 * N2 + c0 + cc);
       if (sig == 0) {
         const float2 a = ld2(x1 + n), b = ld2(v + n);
@@ -91,7 +91,6 @@ __global__ void __launch_bounds__(ColCfgFwd<N1>::NT) __attribute__((amdgpu_waves
 
 // 1024 lanes: six rows of 2048 points (u, k, h at f1 = fa and fb) on 768 of
 // them during the transforms, all of them during the products.
-template <bool CIRC>
 __global__ void __launch_bounds__(1024)
     fsb_core(float2* __restrict__ ws, const void* __restrict__ Dp, int dbf16, int64_t line0, int C, int N1,
              int log2M, int64_t per_line, float scale) {
@@ -192,7 +191,7 @@ __global__ void __launch_bounds__(1024)
   }
 }
 
-template <int N1, bool CIRC, typename TS>
+template <int N1, typename TS>
 __global__ void __launch_bounds__(512)
     fsb_cols_inv(const float2* __restrict__ ws, const TS* __restrict__ x1, const TS* __restrict__ v,
                  const TS* __restrict__ gy, const TS* __restrict__ x2, TS* __restrict__ gx1, TS* __restrict__ gx2,
@@ -200,7 +199,6 @@ __global__ void __launch_bounds__(512)
                  int64_t per_line) {
   using Cf = ColCfg<N1>;
   constexpr int E = Cf::E, T = Cf::T, NT = Cf::NT, TL = Cf::TL, TLP = Cf::TLP;
-  constexpr int NOUT = CIRC ? N1 : N1 / 2;  // cropped rows m1
   static_assert(NT / T >= TL, "one round covers the tile");
   __shared__ float2 tile[N1 * TLP];
   __shared__ float2 twl[imax(1, PassTw<N1, E>::kCount)];
@@ -211,7 +209,7 @@ __global__ void __launch_bounds__(512)
   const int64_t line = bid / ntile;
   const int c0 = (int)(bid % ntile) * TL;
   const int64_t M = (int64_t)N1 * N2;
-  const int64_t L = CIRC ? 2 * M : M;
+  const int64_t L = 2 * M;
   const int tid = threadIdx.x;
   const int cc = tid % (NT / T), t = tid / (NT / T);
   const bool act = cc < TL;
@@ -235,15 +233,13 @@ __global__ void __launch_bounds__(512)
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int m1 = t + T * e;
-      if (CIRC || m1 < NOUT) {
-        const size_t n = gbase + 2 * (size_t)m1 * N2;
-        const float2 a = ld2(x1 + n), b = ld2(v + n), g = ld2(gy + n), q = ld2(x2 + n);
-        st2(gx2 + n, make_float2(g.x * wz[e].x, g.y * wz[e].y));
-        st2(gx1 + n, make_float2(b.x * wu[e].x, b.y * wu[e].y));
-        st2(gv + n, make_float2(a.x * wu[e].x, a.y * wu[e].y));
-        st2(gk + n, wk[e]);
-        hu += (a.x * b.x) * (g.x * q.x) + (a.y * b.y) * (g.y * q.y);
-      }
+      const size_t n = gbase + 2 * (size_t)m1 * N2;
+      const float2 a = ld2(x1 + n), b = ld2(v + n), g = ld2(gy + n), q = ld2(x2 + n);
+      st2(gx2 + n, make_float2(g.x * wz[e].x, g.y * wz[e].y));
+      st2(gx1 + n, make_float2(b.x * wu[e].x, b.y * wu[e].y));
+      st2(gv + n, make_float2(a.x * wu[e].x, a.y * wu[e].y));
+      st2(gk + n, wk[e]);
+      hu += (a.x * b.x) * (g.x * q.x) + (a.y * b.y) * (g.y * q.y);
     }
   }
   const float tot = fs_wg_sum<NT>(hu, red, tid);
@@ -269,11 +265,9 @@ hipError_t b_cols_fwd(const FsbLaunch& L) {
 #define HY_ARGS(TS) \
   (const TS*)a.x1, (const TS*)a.v, (const TS*)a.k, (const TS*)L.b->gy, (const TS*)a.x2, L.ws, L.line0, kN2, L.log2M, L.per
   if (a.bf16) {
-    if (a.circular) hipLaunchKernelGGL((fsb_cols_fwd<N1, true, uint16_t>), grid, dim3(ColCfgFwd<N1>::NT), 0, L.s, HY_ARGS(uint16_t));
-    else hipLaunchKernelGGL((fsb_cols_fwd<N1, false, uint16_t>), grid, dim3(ColCfgFwd<N1>::NT), 0, L.s, HY_ARGS(uint16_t));
+    hipLaunchKernelGGL((fsb_cols_fwd<N1, uint16_t>), grid, dim3(ColCfgFwd<N1>::NT), 0, L.s, HY_ARGS(uint16_t));
   } else {
-    if (a.circular) hipLaunchKernelGGL((fsb_cols_fwd<N1, true, float>), grid, dim3(ColCfgFwd<N1>::NT), 0, L.s, HY_ARGS(float));
-    else hipLaunchKernelGGL((fsb_cols_fwd<N1, false, float>), grid, dim3(ColCfgFwd<N1>::NT), 0, L.s, HY_ARGS(float));
+    hipLaunchKernelGGL((fsb_cols_fwd<N1, float>), grid, dim3(ColCfgFwd<N1>::NT), 0, L.s, HY_ARGS(float));
   }
 #undef HY_ARGS
   return hipGetLastError();
@@ -289,11 +283,9 @@ hipError_t b_cols_inv(const FsbLaunch& L) {
   L.ws, (const TS*)a.x1, (const TS*)a.v, (const TS*)b.gy, (const TS*)a.x2, (TS*)b.gx1, (TS*)b.gx2, (TS*)b.gv, \
       (TS*)b.gk, b.partial, L.line0, kN2, L.per
   if (a.bf16) {
-    if (a.circular) hipLaunchKernelGGL((fsb_cols_inv<N1, true, uint16_t>), grid, dim3(512), 0, L.s, HY_ARGS(uint16_t));
-    else hipLaunchKernelGGL((fsb_cols_inv<N1, false, uint16_t>), grid, dim3(512), 0, L.s, HY_ARGS(uint16_t));
+    hipLaunchKernelGGL((fsb_cols_inv<N1, uint16_t>), grid, dim3(512), 0, L.s, HY_ARGS(uint16_t));
   } else {
-    if (a.circular) hipLaunchKernelGGL((fsb_cols_inv<N1, true, float>), grid, dim3(512), 0, L.s, HY_ARGS(float));
-    else hipLaunchKernelGGL((fsb_cols_inv<N1, false, float>), grid, dim3(512), 0, L.s, HY_ARGS(float));
+    hipLaunchKernelGGL((fsb_cols_inv<N1, float>), grid, dim3(512), 0, L.s, HY_ARGS(float));
   }
 #undef HY_ARGS
   return hipGetLastError();
@@ -350,7 +342,7 @@ int64_t backward_fs_partials_per_line(const FftConvArgs& a) {
 
 hipError_t launch_backward_fs(const FftConvBwdArgs& b, int64_t line0, int64_t nl, void* ws, hipStream_t s) {
   const FftConvArgs& a = b.f;
-  if (!backward_fs_supported(a) || nl < 1 || line0 < 0 || line0 + nl > a.lines) return hipErrorInvalidValue;
+  if (!backward_fs_supported(a) || !a.circular || nl < 1 || line0 < 0 || line0 + nl > a.lines) return hipErrorInvalidValue;
   FsbLaunch L;
   L.b = &b;
   L.ws = (float2*)ws;
@@ -365,12 +357,8 @@ hipError_t launch_backward_fs(const FftConvBwdArgs& b, int64_t line0, int64_t nl
   hipError_t e;
   if ((e = d_b_cols_fwd(L)) != hipSuccess) return e;
   const dim3 grid((unsigned)((int64_t)L.nl * (L.N1 / 2 + 1)));
-  if (a.circular)
-    hipLaunchKernelGGL((fsb_core<true>), grid, dim3(1024), 0, s, L.ws, a.D, (int)a.bf16, line0, (int)a.C, L.N1,
-                       L.log2M, L.per, L.scale);
-  else
-    hipLaunchKernelGGL((fsb_core<false>), grid, dim3(1024), 0, s, L.ws, a.D, (int)a.bf16, line0, (int)a.C, L.N1,
-                       L.log2M, L.per, L.scale);
+  hipLaunchKernelGGL(fsb_core, grid, dim3(1024), 0, s, L.ws, a.D, (int)a.bf16, line0, (int)a.C, L.N1, L.log2M, L.per,
+                     L.scale);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   return d_b_cols_inv(L);
 }

@@ -1,4 +1,5 @@
-// Multi-pass 1D plan for lines longer than the single-pass limit.
+// Multi-pass 1D plan for circular lines longer than the single-pass limit, and
+// for linear ones with the fused modal filter (the others: conv1d_ra.hip).
 //
 // The real line of transform length P is read as its even/odd packed complex
 // line z[m] = x[2m] + i x[2m+1] of length M = P/2, and the length-M transform
@@ -26,17 +27,14 @@ namespace hyenand {
 
 namespace {
 
-// KC: k is the centered kernel of 2L - 1 points (linear transform grid); its
-// column lines have no zero half.
-template <int N1, bool CIRC, typename TS, bool KC = false, bool ACT = false>
+template <int N1, bool CIRC, typename TS, bool ACT = false>
 __global__ void __launch_bounds__(ColCfgFwd<N1>::NT) __attribute__((amdgpu_waves_per_eu(ColCfgFwd<N1>::kWaves)))
     fs_cols_fwd(const TS* __restrict__ x1, const TS* __restrict__ v, const TS* __restrict__ k,
                 float2* __restrict__ ws, int64_t line0, int N2, int log2M, int64_t per_line, int kC, ActIn ain,
                 int C, int u_only) {
-  static_assert(!(KC && CIRC), "centered kernels use the linear transform grid");
   using Cf = ColCfgFwd<N1>;
   constexpr int E = Cf::E, T = Cf::T, NT = Cf::NT, TL = Cf::TL, TLP = Cf::TLP;
-  constexpr int NZ = CIRC ? N1 : N1 / 2;  // nonzero rows m1 of u (and of k unless centered)
+  constexpr int NZ = CIRC ? N1 : N1 / 2;  // nonzero rows m1
   static_assert(NT / T >= TL, "one round covers the tile");
   __shared__ float2 tile[N1 * TLP];  // exchange scratch, one column per line
   __shared__ float2 twl[imax(1, PassTw<N1, E>::kCount)];
@@ -62,32 +60,16 @@ __global__ void __launch_bounds__(ColCfgFwd<N1>::NT) __attribute__((amdgpu_waves
   // column points straight from global memory into registers (lane t holds
   // m1 = t + T e); rows at or beyond NZ are the zero padding
   float2 w[E];
-  if (KC && sig == 1) {
-    // grid points 2m, 2m + 1 (m = m1 N2 + m2) from the 2L - 1 centered points
-    const TS* kl = k + (size_t)k_line(line0 + line, kC) * (size_t)(2 * L - 1);
-    const int Li = (int)L;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int m1 = t + T * e;
-      w[e] = czero();
-      if (act) {
-        const int g = 2 * (m1 * N2 + c0 + cc);
-        const int ja = centered_index(g, Li, 2 * Li), jb = centered_index(g + 1, Li, 2 * Li);
-        w[e] = make_float2(ja >= 0 ? ld1(kl + ja) : 0.f, jb >= 0 ? ld1(kl + jb) : 0.f);
-      }
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int m1 = t + T * e;
-      w[e] = czero();
-      if (act && (CIRC || m1 < NZ)) {
-        const size_t n = gbase + 2 * ((size_t)m1 * N2 + c0 + cc);
-        if (sig == 0) {
-          w[e] = line_gates<ACT, TS>(ain, line0 + line, C).u2(ld2(x1 + n), ld2(v + n), (int64_t)(n - gbase));
-        } else {
-          w[e] = ld2(k + n - gbase + kbase);
-        }
+  for (int e = 0; e < E; ++e) {
+    const int m1 = t + T * e;
+    w[e] = czero();
+    if (act && (CIRC || m1 < NZ)) {
+      const size_t n = gbase + 2 * ((size_t)m1 * N2 + c0 + cc);
+      if (sig == 0) {
+        w[e] = line_gates<ACT, TS>(ain, line0 + line, C).u2(ld2(x1 + n), ld2(v + n), (int64_t)(n - gbase));
+      } else {
+        w[e] = ld2(k + n - gbase + kbase);
       }
     }
   }
@@ -359,15 +341,17 @@ hipError_t cols_fwd(const FsLaunch& L) {
   }
 #define HY_ARGS(TS) \
   (const TS*)a.x1, (const TS*)a.v, (const TS*)a.k, L.ws, L.line0, kN2, L.log2M, L.per, a.kC, a.act_in, (int)a.C, u_only
-#define HY_LAUNCH(CI, TS, KC)                                                                                     \
-  if (a.act) hipLaunchKernelGGL((fs_cols_fwd<N1, CI, TS, KC, true>), grid, dim3(ColCfgFwd<N1>::NT), 0, L.s, HY_ARGS(TS)); \
-  else hipLaunchKernelGGL((fs_cols_fwd<N1, CI, TS, KC, false>), grid, dim3(ColCfgFwd<N1>::NT), 0, L.s, HY_ARGS(TS));
-  if (a.centered) {
-    if (a.bf16) { HY_LAUNCH(false, uint16_t, true) } else { HY_LAUNCH(false, float, true) }
+#define HY_LAUNCH(CI, TS, ACT) \
+  hipLaunchKernelGGL((fs_cols_fwd<N1, CI, TS, ACT>), grid, dim3(ColCfgFwd<N1>::NT), 0, L.s, HY_ARGS(TS))
+  if (!a.circular) {  // u beside the generated filter
+    if (a.bf16) HY_LAUNCH(false, uint16_t, false);
+    else HY_LAUNCH(false, float, false);
   } else if (a.bf16) {
-    if (a.circular) { HY_LAUNCH(true, uint16_t, false) } else { HY_LAUNCH(false, uint16_t, false) }
+    if (a.act) HY_LAUNCH(true, uint16_t, true);
+    else HY_LAUNCH(true, uint16_t, false);
   } else {
-    if (a.circular) { HY_LAUNCH(true, float, false) } else { HY_LAUNCH(false, float, false) }
+    if (a.act) HY_LAUNCH(true, float, true);
+    else HY_LAUNCH(true, float, false);
   }
 #undef HY_LAUNCH
 #undef HY_ARGS
@@ -380,13 +364,17 @@ hipError_t cols_inv(const FsLaunch& L) {
   const dim3 grid((unsigned)((int64_t)L.nl * (kN2 / TL)));
   const FftConvArgs& a = *L.a;
 #define HY_ARGS(TS) L.ws, (const TS*)a.x2, (TS*)a.y, L.line0, kN2, L.per
-#define HY_LAUNCH(CI, TS)                                                                                  \
-  if (a.act) hipLaunchKernelGGL((fs_cols_inv<N1, CI, TS, true>), grid, dim3(ColCfgFwd<N1>::NT), 0, L.s, HY_ARGS(TS)); \
-  else hipLaunchKernelGGL((fs_cols_inv<N1, CI, TS, false>), grid, dim3(ColCfgFwd<N1>::NT), 0, L.s, HY_ARGS(TS));
-  if (a.bf16) {
-    if (a.circular) { HY_LAUNCH(true, uint16_t) } else { HY_LAUNCH(false, uint16_t) }
+#define HY_LAUNCH(CI, TS, ACT) \
+  hipLaunchKernelGGL((fs_cols_inv<N1, CI, TS, ACT>), grid, dim3(ColCfgFwd<N1>::NT), 0, L.s, HY_ARGS(TS))
+  if (!a.circular) {
+    if (a.bf16) HY_LAUNCH(false, uint16_t, false);
+    else HY_LAUNCH(false, float, false);
+  } else if (a.bf16) {
+    if (a.act) HY_LAUNCH(true, uint16_t, true);
+    else HY_LAUNCH(true, uint16_t, false);
   } else {
-    if (a.circular) { HY_LAUNCH(true, float) } else { HY_LAUNCH(false, float) }
+    if (a.act) HY_LAUNCH(true, float, true);
+    else HY_LAUNCH(true, float, false);
   }
 #undef HY_LAUNCH
 #undef HY_ARGS
@@ -424,7 +412,8 @@ size_t fourstep_bytes_per_line(const FftConvArgs& a) {
 }
 
 hipError_t launch_fourstep(const FftConvArgs& a, int64_t line0, int64_t nl, void* ws, hipStream_t s) {
-  if (!fourstep_supported(a) || nl < 1 || line0 < 0 || line0 + nl > a.lines) return hipErrorInvalidValue;
+  // the linear and centered lines run in conv1d_ra.hip, but for the fused modal filter
+  if (!fourstep_supported(a) || (!a.circular && (a.modal.M == 0 || a.act)) || nl < 1 || line0 < 0 || line0 + nl > a.lines) return hipErrorInvalidValue;
   FsLaunch L;
   L.a = &a;
   L.ws = (float2*)ws;

@@ -204,18 +204,18 @@ static hipError_t launch_1d_fused_t(const FftConvArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// non-circular lines from 1024 transform points on run in conv1d_ra.hip
 template <int P>
 static hipError_t launch_1d_fused_p(const FftConvArgs& a, hipStream_t s) {
-  if constexpr (P >= 4) {
-    if (a.centered)
-      return a.bf16 ? launch_1d_fused_t<P, false, uint16_t, true>(a, s) : launch_1d_fused_t<P, false, float, true>(a, s);
-  } else {
-    if (a.centered) return hipErrorInvalidValue;
-  }
-  if (a.circular) {
+  if (a.circular)
     return a.bf16 ? launch_1d_fused_t<P, true, uint16_t>(a, s) : launch_1d_fused_t<P, true, float>(a, s);
+  if constexpr (P < 1024) {
+    if (!a.centered)
+      return a.bf16 ? launch_1d_fused_t<P, false, uint16_t>(a, s) : launch_1d_fused_t<P, false, float>(a, s);
+    if constexpr (P >= 4)
+      return a.bf16 ? launch_1d_fused_t<P, false, uint16_t, true>(a, s) : launch_1d_fused_t<P, false, float, true>(a, s);
   }
-  return a.bf16 ? launch_1d_fused_t<P, false, uint16_t>(a, s) : launch_1d_fused_t<P, false, float>(a, s);
+  return hipErrorInvalidValue;
 }
 
 bool fused1d_supported(int64_t P) { return P >= 2 && P <= 16384 && (P & (P - 1)) == 0; }

@@ -7,7 +7,7 @@
 // gathered point by point (rows of odd length are not pair-aligned), the zero
 // padding is never stored, and the crop keeps the first L points.
 //
-//  * conv1d_rl<P>: 1D lines, P <= 16384.
+//  * conv1d_rl<P>: 1D lines, P <= 512 (longer ones: conv1d_ra.hip).
 //  * conv2d_rl<P0, P1>: 2D images whose U and K half spectra fit in LDS side
 //    by side (linear: L0 + L0 rows; centered: L0 + P0 rows).
 //
@@ -408,11 +408,6 @@ hipError_t launch_fused_rl(const FftConvArgs& a, hipStream_t s) {
       case 128: return launch_1d_p<128>(a, s);
       case 256: return launch_1d_p<256>(a, s);
       case 512: return launch_1d_p<512>(a, s);
-      case 1024: return launch_1d_p<1024>(a, s);
-      case 2048: return launch_1d_p<2048>(a, s);
-      case 4096: return launch_1d_p<4096>(a, s);
-      case 8192: return launch_1d_p<8192>(a, s);
-      case 16384: return launch_1d_p<16384>(a, s);
       default: return hipErrorInvalidValue;
     }
   }

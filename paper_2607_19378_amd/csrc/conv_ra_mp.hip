@@ -91,14 +91,17 @@ __global__ void __launch_bounds__(kRaNT)
       } else {
         const int64_t o = (int64_t)lr * g.LL + t;
         const TS* const a = x + (w ? gl : k_line(gl, kC)) * g.data + o;
-        const TS* const b = w + gl * g.data + o;
+        const TS* const b = w + (w ? gl * g.data + o : 0);
         const Gates<ACT> G = line_gates<ACT, TS>(ain, gl, C);
         float p[E], q[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-          const bool in = act && t + T * e < g.LL;
-          p[e] = in ? ld1(a + T * e) : 0.f;
-          q[e] = in && w ? ld1(b + T * e) : 1.f;
+          p[e] = ra_ld_in(a - t, t + T * e, act && t + T * e < g.LL);
+          q[e] = 1.f;
+        }
+        if (w) {
+#pragma unroll
+          for (int e = 0; e < E; ++e) q[e] = ra_ld_in(b - t, t + T * e, act && t + T * e < g.LL);
         }
 #pragma unroll
         for (int e = 0; e < E; ++e) {
@@ -153,6 +156,9 @@ __global__ void __launch_bounds__(kRaNT)
     float2 v[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) v[e] = src[T * e];
+    const int64_t o0 = gl * g.data + (int64_t)lr * g.LL;  // the row's first point (not dbl)
+    RaGates<E> gt;
+    if (!vec && !dbl) gt.load(out, p, q, o0, t, T, g.LL, act);
     Row::inverse(v, t, row, tw);
     if (dbl) {
       if (act) {
@@ -174,13 +180,7 @@ __global__ void __launch_bounds__(kRaNT)
       const int64_t o = line0 * g.data + (int64_t)rw * g.LL;
       ra_rows_out<Row::PITCH, Cf::RW, N, ACT>(out, p + o, q + o, o1 + o, o2 + o, nrows, g.LL, wrow, lane);
     } else if (act) {
-      const int64_t o = gl * g.data + (int64_t)lr * g.LL + t;
-#pragma unroll
-      for (int e = 0; e < E; ++e)
-        if (t + T * e < g.LL) {
-          if (out == RA_GK) st1(o1 + o + T * e, Row::re(v[e], e));
-          else ra_store<TS, ACT>(out, p, q, o1, o2, o + T * e, Row::re(v[e], e));
-        }
+      gt.template store<ACT>(out, o1, o2, o0, t, T, g.LL, [&](int e) { return Row::re(v[e], e); });
     }
   }
 }
@@ -500,6 +500,12 @@ hipError_t inverse_axes(const RaPass& p, const RaIos& ios) {
   return e == hipSuccess && !p.g.slab ? d_rows_inverse(p, ios) : e;
 }
 
+int64_t line_points(const FftConvArgs& a) {
+  int64_t n = 1;
+  for (int d = 0; d < a.ndim; ++d) n *= a.L[d];
+  return n;
+}
+
 RaPass make_pass(const FftConvArgs& a, const RaGeom& g, bool bwd, int64_t line0, int64_t nl, void* ws, hipStream_t s) {
   RaPass p;
   p.a = &a;
@@ -553,14 +559,14 @@ hipError_t launch_ra_mp_backward(const FftConvBwdArgs& b, int64_t line0, int64_t
 }
 
 int64_t ra_mp_partials_per_line(const FftConvArgs& a) {
-  const int64_t n = (ra_geom(a).data + kHuPts - 1) / kHuPts;
+  const int64_t n = (line_points(a) + kHuPts - 1) / kHuPts;
   return n < 64 ? n : 64;
 }
 
 hipError_t launch_ra_mp_hu(const FftConvBwdArgs& b, float* partial, hipStream_t s) {
   const FftConvArgs& a = b.f;
   const int parts = (int)ra_mp_partials_per_line(a);
-  const int64_t data = ra_geom(a).data;
+  const int64_t data = line_points(a);
   const dim3 grid((unsigned)(a.lines * parts));
   if (a.bf16)
     hipLaunchKernelGGL((ra_hu<uint16_t>), grid, dim3(256), 0, s, (const uint16_t*)a.x1, (const uint16_t*)a.v,

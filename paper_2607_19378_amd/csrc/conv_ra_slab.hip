@@ -121,8 +121,14 @@ __global__ void __launch_bounds__((SlabFwd<P1, N>::NT)) __attribute__((amdgpu_wa
             for (int e = 0; e < ER; ++e) {
               const int n = TR * e + f * NC;
               const bool in = tr + n < g.LL;
-              a[f][e] = !in ? 0.f : (vrow ? reinterpret_cast<const float*>(S + r * PITCH)[tr + n] : ld1(kl + o + n));
-              b[f][e] = gated && in && !vrow ? ld1(wl + o + n) : 1.f;
+              b[f][e] = 1.f;
+              if (vrow) {
+                const float u = reinterpret_cast<const float*>(S + r * PITCH)[tr + n];
+                a[f][e] = in ? u : 0.f;
+              } else {
+                a[f][e] = ra_ld_in(kl + o - tr, tr + n, in);
+                if (gated) b[f][e] = ra_ld_in(wl + o - tr, tr + n, in);
+              }
             }
 #pragma unroll
           for (int e = 0; e < ER; ++e) {
@@ -244,6 +250,9 @@ __global__ void __launch_bounds__((SlabInv<P1, N>::NT)) __attribute__((amdgpu_wa
 #pragma unroll
         for (int e = 0; e < ER; ++e) v[e] = pr[(TR / 2) * e + (TR / 2 * e) / ER];
       }
+      const int64_t lr = (int64_t)pl * g.L1 + r;
+      RaGates<ER> gt;
+      if (!vec && !dbl) gt.load(OUT, p, q, gl * g.data + lr * g.LL, tr, TR, g.LL, true);
       Row::inverse(v, tr, row, itw);
       if (vec && !dbl) {
         wave_sync();
@@ -252,28 +261,18 @@ __global__ void __launch_bounds__((SlabInv<P1, N>::NT)) __attribute__((amdgpu_wa
         for (int e = 0; e < ER; ++e) rf[TR * e] = Row::re(v[e], e);
         continue;
       }
-      const int64_t lr = (int64_t)pl * g.L1 + r;
-      if constexpr (OUT == RA_GK) {
-        if (dbl) {
-          const RaKRow kr = ra_krow(g, pl - (g.L0 - 1), d1);
-          TS* const d = o1 + gl * g.kpts + kr.row;
+      if (dbl) {
+        const RaKRow kr = ra_krow(g, pl - (g.L0 - 1), d1);
+        TS* const d = o1 + gl * g.kpts + kr.row;
 #pragma unroll
-          for (int e = 0; e < ER; ++e) {
-            const int n = tr + TR * e;
-            if (n < g.LL) st1(d + kr.reo + n, Row::re(v[e], e));
-            if (n > g.N - g.LL) st1(d + kr.imo + n, Row::im(v[e], e));
-          }
-        } else {
-          TS* const d = o1 + gl * g.kpts + lr * g.LL + tr;
-#pragma unroll
-          for (int e = 0; e < ER; ++e)
-            if (tr + TR * e < g.LL) st1(d + TR * e, Row::re(v[e], e));
+        for (int e = 0; e < ER; ++e) {
+          const int n = tr + TR * e;
+          if (n < g.LL) st1(d + kr.reo + n, Row::re(v[e], e));
+          if (n > g.N - g.LL) st1(d + kr.imo + n, Row::im(v[e], e));
         }
       } else {
-        const int64_t o = gl * g.data + lr * g.LL + tr;
-#pragma unroll
-        for (int e = 0; e < ER; ++e)
-          if (tr + TR * e < g.LL) ra_store<TS, ACT>(OUT, p, q, o1, o2, o + TR * e, Row::re(v[e], e));
+        gt.template store<ACT>(OUT, o1, o2, gl * g.data + lr * g.LL, tr, TR, g.LL,
+                               [&](int e) { return Row::re(v[e], e); });
       }
     }
   }

@@ -279,6 +279,12 @@ bool runs_ra_mp(const FftConvArgs& a, Plan p) {
          ra_mp_bytes_per_line(a, false) <= bytes_per_line(a, p);
 }
 
+// The same for lines (conv1d_ra.hip).
+bool runs_ra_line(const FftConvArgs& a, Plan p) {
+  return (p == PLAN_FOURSTEP || p == PLAN_EMBED) && ra_line_supported(a) &&
+         ra_line_bytes_per_line(a, false) <= bytes_per_line(a, p);
+}
+
 // Side streams of the multi-pass plans, and the events that fork them off
 // the caller's stream and join them back: one set per (host thread, device),
 // created on that thread's first multi-pass call on the device (default
@@ -475,6 +481,18 @@ bool bwd_runs_ra_mp(const FftConvArgs& a, BwdPlan p, size_t least) {
          ra_partial_bytes(a) + ra_mp_bytes_per_line(a, true) <= least;
 }
 
+bool bwd_runs_ra_line(const FftConvArgs& a, BwdPlan p, size_t least) {
+  return (p == BWD_FOURSTEP || p == BWD_EMBED) && ra_line_supported(a) && !a.periodic &&
+         ra_partial_bytes(a) + ra_line_bytes_per_line(a, true) <= least;
+}
+// one float per line of workspace, which every plan has (HYENAND_PLAN=mixed
+// keeps lines on the mixed-radix kernels)
+bool bwd_runs_ra1d(const FftConvArgs& a, BwdPlan p) {
+  const char* force = getenv("HYENAND_PLAN");
+  const bool mixed = p == BWD_MIXED && force && strcmp(force, "mixed") == 0;
+  return p != BWD_NONE && !mixed && ra1d_backward_supported(a);
+}
+
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
   const uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;
   return a0 < b0 + nb && b0 < a0 + na;
@@ -557,11 +575,30 @@ hyenand_status hyenand_fftconv_plan_name(int ndim, const int64_t* dims, hyenand_
 
 namespace {
 
+bool mixed_forced() {
+  const char* force = getenv("HYENAND_PLAN");
+  return force && strcmp(force, "mixed") == 0;
+}
+
+// Circular lines reach the mixed-radix kernels with a transform of their own L
+// points; a right-angle one of N >= L points is the faster when it is not much
+// longer (1024 lines of 1000 points, N = 1024: 13.0 against 16.3 us, of 3000
+// points, N = 4096: 28.9 against 42.3).
+bool mixed_line_on_ra1d(const FftConvArgs& a) {
+  return ra1d_supported(a) && !mixed_forced() && 5 * (a.P[0] / 2) <= 7 * a.L[0];
+}
+
+hipError_t run_ra_line(const FftConvArgs& a, hipStream_t s) {
+  return run_chunked(a, ra_line_bytes_per_line(a, false), s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
+    return launch_ra_line(a, l0, nl, ws, st);
+  }, a.rl);
+}
+
 // Every step of the path for a validated call: the plan's kernels, chunked
 // over side streams for the multi-pass plans.
 hipError_t launch_plan(const FftConvArgs& a, Plan p, size_t per, hipStream_t s) {
   switch (p) {
-    case PLAN_FUSED1D: return launch_fused1d(a, s);
+    case PLAN_FUSED1D: return ra1d_supported(a) ? launch_ra1d(a, s) : launch_fused1d(a, s);
     case PLAN_FUSED2D: return launch_fused2d(a, s);
     case PLAN_EMBED:  // forward() embeds the other shapes itself
     case PLAN_MULTIPASS:
@@ -569,16 +606,18 @@ hipError_t launch_plan(const FftConvArgs& a, Plan p, size_t per, hipStream_t s) 
         return run_chunked(a, ra_mp_bytes_per_line(a, false), s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
           return launch_ra_mp(a, l0, nl, ws, st);
         }, a.rl);
+      if (runs_ra_line(a, p)) return run_ra_line(a, s);
       if (p == PLAN_EMBED) return hipErrorInvalidValue;
       return run_chunked(a, per, s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
         return launch_multipass(a, l0, nl, ws, st);
       });
     case PLAN_FOURSTEP:
+      if (runs_ra_line(a, p)) return run_ra_line(a, s);
       return run_chunked(a, per, s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
         return launch_fourstep(a, l0, nl, ws, st);
       });
-    case PLAN_FUSED_RL: return launch_fused_rl(a, s);
-    case PLAN_MIXED: return launch_mixed(a, s);
+    case PLAN_FUSED_RL: return ra1d_supported(a) ? launch_ra1d(a, s) : launch_fused_rl(a, s);
+    case PLAN_MIXED: return mixed_line_on_ra1d(a) ? launch_ra1d(a, s) : launch_mixed(a, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -663,7 +702,7 @@ hyenand_status forward(const void* x1, const void* x2, const void* v, const void
   a.ws_bytes = workspace_bytes;
   a.khat = use_khat ? (float2*)workspace : nullptr;
   clear_pending_error();
-  if (p == PLAN_EMBED && !runs_ra_mp(a, p)) {
+  if (p == PLAN_EMBED && !runs_ra_mp(a, p) && !runs_ra_line(a, p)) {
     // x1, x2, v, k into the transform grid, the circular plan there, y back
     GridProblem m;
     embedded_inner_plan(a, &m);
@@ -945,16 +984,21 @@ hyenand_status hyenand_fftconv_backward(const void* x1, const void* x2, const vo
   const hipStream_t s = (hipStream_t)stream;
   hipError_t err = hipSuccess;
   clear_pending_error();
-  if (bwd_runs_ra_mp(a, p, need)) {
+  if (bwd_runs_ra1d(a, p)) {
+    err = launch_ra1d_backward(b, s);
+    if (err == hipSuccess) err = launch_backward_reduce(b, 1, s);
+  } else if (const bool line = bwd_runs_ra_line(a, p, need); line || bwd_runs_ra_mp(a, p, need)) {
     FftConvArgs sa = b.f;
     const size_t rb = ra_partial_bytes(a);
     sa.ws = (char*)workspace + rb;
     sa.ws_bytes = workspace_bytes - rb;
     err = launch_ra_mp_hu(b, b.partial, s);
     if (err == hipSuccess)
-      err = run_chunked(sa, ra_mp_bytes_per_line(a, true), s, [&b](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
-        return launch_ra_mp_backward(b, l0, nl, ws, st);
-      }, a.rl);
+      err = run_chunked(sa, line ? ra_line_bytes_per_line(a, true) : ra_mp_bytes_per_line(a, true), s,
+                        [&b, line](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
+                          return line ? launch_ra_line_backward(b, l0, nl, ws, st)
+                                      : launch_ra_mp_backward(b, l0, nl, ws, st);
+                        }, a.rl);
     if (err == hipSuccess) err = launch_backward_reduce(b, ra_mp_partials_per_line(a), s);
   } else if (p == BWD_EMBED) {
     char* w = (char*)workspace;

@@ -97,6 +97,14 @@ bool ra_mp_supported(const FftConvArgs& a);
 size_t ra_mp_bytes_per_line(const FftConvArgs& a, bool backward);
 hipError_t launch_ra_mp(const FftConvArgs& a, int64_t line0, int64_t nl, void* ws, hipStream_t s);
 
+// non-circular lines on right-angle transforms, of any length (conv1d_ra.hip):
+// up to 8192 points in one pass, beyond in three
+bool ra1d_supported(const FftConvArgs& a);
+hipError_t launch_ra1d(const FftConvArgs& a, hipStream_t s);
+bool ra_line_supported(const FftConvArgs& a);
+size_t ra_line_bytes_per_line(const FftConvArgs& a, bool backward);
+hipError_t launch_ra_line(const FftConvArgs& a, int64_t line0, int64_t nl, void* ws, hipStream_t s);
+
 // backward
 struct FftConvBwdArgs {
   FftConvArgs f;  // shapes and the forward inputs (f.y unused)
@@ -124,6 +132,11 @@ bool ra_mp_backward_supported(const FftConvArgs& a);
 int64_t ra_mp_partials_per_line(const FftConvArgs& a);
 hipError_t launch_ra_mp_hu(const FftConvBwdArgs& b, float* partial, hipStream_t s);  // the gD sums of all lines
 hipError_t launch_ra_mp_backward(const FftConvBwdArgs& b, int64_t line0, int64_t nl, void* ws, hipStream_t s);
+// 1D on right-angle transforms (conv1d_ra.hip): single pass up to 8192 points
+// (one float of partial per line, without the gD reduction), or three passes
+bool ra1d_backward_supported(const FftConvArgs& a);
+hipError_t launch_ra1d_backward(const FftConvBwdArgs& b, hipStream_t s);
+hipError_t launch_ra_line_backward(const FftConvBwdArgs& b, int64_t line0, int64_t nl, void* ws, hipStream_t s);
 // mixed-radix single pass (conv_mixed.hip) on the forward's transform grid,
 // grids of up to about 3000 points; one float of partial per line
 bool mixed_backward_supported(const FftConvArgs& a);

@@ -88,9 +88,25 @@ __device__ __forceinline__ RaKRow ra_krow(const RaGeom& g, int d0, int d1) {
   }
   return r;
 }
+// p[i], or 0 where not in (p[0] is read instead).
+template <typename TS>
+__device__ __forceinline__ float ra_ld_sel(const TS* p, int64_t i, bool in) {
+  const float v = ld1(p + (in ? i : 0));
+  return in ? v : 0.f;
+}
+// The same where many lanes are out (a kernel row fills part of its line):
+// fp32 loads under their condition (rows of 200 x 150 kernels 140 -> 78 us).
+// The compiler would widen a conditional bf16 load under its condition, so
+// each would be waited for before the next is issued.
+template <typename TS>
+__device__ __forceinline__ float ra_ld_in(const TS* p, int64_t i, bool in) {
+  if constexpr (sizeof(TS) == 4) return in ? ld1(p + i) : 0.f;
+  return ra_ld_sel(p, i, in);
+}
 template <typename TS>
 __device__ __forceinline__ float2 ra_kvalue(const TS* kl, const RaKRow& r, const RaGeom& g, int n) {
-  return make_float2(n < g.LL ? ld1(kl + r.row + r.reo + n) : 0.f, n > g.N - g.LL ? ld1(kl + r.row + r.imo + n) : 0.f);
+  const TS* const p = kl + r.row + r.reo;
+  return make_float2(ra_ld_in(p, n, n < g.LL), ra_ld_in(p, n + r.imo - r.reo, n > g.N - g.LL));
 }
 
 // Rows between memory and LDS in 16-byte accesses.  A wavefront's rows are
@@ -183,16 +199,46 @@ __device__ __forceinline__ void ra_rows_out(RaOut out, const TS* p, const TS* q,
   wave_sync();
 }
 
-// one point of an inverse pass: z at data point o (line base + index)
-template <typename TS, bool ACT>
-__device__ __forceinline__ void ra_store(RaOut out, const TS* p, const TS* q, TS* o1, TS* o2, int64_t o, float z) {
-  if (out == RA_Y) st1(o1 + o, Gates<ACT>{}.g1(ld1(p + o)) * z);
-  if (out == RA_GX2) st1(o1 + o, ld1(p + o) * z);
-  if (out == RA_GU) {
-    st1(o1 + o, z * ld1(p + o));
-    st1(o2 + o, z * ld1(q + o));
+// The gates of a lane's points i + step e, fetched before the inverse
+// transform, and the points' store after it (n < LL).
+template <int E>
+struct RaGates {
+  float p[E], q[E];
+  template <typename TS>
+  __device__ __forceinline__ void load(RaOut out, const TS* pp, const TS* qq, int64_t base, int64_t n0, int64_t step,
+                                       int64_t L, bool act) {
+    if (out == RA_GK) return;
+#pragma unroll
+    for (int e = 0; e < E; ++e) p[e] = ra_ld_in(pp + base, n0 + step * e, act && n0 + step * e < L);
+    if (out == RA_GU) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) q[e] = ra_ld_in(qq + base, n0 + step * e, act && n0 + step * e < L);
+    }
   }
-}
+  template <bool ACT, typename TS, class Re>
+  __device__ __forceinline__ void store(RaOut out, TS* o1, TS* o2, int64_t base, int64_t n0, int64_t step, int64_t L,
+                                        const Re& re) const {
+    TS* const a = o1 + base + n0;
+    if (out == RA_GU) {
+      TS* const b = o2 + base + n0;
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (n0 + step * e < L) {
+          const float z = re(e);
+          st1(a + step * e, z * p[e]);
+          st1(b + step * e, z * q[e]);
+        }
+    } else if (out == RA_GK) {
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (n0 + step * e < L) st1(a + step * e, re(e));
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (n0 + step * e < L) st1(a + step * e, (out == RA_Y ? Gates<ACT>{}.g1(p[e]) : p[e]) * re(e));
+    }
+  }
+};
 
 }  // namespace
 }  // namespace hyenand

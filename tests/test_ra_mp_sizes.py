@@ -30,3 +30,13 @@ def test_power_of_two_grids_fit(monkeypatch):
         sums = (min(64, -(-data // 8192)) * 4 + 255) // 256 * 256
         assert sums + _ra_bytes(grid, mode, True) <= H.backward_workspace_min(shape, mode, "f32") or max(grid[:2]) <= 64 \
             and len(grid) == 2, (grid, mode)
+
+
+def test_lines_fit():
+    """Three-pass lines: two (backward three) spectra of N = P / 2 points, and the sums of h u."""
+    for L, mode in itertools.product((16384, 20000, 65537, 300001, 1 << 20, 1 << 21), ("linear", "centered")):
+        n = 1 << (2 * L - 2).bit_length() - 1
+        shape = (1, 1, L)
+        assert 2 * n * 8 <= H.workspace_min(shape, mode, "f32"), (L, mode)
+        sums = (min(64, -(-L // 8192)) * 4 + 255) // 256 * 256
+        assert sums + 3 * n * 8 <= H.backward_workspace_min(shape, mode, "f32"), (L, mode)
