@@ -20,7 +20,7 @@
 // one image per CU, its loads, arithmetic and stores in turn; at 128 VGPRs it
 // spills (360 us).  Keeping a workgroup resident and fetching the next image's
 // inputs during the inverse rows spilled too (80 us forward).
-#include "ra_device.hpp"
+#include "ra_mp.hpp"
 
 namespace hyenand {
 
@@ -38,35 +38,70 @@ struct Ra2D {
   static_assert(P0 % RPR == 0 && (NR == 1 || RPR == L0), "rounds hold whole signals or both");
 };
 
-// k of one line: kernel point of displacement (d0, d1)
-template <bool KC, int L0, int L1, typename TS>
-__device__ __forceinline__ float2 ra_kernel_point(const TS* kl, int g0, int n, float scale) {
-  if constexpr (!KC) {
-    return make_float2(ld1(kl + g0 * L1 + n) * scale, 0.f);
-  } else {
-    constexpr int K1 = 2 * L1 - 1;
-    float2 z = czero();
-    if (g0 != L0) {  // row L0 holds no displacement
-      const TS* kr = kl + (g0 < L0 ? g0 + L0 - 1 : g0 - L0 - 1) * K1;
-      z.x = ld1(kr + L1 - 1 + n) * scale;
-      if (n > 0) z.y = ld1(kr + n - 1) * scale;
-    }
-    return z;
+// Rows of an image and of its kernel in the region.  RAG: M0 x M1 points in the
+// corner of the L0 x L1 that the transforms take, the rest zeros.
+template <bool RAG, int P0, int N>
+struct RaImage {
+  int m0, m1;
+  bool per;  // k of a circular mode: displacement d is point d mod M
+  __device__ __forceinline__ RaImage(int M0, int M1, bool p) : m0(RAG ? M0 : P0 / 2), m1(RAG ? M1 : N), per(RAG && p) {}
+  __device__ __forceinline__ bool row(int r) const { return !RAG || r < m0; }
+  __device__ __forceinline__ bool in(int r, int n) const { return !RAG || (r < m0 && n < m1); }
+  __device__ __forceinline__ int points() const { return m0 * m1; }
+  template <bool KC>
+  __device__ __forceinline__ int kpoints() const {
+    return KC && !per ? (2 * m0 - 1) * (2 * m1 - 1) : m0 * m1;
   }
-}
+  // value i (of a row at p), zero outside the image
+  template <typename TS>
+  __device__ __forceinline__ float ld(const TS* p, int i, bool inside) const {
+    return RAG ? ra_ld_sel(p, i, inside) : ld1(p + i);
+  }
+  // centered kernels: row g0 of the double grid holds a displacement, and which
+  __device__ __forceinline__ bool krow(int g0) const { return RAG ? g0 < m0 || g0 > P0 - m0 : g0 != P0 / 2; }
+  __device__ __forceinline__ int kofs(int g0) const {
+    if (per) return (g0 < P0 / 2 ? g0 : g0 - P0 + m0) * m1;
+    return (g0 < P0 / 2 ? g0 + m0 - 1 : g0 - P0 + m0 - 1) * (2 * m1 - 1);
+  }
+  // column n: displacements n and n - N
+  __device__ __forceinline__ bool kre(int n) const { return !RAG || n < m1; }
+  __device__ __forceinline__ bool kim(int n) const { return RAG ? n > N - m1 : n > 0; }
+  __device__ __forceinline__ int kre_ofs(int n) const { return per ? n : n + m1 - 1; }
+  __device__ __forceinline__ int kim_ofs(int n) const { return per ? n - N + m1 : n - N + m1 - 1; }
+  // k of one line: the points of row g0, column n
+  template <bool KC, typename TS>
+  __device__ __forceinline__ float2 kernel_point(const TS* kl, int g0, int n, float scale) const {
+    if constexpr (!KC) {
+      return make_float2(ld(kl, g0 * m1 + n, in(g0, n)) * scale, 0.f);
+    } else if constexpr (RAG) {
+      const bool r = krow(g0);
+      const int o = kofs(g0);
+      return make_float2(ld(kl, o + kre_ofs(n), r && kre(n)) * scale, ld(kl, o + kim_ofs(n), r && kim(n)) * scale);
+    } else {
+      float2 z = czero();
+      if (krow(g0)) {  // row L0 holds no displacement
+        const TS* kr = kl + kofs(g0);
+        z.x = ld1(kr + kre_ofs(n)) * scale;
+        if (kim(n)) z.y = ld1(kr + kim_ofs(n)) * scale;
+      }
+      return z;
+    }
+  }
+};
 
 // KH as in the circular kernel: 0 transforms each image's own k, 1 writes the
 // spectrum of each channel's k to khat[c][n][col] and stops, 2 reads it.
-template <int P0, int N, bool KC, typename TS, bool ACT, int KH>
+template <int P0, int N, bool KC, typename TS, bool ACT, int KH, bool RAG>
 __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves_per_eu(4)))
     conv2d_ra(const TS* __restrict__ x1, const TS* __restrict__ x2, const TS* __restrict__ v,
               const TS* __restrict__ k, const TS* __restrict__ Dp, TS* __restrict__ y, int C, int kC, ActIn ain,
-              float2* __restrict__ khat) {
-  static_assert(KH == 0 || (!KC && !ACT), "kept spectra: linear, plain gates");
+              float2* __restrict__ khat, int M0, int M1, bool per) {
+  static_assert(KH == 0 || (!KC && !ACT && !RAG), "kept spectra: linear, plain gates, powers of two");
   using F = Ra2D<P0, N>;
   using Row = typename F::Row;
   using Col = typename F::Col;
-  constexpr int L0 = F::L0, L1 = F::L1, PITCH = F::PITCH, RPR = F::RPR, NR = F::NR, TR = Row::T;
+  constexpr int L0 = F::L0, PITCH = F::PITCH, RPR = F::RPR, NR = F::NR, TR = Row::T;
+  const RaImage<RAG, P0, N> im(M0, M1, per);
   constexpr int E = Col::E, TC = Col::T;
   constexpr float scale = 1.f / ((float)P0 * (float)N);  // of the unnormalised inverses, a power of two
   __shared__ float2 S[P0 * PITCH];
@@ -87,8 +122,9 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
   float2* const cp = S + Row::slot(col);
   const int r = rr % L0;                          // data row of this lane
   const bool has_u = NR == 2 || rr < L0;          // with one round, lanes rr >= L0 take K's rows
-  const size_t rb = (size_t)img * L0 * L1 + r * L1 + tr;  // its first point
-  const TS* const kl = k + (size_t)k_line(img, kC) * (KC ? (2 * L0 - 1) * (2 * L1 - 1) : L0 * L1);
+  const size_t base = (size_t)img * im.points();
+  const int rb = r * im.m1 + tr;  // its first point
+  const TS* const kl = k + (size_t)k_line(img, kC) * im.template kpoints<KC>();
   const Gates<ACT> G = line_gates<ACT, TS>(ain, img, C);
 
   typename Row::FwdTw ftw;
@@ -96,17 +132,22 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
   auto load_u = [&](float (&a)[8], float (&b)[8]) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      a[e] = ld1(x1 + rb + TR * e);
-      b[e] = ld1(v + rb + TR * e);
+      const bool in = im.in(r, tr + TR * e);
+      a[e] = im.ld(x1 + base, rb + TR * e, in);
+      b[e] = im.ld(v + base, rb + TR * e, in);
     }
   };
   auto gate_u = [&](const float (&a)[8], const float (&b)[8], float2 (&w)[8]) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) w[e] = Row::lead(G.u1(a[e], b[e], r * L1 + tr + TR * e), e);
+    for (int e = 0; e < 8; ++e) {
+      const bool in = im.in(r, tr + TR * e);
+      const float u = G.u1(a[e], b[e], in ? rb + TR * e : 0);
+      w[e] = Row::lead(in ? u : 0.f, e);
+    }
   };
   auto load_k = [&](int g0, float2 (&w)[8]) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) w[e] = ra_kernel_point<KC, L0, L1>(kl, g0, tr + TR * e, scale);
+    for (int e = 0; e < 8; ++e) w[e] = im.template kernel_point<KC>(kl, g0, tr + TR * e, scale);
   };
   auto lead_k = [&](float2 (&w)[8]) {
 #pragma unroll
@@ -212,7 +253,7 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
   typename Row::InvTw itw;
   if (has_u) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) g[e] = ld1(x2 + rb + TR * e);
+    for (int e = 0; e < 8; ++e) g[e] = im.ld(x2 + base, rb + TR * e, im.in(r, tr + TR * e));
     itw.load(tr);
   }
   Col::template run<true>(wu, tc, cp, ctw);
@@ -229,39 +270,40 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
   for (int e = 0; e < 8; ++e) w[e] = row[tr + Row::off(e)];
   Row::inverse(w, tr, row, itw);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) st1(y + rb + TR * e, G.g1(g[e]) * Row::re(w[e], e));
+  for (int e = 0; e < 8; ++e)
+    if (im.in(r, tr + TR * e)) st1(y + base + rb + TR * e, G.g1(g[e]) * Row::re(w[e], e));
 }
 
 // Backward (conv_backward.hip states the products): U and H take the region
 // side by side, then K; the three products' inverses return z and gu together,
 // then gk.  x1, v and gy stay in registers from staging to the epilogue (the
 // lane that stages row r of u and h stores row r of the gradients).
-template <int P0, int N, bool KC, typename TS>
+template <int P0, int N, bool KC, typename TS, bool RAG>
 __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves_per_eu(2)))
     bwd2d_ra(const TS* __restrict__ x1, const TS* __restrict__ x2, const TS* __restrict__ v,
              const TS* __restrict__ k, const TS* __restrict__ Dp, const TS* __restrict__ gy, TS* __restrict__ gx1,
-             TS* __restrict__ gx2, TS* __restrict__ gv, TS* __restrict__ gk, float* __restrict__ partial, int C) {
+             TS* __restrict__ gx2, TS* __restrict__ gv, TS* __restrict__ gk, float* __restrict__ partial, int C, int M0, int M1) {
   using F = Ra2D<P0, N>;
   using Row = typename F::Row;
   using Col = typename F::Col;
-  constexpr int L0 = F::L0, L1 = F::L1, PITCH = F::PITCH, RPR = F::RPR, NR = F::NR, TR = Row::T, NT = F::NT;
+  constexpr int L0 = F::L0, PITCH = F::PITCH, RPR = F::RPR, NR = F::NR, TR = Row::T, NT = F::NT;
+  const RaImage<RAG, P0, N> im(M0, M1, false);
   constexpr int E = Col::E, TC = Col::T;
   constexpr float scale = 1.f / ((float)P0 * (float)N);
   __shared__ float2 S[P0 * PITCH];
   __shared__ float red[imax(1, NT / 64)];
   const int img = blockIdx.x;
   const int c = img % C;
-  const size_t base = (size_t)img * L0 * L1;
-  constexpr int KPTS = KC ? (2 * L0 - 1) * (2 * L1 - 1) : L0 * L1;
-  const TS* const kl = k + (size_t)img * KPTS;
-  TS* const gkl = gk + (size_t)img * KPTS;
+  const size_t base = (size_t)img * im.points();
+  const TS* const kl = k + (size_t)img * im.template kpoints<KC>();
+  TS* const gkl = gk + (size_t)img * im.template kpoints<KC>();
   const int tid = threadIdx.x;
   const int rr = tid / TR, tr = tid % TR;
   const int lane = tid & 63;
   const int col = (tid >> 6) * Col::CW + lane % Col::CW, tc = lane / Col::CW;
   float2* const cp = S + Row::slot(col);
   const int r = rr % L0;                        // data row of this lane
-  const size_t rb = base + (size_t)r * L1 + tr;  // its first point
+  const int rb = r * im.m1 + tr;                // its first point
 
   // rows of u [0, L0) and h [L0, P0)
   float xa[8], xv[8], xg[8];
@@ -277,10 +319,11 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
     float xe[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      xa[e] = ld1(x1 + rb + TR * e);
-      xv[e] = ld1(v + rb + TR * e);
-      xg[e] = ld1(gy + rb + TR * e);
-      xe[e] = ld1(x2 + rb + TR * e);
+      const bool in = im.in(r, tr + TR * e);
+      xa[e] = im.ld(x1 + base, rb + TR * e, in);
+      xv[e] = im.ld(v + base, rb + TR * e, in);
+      xg[e] = im.ld(gy + base, rb + TR * e, in);
+      xe[e] = im.ld(x2 + base, rb + TR * e, in);
     }
     float hu = 0.f;
 #pragma unroll
@@ -307,7 +350,7 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
     const int g0 = q * RPR + rr;
     if (KC || g0 < L0) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) wr[q][e] = ra_kernel_point<KC, L0, L1>(kl, g0, tr + TR * e, scale);
+      for (int e = 0; e < 8; ++e) wr[q][e] = im.template kernel_point<KC>(kl, g0, tr + TR * e, scale);
     }
   }
   __syncthreads();
@@ -379,12 +422,14 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const float g = Row::re(w[e], e);
-        st1(gx1 + rb + TR * e, g * xv[e]);
-        st1(gv + rb + TR * e, g * xa[e]);
+        if (!im.in(r, tr + TR * e)) continue;
+        st1(gx1 + base + rb + TR * e, g * xv[e]);
+        st1(gv + base + rb + TR * e, g * xa[e]);
       }
     } else {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) st1(gx2 + rb + TR * e, Row::re(w[e], e) * xg[e]);
+      for (int e = 0; e < 8; ++e)
+        if (im.in(r, tr + TR * e)) st1(gx2 + base + rb + TR * e, Row::re(w[e], e) * xg[e]);
     }
   }
   __syncthreads();
@@ -406,51 +451,51 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
       Row::inverse(w, tr, row, itw);
       if constexpr (!KC) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) st1(gkl + g0 * L1 + tr + TR * e, Row::re(w[e], e));
-      } else if (g0 != L0) {
-        constexpr int K1 = 2 * L1 - 1;
-        TS* const kr = gkl + (g0 < L0 ? g0 + L0 - 1 : g0 - L0 - 1) * K1;
+        for (int e = 0; e < 8; ++e)
+          if (im.in(g0, tr + TR * e)) st1(gkl + g0 * im.m1 + tr + TR * e, Row::re(w[e], e));
+      } else if (im.krow(g0)) {
+        TS* const kr = gkl + im.kofs(g0);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const int n = tr + TR * e;
-          st1(kr + L1 - 1 + n, Row::re(w[e], e));
-          if (n > 0) st1(kr + n - 1, Row::im(w[e], e));
+          if (im.kre(n)) st1(kr + im.kre_ofs(n), Row::re(w[e], e));
+          if (im.kim(n)) st1(kr + im.kim_ofs(n), Row::im(w[e], e));
         }
       }
     }
   }
 }
 
-template <int P0, int N, typename TS>
+template <int P0, int N, typename TS, bool RAG>
 hipError_t launch_fwd_t(const FftConvArgs& a, hipStream_t s) {
   constexpr int NT = Ra2D<P0, N>::NT;
 #define HY_RA(KC, ACT, KH, GRID)                                                                               \
-  hipLaunchKernelGGL((conv2d_ra<P0, N, KC, TS, ACT, KH>), dim3((unsigned)(GRID)), dim3(NT), 0, s,              \
+  hipLaunchKernelGGL((conv2d_ra<P0, N, KC, TS, ACT, KH, RAG>), dim3((unsigned)(GRID)), dim3(NT), 0, s,              \
                      (const TS*)a.x1, (const TS*)a.x2, (const TS*)a.v, (const TS*)a.k, (const TS*)a.D,         \
-                     (TS*)a.y, (int)a.C, a.kC, a.act_in, a.khat)
-  if (a.centered) {
+                     (TS*)a.y, (int)a.C, a.kC, a.act_in, a.khat, (int)a.L[0], (int)a.L[1], a.periodic)
+  if (a.centered || a.periodic) {
     if (a.act) HY_RA(true, true, 0, a.lines);
     else HY_RA(true, false, 0, a.lines);
   } else if (a.act) {
     HY_RA(false, true, 0, a.lines);
-  } else if (a.khat) {
+  } else if (RAG || !a.khat) {
+    HY_RA(false, false, 0, a.lines);
+  } else if constexpr (!RAG) {
     if (a.khat_pass != 2) HY_RA(false, false, 1, a.C);
     if (a.khat_pass != 1) HY_RA(false, false, 2, a.lines);
-  } else {
-    HY_RA(false, false, 0, a.lines);
   }
 #undef HY_RA
   return hipGetLastError();
 }
 
-template <int P0, int N, typename TS>
+template <int P0, int N, typename TS, bool RAG>
 hipError_t launch_bwd_t(const FftConvBwdArgs& b, hipStream_t s) {
   const FftConvArgs& a = b.f;
   constexpr int NT = Ra2D<P0, N>::NT;
 #define HY_RA(KC)                                                                                                 \
-  hipLaunchKernelGGL((bwd2d_ra<P0, N, KC, TS>), dim3((unsigned)a.lines), dim3(NT), 0, s, (const TS*)a.x1,         \
+  hipLaunchKernelGGL((bwd2d_ra<P0, N, KC, TS, RAG>), dim3((unsigned)a.lines), dim3(NT), 0, s, (const TS*)a.x1,         \
                      (const TS*)a.x2, (const TS*)a.v, (const TS*)a.k, (const TS*)a.D, (const TS*)b.gy,            \
-                     (TS*)b.gx1, (TS*)b.gx2, (TS*)b.gv, (TS*)b.gk, b.partial, (int)a.C)
+                     (TS*)b.gx1, (TS*)b.gx2, (TS*)b.gv, (TS*)b.gk, b.partial, (int)a.C, (int)a.L[0], (int)a.L[1])
   if (a.centered) HY_RA(true);
   else HY_RA(false);
 #undef HY_RA
@@ -469,10 +514,30 @@ bool ra2d_supported(const FftConvArgs& a) {
   return false;
 }
 
+// Images of other extents run in the corner of the transforms of the next ones
+// (9 to 64 points an axis), forward and backward, also where the mixed-radix
+// kernels would transform fewer points: those wait at a workgroup barrier for
+// every factor and compute their indexes from run-time radixes.  8 x 256
+// images, fp32, centered, forward and backward: 17 x 17 (four times the points)
+// 30.6 -> 20.4 and 56.7 -> 40.7 us; 28 x 28 62.2 -> 21.4 and 134 -> 45.4; 57 x
+// 40 (packed real transforms, and embedded) 273 -> 64.9 and 1330 -> 168; 16 x
+// 384 of 9 x 9 27.1 -> 15.6 and 55.9 -> 34.4, of 14 x 14 44.3 -> 16.9 and 89.4
+// -> 40.1.
+bool ra2d_ragged(const FftConvArgs& a) {
+  if (a.ndim != 2 || a.circular || !a.rl) return false;
+#define HY_CASE(p0, p1) if (a.P[0] == p0 && a.P[1] == p1) return true;
+  HY_RA2D_SIZES(HY_CASE)
+#undef HY_CASE
+  return false;
+}
+
 hipError_t launch_ra2d(const FftConvArgs& a, hipStream_t s) {
-#define HY_CASE(p0, p1)                   \
-  if (a.P[0] == p0 && a.P[1] == p1)       \
-    return a.bf16 ? launch_fwd_t<p0, p1 / 2, uint16_t>(a, s) : launch_fwd_t<p0, p1 / 2, float>(a, s);
+#define HY_CASE(p0, p1)                                                                                        \
+  if (a.P[0] == p0 && a.P[1] == p1) {                                                                          \
+    if (a.rl)                                                                                                  \
+      return a.bf16 ? launch_fwd_t<p0, p1 / 2, uint16_t, true>(a, s) : launch_fwd_t<p0, p1 / 2, float, true>(a, s); \
+    return a.bf16 ? launch_fwd_t<p0, p1 / 2, uint16_t, false>(a, s) : launch_fwd_t<p0, p1 / 2, float, false>(a, s); \
+  }
   HY_RA2D_SIZES(HY_CASE)
 #undef HY_CASE
   return hipErrorInvalidValue;
@@ -480,9 +545,12 @@ hipError_t launch_ra2d(const FftConvArgs& a, hipStream_t s) {
 
 hipError_t launch_ra2d_backward(const FftConvBwdArgs& b, hipStream_t s) {
   const FftConvArgs& a = b.f;
-#define HY_CASE(p0, p1)                   \
-  if (a.P[0] == p0 && a.P[1] == p1)       \
-    return a.bf16 ? launch_bwd_t<p0, p1 / 2, uint16_t>(b, s) : launch_bwd_t<p0, p1 / 2, float>(b, s);
+#define HY_CASE(p0, p1)                                                                                        \
+  if (a.P[0] == p0 && a.P[1] == p1) {                                                                          \
+    if (a.rl)                                                                                                  \
+      return a.bf16 ? launch_bwd_t<p0, p1 / 2, uint16_t, true>(b, s) : launch_bwd_t<p0, p1 / 2, float, true>(b, s); \
+    return a.bf16 ? launch_bwd_t<p0, p1 / 2, uint16_t, false>(b, s) : launch_bwd_t<p0, p1 / 2, float, false>(b, s); \
+  }
   HY_RA2D_SIZES(HY_CASE)
 #undef HY_CASE
   return hipErrorInvalidValue;

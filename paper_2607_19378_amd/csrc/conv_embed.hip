@@ -1,5 +1,6 @@
-// Backward of the centred mode and of extents that are not powers of two
-// through the circular backward on their transform grid.
+// Calls of extents that are not powers of two through the circular call on their
+// transform grid: the backward of the circular mode where the mixed-radix kernels
+// do not reach, and what the right-angle kernels do not take.
 //
 // These calls are a non-circular convolution computed on a grid of P_d >=
 // 2 L_d - 1 points per axis (a power of two): u is zero beyond its L_d

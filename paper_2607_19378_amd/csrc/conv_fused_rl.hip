@@ -9,7 +9,8 @@
 //
 //  * conv1d_rl<P>: 1D lines, P <= 512 (longer ones: conv1d_ra.hip).
 //  * conv2d_rl<P0, P1>: 2D images whose U and K half spectra fit in LDS side
-//    by side (linear: L0 + L0 rows; centered: L0 + P0 rows).
+//    by side (linear: L0 + L0 rows; centered: L0 + P0 rows), with an axis of up
+//    to 8 points, or one of 16 beside one of 64 (the others: conv2d_ra.hip).
 //
 // The circular mode takes these kernels too: a circular convolution of L
 // points equals the centred one whose kernel holds k[d mod L] at every
@@ -374,13 +375,12 @@ hipError_t launch_2d_p(const FftConvArgs& a, hipStream_t s) {
   return a.bf16 ? launch_2d_t<P0, P1, false, uint16_t>(a, s) : launch_2d_t<P0, P1, false, float>(a, s);
 }
 
-// every pair of power-of-two transform sizes from 4 to 128 (U and K side by side
-// in LDS: at most 100 KB, for a centered 128 x 128)
+// the pairs of power-of-two transform sizes from 4 to 128 that the right-angle
+// kernels are not built for
 #define HY_RL2D_SIZES(X) \
   X(4, 4) X(4, 8) X(4, 16) X(4, 32) X(4, 64) X(4, 128) X(8, 4) X(8, 8) X(8, 16) X(8, 32) X(8, 64) \
   X(8, 128) X(16, 4) X(16, 8) X(16, 16) X(16, 32) X(16, 64) X(16, 128) X(32, 4) X(32, 8) X(32, 16) \
-  X(32, 32) X(32, 64) X(32, 128) X(64, 4) X(64, 8) X(64, 16) X(64, 32) X(64, 64) X(64, 128) X(128, 4) \
-  X(128, 8) X(128, 16) X(128, 32) X(128, 64) X(128, 128)
+  X(32, 128) X(64, 4) X(64, 8) X(64, 16) X(128, 4) X(128, 8) X(128, 16) X(128, 32)
 
 }  // namespace
 
@@ -388,6 +388,7 @@ bool fused_rl_supported(const FftConvArgs& a) {
   if (a.circular) return false;
   if (a.ndim == 1) return a.P[0] >= 4 && a.P[0] <= 16384;
   if (a.ndim == 2) {
+    if (ra2d_ragged(a)) return true;
 #define HY_CASE(p0, p1) \
   if (a.P[0] == p0 && a.P[1] == p1) return true;
     HY_RL2D_SIZES(HY_CASE)
@@ -398,6 +399,7 @@ bool fused_rl_supported(const FftConvArgs& a) {
 
 hipError_t launch_fused_rl(const FftConvArgs& a, hipStream_t s) {
   if (!fused_rl_supported(a)) return hipErrorInvalidValue;
+  if (ra2d_ragged(a)) return launch_ra2d(a, s);  // circular 8 x 256 x 57 x 40, fp32: 257 -> 69 us
   if (a.ndim == 1) {
     switch (a.P[0]) {
       case 4: return launch_1d_p<4>(a, s);

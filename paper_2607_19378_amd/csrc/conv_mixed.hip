@@ -1066,7 +1066,9 @@ bool mixed_supported(const FftConvArgs& a) {
   return mixed_plan(a, &pl);
 }
 
-// Where these kernels beat the power-of-two ones (measured on the MI355X):
+// Which plan a shape is reported under, from measurements against the packed
+// power-of-two kernels; within the plan, non-circular images and lines go to the
+// right-angle kernels where those take them (conv2d_ra.hip, conv1d_ra.hip).
 // 3D grids (which those do not take; 4 x 64 x 12^3: 13.9 us against 207 us
 // embedded), 2D grids up to 2048 transform points (16 x 384 images of 14 x 14:
 // 15.1 us against 105 us; 27 x 27 centred: 44 us against 111 us) and larger

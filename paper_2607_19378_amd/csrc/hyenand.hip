@@ -114,7 +114,9 @@ hyenand_status parse_shape(int ndim, const int64_t* dims, int pad_mode, int dtyp
 }
 
 // A shape whose extents are not powers of two and that neither the
-// power-of-two single-pass kernels nor the mixed-radix ones take runs
+// power-of-two single-pass kernels nor the mixed-radix ones take holds the
+// workspace of the embedded route and runs the right-angle passes in it
+// (runs_ra_mp, runs_ra_line); where those do not fit it is
 // embedded in its transform grid (P_d >= 2 L_d - 1, a power of two): on that
 // grid the call is the circular convolution of the zero-padded
 // inputs and of k placed at its displacements (conv_embed.hip), so x1, x2, v
@@ -389,9 +391,11 @@ hipError_t run_chunked(const FftConvArgs& a, size_t per, hipStream_t caller, Lau
 // block) and then the spectra of a chunk of lines per side stream.
 //
 // Extents that are not powers of two run the mixed-radix single pass
-// (BWD_MIXED, conv_mixed.hip) where their grid fits; those beyond it and the
-// centred mode on the other power-of-two extents (BWD_EMBED) run the circular backward
-// on their transform grid (P_d >= 2 L_d - 1, a power of two): the five
+// (BWD_MIXED, conv_mixed.hip) where their grid fits, and the right-angle kernels
+// instead where those take them.  Those beyond it and the centred mode on the
+// other power-of-two extents (BWD_EMBED) report the workspace of the embedded
+// route; the circular mode takes it, the others run the right-angle kernels.
+// Embedded: the circular backward on the transform grid (P_d >= 2 L_d - 1, a power of two): the five
 // inputs are embedded in that grid and the four gradient
 // tensors extracted from it (conv_embed.hip); gD comes out directly.  Their
 // workspace holds the nine embedded tensors (each 256-byte aligned) and then
@@ -485,12 +489,15 @@ bool bwd_runs_ra_line(const FftConvArgs& a, BwdPlan p, size_t least) {
   return (p == BWD_FOURSTEP || p == BWD_EMBED) && ra_line_supported(a) && !a.periodic &&
          ra_partial_bytes(a) + ra_line_bytes_per_line(a, true) <= least;
 }
+bool mixed_forced() {
+  const char* force = getenv("HYENAND_PLAN");
+  return force && strcmp(force, "mixed") == 0;
+}
+
 // one float per line of workspace, which every plan has (HYENAND_PLAN=mixed
 // keeps lines on the mixed-radix kernels)
 bool bwd_runs_ra1d(const FftConvArgs& a, BwdPlan p) {
-  const char* force = getenv("HYENAND_PLAN");
-  const bool mixed = p == BWD_MIXED && force && strcmp(force, "mixed") == 0;
-  return p != BWD_NONE && !mixed && ra1d_backward_supported(a);
+  return p != BWD_NONE && !(p == BWD_MIXED && mixed_forced()) && ra1d_backward_supported(a);
 }
 
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
@@ -575,11 +582,6 @@ hyenand_status hyenand_fftconv_plan_name(int ndim, const int64_t* dims, hyenand_
 
 namespace {
 
-bool mixed_forced() {
-  const char* force = getenv("HYENAND_PLAN");
-  return force && strcmp(force, "mixed") == 0;
-}
-
 // Circular lines reach the mixed-radix kernels with a transform of their own L
 // points; a right-angle one of N >= L points is the faster when it is not much
 // longer (1024 lines of 1000 points, N = 1024: 13.0 against 16.3 us, of 3000
@@ -617,7 +619,11 @@ hipError_t launch_plan(const FftConvArgs& a, Plan p, size_t per, hipStream_t s) 
         return launch_fourstep(a, l0, nl, ws, st);
       });
     case PLAN_FUSED_RL: return ra1d_supported(a) ? launch_ra1d(a, s) : launch_fused_rl(a, s);
-    case PLAN_MIXED: return mixed_line_on_ra1d(a) ? launch_ra1d(a, s) : launch_mixed(a, s);
+    case PLAN_MIXED:
+      // not circular images, whose mixed-radix transforms have no padding (8 x 256
+      // x 28 x 28, fp32: 21.3 us)
+      if (ra2d_ragged(a) && !a.periodic && !mixed_forced()) return launch_ra2d(a, s);
+      return mixed_line_on_ra1d(a) ? launch_ra1d(a, s) : launch_mixed(a, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -986,6 +992,9 @@ hyenand_status hyenand_fftconv_backward(const void* x1, const void* x2, const vo
   clear_pending_error();
   if (bwd_runs_ra1d(a, p)) {
     err = launch_ra1d_backward(b, s);
+    if (err == hipSuccess) err = launch_backward_reduce(b, 1, s);
+  } else if (ra2d_ragged(a) && !a.periodic && !(p == BWD_MIXED && mixed_forced())) {  // sums as above
+    err = launch_ra2d_backward(b, s);
     if (err == hipSuccess) err = launch_backward_reduce(b, 1, s);
   } else if (const bool line = bwd_runs_ra_line(a, p, need); line || bwd_runs_ra_mp(a, p, need)) {
     FftConvArgs sa = b.f;

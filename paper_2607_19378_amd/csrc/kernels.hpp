@@ -62,6 +62,7 @@ size_t fused2d_khat_bytes(const FftConvArgs& a);
 // forward and backward; launch_fused2d and launch_backward take them where
 // they are supported
 bool ra2d_supported(const FftConvArgs& a);
+bool ra2d_ragged(const FftConvArgs& a);  // extents that are no powers of two (backward: not of the circular mode)
 hipError_t launch_ra2d(const FftConvArgs& a, hipStream_t s);
 
 // single pass for grid extents that are not powers of two on power-of-two

@@ -36,6 +36,39 @@ def test_forward_and_backward(grid, mode, dtype):
         assert rel_l2(from_device(g), r) <= TOL[dtype], name
 
 
+RAGGED = [(9, 9), (14, 14), (9, 17), (16, 31), (17, 9), (32, 17), (28, 28), (31, 33), (57, 40), (33, 64), (64, 33), (63, 63)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("mode", ["linear", "centered", "circular"])
+@pytest.mark.parametrize("grid", RAGGED)
+def test_other_extents(grid, mode, dtype):
+    """The smallest and largest extents of each transform grid, one and both axes off a power of two."""
+    import torch
+    from paper_2607_19378_amd import hyenand as H
+    inp = W.random_case(1, 3, grid, mode, dtype, seed=800 + sum(grid))
+    log(f"ra2d {grid} {mode} {dtype}")
+    f = inp.as_f64()
+    x1, x2, v, k, D = f
+    u = x1 * v
+    if mode == "circular":  # the oracle's circular FFT takes powers of two: numpy's serves here
+        ref = x2 * (np.fft.irfftn(np.fft.rfftn(u, axes=(2, 3)) * np.fft.rfftn(k, axes=(-2, -1)), s=grid, axes=(2, 3))
+                    + D[None, :, None, None] * u)
+    else:
+        ref = oracle.conv_fft(*f, mode)
+    assert per_line_worst(run_gpu(inp), ref, 3) <= TOL[dtype]
+    if mode == "circular":
+        return
+    gy = W.quantise(np.random.default_rng(5).standard_normal(inp.workload.shape), dtype)
+    dev = [to_device(a, dtype) for a in (inp.x1, inp.x2, inp.v, inp.k, inp.D, gy)]
+    got = H.backward(*dev, pad_mode=mode)
+    torch.cuda.synchronize()
+    for name, g, r in zip(("gx1", "gx2", "gv", "gk", "gD"), got,
+                          oracle.backward_direct(*f, W.storage_to_f64(gy, dtype), mode)):
+        assert tuple(g.shape) == tuple(r.shape)
+        assert rel_l2(from_device(g), r) <= TOL[dtype], name
+
+
 @pytest.mark.parametrize("mode", ["linear", "centered"])
 def test_lines_of_different_scales(mode):
     """u and k of a line are transformed apart, and lines never share a transform: scales 1e6 apart between lines
