@@ -96,13 +96,11 @@ typedef enum { HYENAND_DTYPE_F32 = 0, HYENAND_DTYPE_BF16 = 1, HYENAND_DTYPE_MAX_
  *                   periodically over the displacements -(L_d - 1) ..
  *                   L_d - 1, which makes it a non-circular one): in one pass
  *                   per line for 1D up to L = 8192 and 2D up to 128-point
- *                   transforms per axis; beyond that embedded in the
- *                   transform grid, where the call is the circular
- *                   convolution of the zero-padded inputs and of k placed at
- *                   its displacements: x1, x2, v and k are copied into the
- *                   workspace on that grid, the circular plan runs there and
- *                   y is copied back (the workspace queries include the five
- *                   embedded tensors; at most 2^31 elements per embedded
+ *                   transforms per axis; beyond that in several passes over
+ *                   the points of the grid.  The workspace queries keep the
+ *                   size of the embedded route there (five tensors on the
+ *                   power-of-two transform grid, and the circular plan's own
+ *                   workspace; at most 2^31 elements per embedded
  *                   tensor).  The operator takes the single-pass shapes only.
  * pad_mode        : hyenand_pad_mode.
  * dtype           : hyenand_dtype.
@@ -294,17 +292,15 @@ hyenand_status hyenand_fftconv_plan_name(int ndim, const int64_t* dims, hyenand_
  *
  * Centred mode (k and gk [B, C, 2 L1 - 1, ...], gu[j] = sum_n k[n - j +
  * (L - 1)] h[n] + D h[j], gk[i] = sum_n h[n] u[n - i + (L - 1)]) and
- * extents that are not powers of two: both are circular convolutions on
- * their transform grid once u is zero-padded and k placed at its
- * displacements.  Centred images of 16 to 64 power-of-two points per axis (at
- * most 2:1) run in one pass, as the linear ones do.  Extents that are not
- * powers of two run in one pass on the
- * forward's mixed-radix grid where it fits (about 3000 transform points per
- * image; the workspace holds the gD sums only).  The other shapes, and the
- * centred mode on other power-of-two extents, are embedded: the library copies x1,
- * x2, v, gy and k into the transform grid (a power of two >= 2 L_d - 1 per
- * axis), runs the circular backward there and extracts the gradients.  The
- * workspace then starts with the nine embedded tensors (each B * C * prod P
+ * extents that are not powers of two.  Lines of up to 8192 points and images of
+ * 9 to 64 points per axis (16 beside 64 excepted) run in one pass, larger grids
+ * in several over the points of the grid; other extents also on the forward's
+ * mixed-radix grid where it fits (about 3000 transform points per image; the
+ * workspace holds the gD sums only).  The circular mode on other extents beyond
+ * that grid is embedded: the library copies x1, x2, v, gy and k into the
+ * transform grid (a power of two >= 2 L_d - 1 per axis), runs the circular
+ * backward there and extracts the gradients.  The workspace of these shapes, of
+ * either kind, holds nine embedded tensors (each B * C * prod P
  * elements of dtype, 256-byte aligned); the workspace queries include them.
  * Extents that are not powers of two may also be 3D here.
  */
