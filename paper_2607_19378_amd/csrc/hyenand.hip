@@ -232,6 +232,12 @@ struct ChunkPlan {
 // than the cache saves: 4 x 64 images of 200 x 150 329 -> 291 us, 2 x 32
 // volumes of 48^3 497 -> 474 us.  Power-of-two grids keep the rule above (one
 // line of 128^3 points is 67 MB: 3378 us, wide 3994 us).
+// Calls of up to 32 MiB of spectra run on one stream too: a second one, with
+// the events that tie it to the caller's, costs about 70 us whatever the call
+// (48 images of 8 x 32 87 -> 24 us, 128 of 128 x 32 69 -> 20, of 128 x 128, at
+// the limit, 71 -> 42; 32 lines of 16384 points 68 -> 23).
+bool ra_one_stream(const FftConvArgs& a, size_t per) { return a.rl || (size_t)a.lines * per <= (size_t)32 << 20; }
+
 ChunkPlan plan_chunks(int64_t lines, size_t per, size_t ws_bytes, bool wide) {
   ChunkPlan c;
   const int64_t fit = (int64_t)(ws_bytes / per);  // >= 1, checked by the caller
@@ -593,7 +599,7 @@ bool mixed_line_on_ra1d(const FftConvArgs& a) {
 hipError_t run_ra_line(const FftConvArgs& a, hipStream_t s) {
   return run_chunked(a, ra_line_bytes_per_line(a, false), s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
     return launch_ra_line(a, l0, nl, ws, st);
-  }, a.rl);
+  }, ra_one_stream(a, ra_line_bytes_per_line(a, false)));
 }
 
 // Every step of the path for a validated call: the plan's kernels, chunked
@@ -607,7 +613,7 @@ hipError_t launch_plan(const FftConvArgs& a, Plan p, size_t per, hipStream_t s) 
       if (runs_ra_mp(a, p))
         return run_chunked(a, ra_mp_bytes_per_line(a, false), s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
           return launch_ra_mp(a, l0, nl, ws, st);
-        }, a.rl);
+        }, ra_one_stream(a, ra_mp_bytes_per_line(a, false)));
       if (runs_ra_line(a, p)) return run_ra_line(a, s);
       if (p == PLAN_EMBED) return hipErrorInvalidValue;
       return run_chunked(a, per, s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
@@ -1002,12 +1008,13 @@ hyenand_status hyenand_fftconv_backward(const void* x1, const void* x2, const vo
     sa.ws = (char*)workspace + rb;
     sa.ws_bytes = workspace_bytes - rb;
     err = launch_ra_mp_hu(b, b.partial, s);
+    const size_t bytes = line ? ra_line_bytes_per_line(a, true) : ra_mp_bytes_per_line(a, true);
     if (err == hipSuccess)
-      err = run_chunked(sa, line ? ra_line_bytes_per_line(a, true) : ra_mp_bytes_per_line(a, true), s,
+      err = run_chunked(sa, bytes, s,
                         [&b, line](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
                           return line ? launch_ra_line_backward(b, l0, nl, ws, st)
                                       : launch_ra_mp_backward(b, l0, nl, ws, st);
-                        }, a.rl);
+                        }, ra_one_stream(a, bytes));
     if (err == hipSuccess) err = launch_backward_reduce(b, ra_mp_partials_per_line(a), s);
   } else if (p == BWD_EMBED) {
     char* w = (char*)workspace;
