@@ -235,14 +235,13 @@ struct ChunkPlan {
 // Calls of up to 32 MiB of spectra run on one stream too: a second one, with
 // the events that tie it to the caller's, costs about 70 us whatever the call
 // (48 images of 8 x 32 87 -> 24 us, 128 of 128 x 32 69 -> 20, of 128 x 128, at
-// the limit, 71 -> 42; 32 lines of 16384 points 68 -> 23).
-bool ra_one_stream(const FftConvArgs& a, size_t per) { return a.rl || (size_t)a.lines * per <= (size_t)32 << 20; }
-
+// the limit, 71 -> 42; 32 lines of 16384 points 68 -> 23; circular, 32 images of
+// 256 x 64 71 -> 25).
 ChunkPlan plan_chunks(int64_t lines, size_t per, size_t ws_bytes, bool wide) {
   ChunkPlan c;
   const int64_t fit = (int64_t)(ws_bytes / per);  // >= 1, checked by the caller
   const bool set = getenv("HYENAND_WS_TARGET_MB") || getenv("HYENAND_CHUNK_STREAMS");
-  wide = wide && !set;
+  wide = (wide || (size_t)lines * per <= (size_t)32 << 20) && !set;
   const int want = wide ? 1 : chunk_streams();
   c.streams = want;
   if (c.streams > fit) c.streams = (int)fit;
@@ -599,7 +598,7 @@ bool mixed_line_on_ra1d(const FftConvArgs& a) {
 hipError_t run_ra_line(const FftConvArgs& a, hipStream_t s) {
   return run_chunked(a, ra_line_bytes_per_line(a, false), s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
     return launch_ra_line(a, l0, nl, ws, st);
-  }, ra_one_stream(a, ra_line_bytes_per_line(a, false)));
+  }, a.rl);
 }
 
 // Every step of the path for a validated call: the plan's kernels, chunked
@@ -613,7 +612,7 @@ hipError_t launch_plan(const FftConvArgs& a, Plan p, size_t per, hipStream_t s) 
       if (runs_ra_mp(a, p))
         return run_chunked(a, ra_mp_bytes_per_line(a, false), s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
           return launch_ra_mp(a, l0, nl, ws, st);
-        }, ra_one_stream(a, ra_mp_bytes_per_line(a, false)));
+        }, a.rl);
       if (runs_ra_line(a, p)) return run_ra_line(a, s);
       if (p == PLAN_EMBED) return hipErrorInvalidValue;
       return run_chunked(a, per, s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
@@ -1014,7 +1013,7 @@ hyenand_status hyenand_fftconv_backward(const void* x1, const void* x2, const vo
                         [&b, line](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
                           return line ? launch_ra_line_backward(b, l0, nl, ws, st)
                                       : launch_ra_mp_backward(b, l0, nl, ws, st);
-                        }, ra_one_stream(a, bytes));
+                        }, a.rl);
     if (err == hipSuccess) err = launch_backward_reduce(b, ra_mp_partials_per_line(a), s);
   } else if (p == BWD_EMBED) {
     char* w = (char*)workspace;
