@@ -57,11 +57,23 @@ constexpr int ra1_e(int N) { return N > 1024 ? 16 : 8; }
 constexpr int64_t kRaShortCall = 512;
 constexpr int ra1_nt(int N) { return N / ra1_e(N); }  // of the backward
 
+// Whether a kernel can scale its lines (norm): the mixed plan has circular lines
+// of up to 4096 points forward (KC), others of up to about 1500 backward.  In the
+// other kernels the code would cost 1 to 2 % (backward of 8192 points, bf16: 125.4
+// -> 127.6 us).
+template <int N, bool KC>
+constexpr bool kRa1Norm = KC && N <= 4096;
+template <int N>
+constexpr bool kRa1BwdNorm = N <= 2048;
+
+// norm: u, k and h scaled by powers of two (ra_device.hpp); the scratch of the
+// magnitudes is free again after the next barrier.
 template <int N, bool KC, typename TS>
 __global__ void __launch_bounds__(ra1_nt(N)) __attribute__((amdgpu_waves_per_eu(2)))
     bwd1d_ra(const TS* __restrict__ x1, const TS* __restrict__ x2, const TS* __restrict__ v,
              const TS* __restrict__ k, const TS* __restrict__ Dp, const TS* __restrict__ gy, TS* __restrict__ gx1,
-             TS* __restrict__ gx2, TS* __restrict__ gv, TS* __restrict__ gk, float* __restrict__ partial, int C, int L) {
+             TS* __restrict__ gx2, TS* __restrict__ gv, TS* __restrict__ gk, float* __restrict__ partial, int C, int L,
+             int norm) {
   constexpr int E = ra1_e(N), T = N / E, NT = T;
   static_assert(NT >= 64, "a wavefront or more");
   __shared__ float2 S[pad16_size(N)];
@@ -96,12 +108,38 @@ __global__ void __launch_bounds__(ra1_nt(N)) __attribute__((amdgpu_waves_per_eu(
   }
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    const float q = wh[e].x;
-    const float u = xa[e] * xv[e], h = xg[e] * q;
-    hu = fmaf(h, u, hu);
-    wu[e] = c_scale(om(e), u);
-    wh[e] = c_scale(om(e), h);
-    wk[e] = KC ? c_scale(c_mul(wk[e], om(e)), scale) : c_scale(om(e), wk[e].x * scale);
+    wh[e].x *= xg[e];
+    wu[e].x = xa[e] * xv[e];
+    hu = fmaf(wh[e].x, wu[e].x, hu);
+  }
+  const float Dv = ld1(Dp + c);
+  int eu = 0, eh = 0, ek = 0;
+  if (kRa1BwdNorm<N> && norm) {
+    RaMags<NT / 64, 3> mags;
+    mags.s = reinterpret_cast<uint32_t*>(S);
+    uint32_t m[3] = {0, 0, 0};
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      m[0] = ra_umax(m[0], ra_mag(wu[e].x));
+      m[1] = ra_umax(m[1], ra_mag(wh[e].x));
+      m[2] = ra_umax(m[2], ra_umax(ra_mag(wk[e].x), ra_mag(wk[e].y)));
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) mags.put(i, m[i], t);
+    mags.sync();
+    eu = mags.get(0), eh = mags.get(1), ek = imax(mags.get(2), ra_exponent(ra_mag(Dv)));
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      wu[e].x *= ra_pow2(-eu);
+      wh[e].x *= ra_pow2(-eh);
+    }
+  }
+  const float ks = scale * ra_pow2(-ek);
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    wu[e] = c_scale(om(e), wu[e].x);
+    wh[e] = c_scale(om(e), wh[e].x);
+    wk[e] = KC ? c_mul(c_scale(wk[e], ks), om(e)) : c_scale(om(e), wk[e].x * ks);
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) hu += __shfl_xor(hu, o, 64);
@@ -118,7 +156,7 @@ __global__ void __launch_bounds__(ra1_nt(N)) __attribute__((amdgpu_waves_per_eu(
   BlockFFT<N, E, false>::run(wu, t, sc, true, twl);
   BlockFFT<N, E, false>::run(wh, t, sc, true, twl);
   BlockFFT<N, E, false>::run(wk, t, sc, true, twl);
-  const float Ds = scale * ld1(Dp + c);
+  const float Ds = ks * Dv;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const float2 kd = make_float2(wk[e].x + Ds, wk[e].y);
@@ -128,6 +166,7 @@ __global__ void __launch_bounds__(ra1_nt(N)) __attribute__((amdgpu_waves_per_eu(
   }
   // point n of the ring element: z conj(om)
   BlockFFT<N, E, true>::run(wu, t, sc, true, twl);
+  if (kRa1BwdNorm<N> && norm) ra_ldexp(wu, eu + ek);
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int n = t + T * e;
@@ -136,6 +175,7 @@ __global__ void __launch_bounds__(ra1_nt(N)) __attribute__((amdgpu_waves_per_eu(
   }
   asm volatile("" : "+v"(wt.x), "+v"(wt.y));
   BlockFFT<N, E, true>::run(wh, t, sc, true, twl);
+  if (kRa1BwdNorm<N> && norm) ra_ldexp(wh, eh + ek);
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int n = t + T * e;
@@ -148,6 +188,7 @@ __global__ void __launch_bounds__(ra1_nt(N)) __attribute__((amdgpu_waves_per_eu(
   }
   asm volatile("" : "+v"(wt.x), "+v"(wt.y));
   BlockFFT<N, E, true>::run(wk, t, sc, true, twl);
+  if (kRa1BwdNorm<N> && norm) ra_ldexp(wk, eu + eh);
   TS* const gkl = gk + line * KL;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
@@ -164,7 +205,7 @@ template <int N, int E, bool KC, typename TS, bool ACT>
 __global__ void __launch_bounds__(N / E) __attribute__((amdgpu_waves_per_eu(N / E == 512 ? 4 : 2)))
     conv1d_ra(const TS* __restrict__ x1, const TS* __restrict__ x2, const TS* __restrict__ v,
               const TS* __restrict__ k, const TS* __restrict__ Dp, TS* __restrict__ y, int C, int kC, int L,
-              int periodic, ActIn ain) {
+              int periodic, int norm, ActIn ain) {
   constexpr int T = N / E, NT = T;
   __shared__ float2 S[pad16_size(N)];
   __shared__ float2 twl[PassTw<N, E>::kCount];
@@ -192,24 +233,48 @@ __global__ void __launch_bounds__(N / E) __attribute__((amdgpu_waves_per_eu(N / 
   }
   PassTw<N, E>::fill(twl, t, NT);
   const Gates<ACT> G = line_gates<ACT, TS>(ain, line, C);
+  const float Dv = ld1(Dp + c);
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    wk[e] = KC ? c_scale(c_mul(wk[e], om(e)), scale) : c_scale(om(e), wk[e].x * scale);
     float u = wu[e].x * wu[e].y;
     if constexpr (ACT) u = t + T * e < L ? G.u1(wu[e].x, wu[e].y, t + T * e) : 0.f;
-    wu[e] = c_scale(om(e), u);
+    wu[e].x = u;
+  }
+  int eu = 0, ek = 0;
+  if (kRa1Norm<N, KC> && norm) {
+    RaMags<NT / 64, 2> mags;
+    mags.s = reinterpret_cast<uint32_t*>(S);
+    uint32_t m[2] = {0, 0};
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      m[0] = ra_umax(m[0], ra_mag(wu[e].x));
+      m[1] = ra_umax(m[1], KC ? ra_umax(ra_mag(wk[e].x), ra_mag(wk[e].y)) : ra_mag(wk[e].x));
+    }
+    mags.put(0, m[0], t);
+    mags.put(1, m[1], t);
+    mags.sync();
+    eu = mags.get(0), ek = imax(mags.get(1), ra_exponent(ra_mag(Dv)));
+#pragma unroll
+    for (int e = 0; e < E; ++e) wu[e].x *= ra_pow2(-eu);
+  }
+  const float ks = scale * ra_pow2(-ek);
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    wk[e] = KC ? c_mul(c_scale(wk[e], ks), om(e)) : c_scale(om(e), wk[e].x * ks);
+    wu[e] = c_scale(om(e), wu[e].x);
   }
   asm volatile("" : "+v"(wt.x), "+v"(wt.y));
   __syncthreads();
   BlockFFT<N, E, false>::run(wk, t, sc, true, twl);
   BlockFFT<N, E, false>::run(wu, t, sc, true, twl);
-  const float Ds = scale * ld1(Dp + c);
+  const float Ds = ks * Dv;
 #pragma unroll
   for (int e = 0; e < E; ++e) wu[e] = gated_product(wu[e], wk[e], Ds);
   float g[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) g[e] = ra_ld_sel(x2 + base, t + T * e, t + T * e < L);
   BlockFFT<N, E, true>::run(wu, t, sc, true, twl);
+  if (kRa1Norm<N, KC> && norm) ra_ldexp(wu, eu + ek);
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int n = t + T * e;
@@ -219,14 +284,17 @@ __global__ void __launch_bounds__(N / E) __attribute__((amdgpu_waves_per_eu(N / 
 }
 
 template <int N, int E, typename TS>
-hipError_t fwd1d_e(const FftConvArgs& a, hipStream_t s) {
+hipError_t fwd1d_e(const FftConvArgs& a, bool norm, hipStream_t s) {
+  if (norm && !kRa1Norm<N, true>) return hipErrorInvalidValue;  // no line of the mixed plan
 #define HY_F(KC, ACT)                                                                                          \
   hipLaunchKernelGGL((conv1d_ra<N, E, KC, TS, ACT>), dim3((unsigned)a.lines), dim3(N / E), 0, s, (const TS*)a.x1, \
                      (const TS*)a.x2, (const TS*)a.v, (const TS*)a.k, (const TS*)a.D, (TS*)a.y, (int)a.C, a.kC, \
-                     (int)a.L[0], (int)a.periodic, a.act_in)
+                     (int)a.L[0], (int)a.periodic, (int)norm, a.act_in)
   if (a.centered || a.periodic) {
     if (a.act) HY_F(true, true);
     else HY_F(true, false);
+  } else if (norm) {
+    return hipErrorInvalidValue;
   } else if (a.act) {
     HY_F(false, true);
   } else {
@@ -236,20 +304,21 @@ hipError_t fwd1d_e(const FftConvArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 template <int N, typename TS>
-hipError_t fwd1d_t(const FftConvArgs& a, hipStream_t s) {
+hipError_t fwd1d_t(const FftConvArgs& a, bool norm, hipStream_t s) {
   if constexpr (N == 2048 || N == 4096) {
-    if (a.lines <= kRaShortCall) return fwd1d_e<N, 8, TS>(a, s);
+    if (a.lines <= kRaShortCall) return fwd1d_e<N, 8, TS>(a, norm, s);
   }
-  return fwd1d_e<N, ra1_e(N), TS>(a, s);
+  return fwd1d_e<N, ra1_e(N), TS>(a, norm, s);
 }
 
 template <int N, typename TS>
-hipError_t bwd1d_t(const FftConvBwdArgs& b, hipStream_t s) {
+hipError_t bwd1d_t(const FftConvBwdArgs& b, bool norm, hipStream_t s) {
   const FftConvArgs& a = b.f;
+  if (norm && !kRa1BwdNorm<N>) return hipErrorInvalidValue;  // no line of the mixed plan
 #define HY_B(KC)                                                                                                  \
   hipLaunchKernelGGL((bwd1d_ra<N, KC, TS>), dim3((unsigned)a.lines), dim3(ra1_nt(N)), 0, s, (const TS*)a.x1,      \
                      (const TS*)a.x2, (const TS*)a.v, (const TS*)a.k, (const TS*)a.D, (const TS*)b.gy,            \
-                     (TS*)b.gx1, (TS*)b.gx2, (TS*)b.gv, (TS*)b.gk, b.partial, (int)a.C, (int)a.L[0])
+                     (TS*)b.gx1, (TS*)b.gx2, (TS*)b.gv, (TS*)b.gk, b.partial, (int)a.C, (int)a.L[0], (int)norm)
   if (a.centered) HY_B(true);
   else HY_B(false);
 #undef HY_B
@@ -578,10 +647,10 @@ bool ra1d_supported(const FftConvArgs& a) {
   return a.ndim == 1 && !a.circular && a.L[0] >= 2 && a.P[0] >= 1024 && a.P[0] <= 16384;
 }
 
-hipError_t launch_ra1d(const FftConvArgs& a, hipStream_t s) {
+hipError_t launch_ra1d(const FftConvArgs& a, bool norm, hipStream_t s) {
   switch (a.P[0] / 2) {
 #define HY_CASE(n) \
-  case n: return a.bf16 ? fwd1d_t<n, uint16_t>(a, s) : fwd1d_t<n, float>(a, s);
+  case n: return a.bf16 ? fwd1d_t<n, uint16_t>(a, norm, s) : fwd1d_t<n, float>(a, norm, s);
     HY_CASE(512) HY_CASE(1024) HY_CASE(2048) HY_CASE(4096) HY_CASE(8192)
 #undef HY_CASE
     default: return hipErrorInvalidValue;
@@ -592,10 +661,10 @@ bool ra1d_backward_supported(const FftConvArgs& a) {
   return ra1d_supported(a) && !a.periodic;
 }
 
-hipError_t launch_ra1d_backward(const FftConvBwdArgs& b, hipStream_t s) {
+hipError_t launch_ra1d_backward(const FftConvBwdArgs& b, bool norm, hipStream_t s) {
   switch (b.f.P[0] / 2) {
 #define HY_CASE(n) \
-  case n: return b.f.bf16 ? bwd1d_t<n, uint16_t>(b, s) : bwd1d_t<n, float>(b, s);
+  case n: return b.f.bf16 ? bwd1d_t<n, uint16_t>(b, norm, s) : bwd1d_t<n, float>(b, norm, s);
     HY_CASE(512) HY_CASE(1024) HY_CASE(2048) HY_CASE(4096) HY_CASE(8192)
 #undef HY_CASE
     default: return hipErrorInvalidValue;

@@ -89,13 +89,19 @@ struct RaImage {
   }
 };
 
+// Whether the forward kernel can scale a line (norm): the mixed plan's images of
+// these transforms.  Beyond them (from 33 x 17 points) that plan's 2048 transform
+// points are passed, and the code would cost 57 x 40 images 10 % in registers.
+template <int P0, int N, bool RAG>
+constexpr bool kRa2Norm = RAG && P0 < 128 && N < 64;
+
 // KH as in the circular kernel: 0 transforms each image's own k, 1 writes the
 // spectrum of each channel's k to khat[c][n][col] and stops, 2 reads it.
 template <int P0, int N, bool KC, typename TS, bool ACT, int KH, bool RAG>
 __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves_per_eu(4)))
     conv2d_ra(const TS* __restrict__ x1, const TS* __restrict__ x2, const TS* __restrict__ v,
               const TS* __restrict__ k, const TS* __restrict__ Dp, TS* __restrict__ y, int C, int kC, ActIn ain,
-              float2* __restrict__ khat, int M0, int M1, bool per) {
+              float2* __restrict__ khat, int M0, int M1, bool per, bool norm) {
   static_assert(KH == 0 || (!KC && !ACT && !RAG), "kept spectra: linear, plain gates, powers of two");
   using F = Ra2D<P0, N>;
   using Row = typename F::Row;
@@ -105,6 +111,9 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
   constexpr int E = Col::E, TC = Col::T;
   constexpr float scale = 1.f / ((float)P0 * (float)N);  // of the unnormalised inverses, a power of two
   __shared__ float2 S[P0 * PITCH];
+  constexpr bool NORM = kRa2Norm<P0, N, RAG>;
+  constexpr int W = F::NT / 64;
+  __shared__ uint32_t magw[NORM ? 2 * W : 1];
   int img = blockIdx.x;
   if constexpr (KH == 2) {
     // the B images of a channel in consecutive slots of one XCD (workgroup j
@@ -137,22 +146,50 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
       b[e] = im.ld(v + base, rb + TR * e, in);
     }
   };
-  auto gate_u = [&](const float (&a)[8], const float (&b)[8], float2 (&w)[8]) {
+  auto gate_u = [&](float (&a)[8], const float (&b)[8]) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const bool in = im.in(r, tr + TR * e);
       const float u = G.u1(a[e], b[e], in ? rb + TR * e : 0);
-      w[e] = Row::lead(in ? u : 0.f, e);
+      a[e] = in ? u : 0.f;
     }
   };
+  auto lead_u = [&](const float (&a)[8], float s, float2 (&w)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) w[e] = Row::lead(NORM ? a[e] * s : a[e], e);
+  };
+  // NORM: unscaled until the magnitudes are known
   auto load_k = [&](int g0, float2 (&w)[8]) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) w[e] = im.template kernel_point<KC>(kl, g0, tr + TR * e, scale);
+    for (int e = 0; e < 8; ++e) w[e] = im.template kernel_point<KC>(kl, g0, tr + TR * e, NORM ? 1.f : scale);
   };
-  auto lead_k = [&](float2 (&w)[8]) {
+  auto lead_k = [&](float2 (&w)[8], float s) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) w[e] = KC ? Row::lead(w[e], e) : Row::lead(w[e].x, e);
+    for (int e = 0; e < 8; ++e) {
+      if constexpr (NORM) w[e] = c_scale(w[e], s);
+      w[e] = KC ? Row::lead(w[e], e) : Row::lead(w[e].x, e);
+    }
   };
+  // norm: the exponents of the largest |u| (0) and of the largest of |k| (1) and |D|
+  const float Dv = KH == 1 ? 0.f : ld1(Dp + c);
+  RaMags<W, 2> mags;
+  mags.s = magw;
+  auto u_mag = [&](const float (&a)[8]) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) m = ra_umax(m, ra_mag(a[e]));
+    return m;
+  };
+  auto k_mag = [&](const float2 (&w)[8]) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      m = ra_umax(m, ra_mag(w[e].x));
+      if constexpr (KC) m = ra_umax(m, ra_mag(w[e].y));
+    }
+    return m;
+  };
+  int eu = 0, ek = 0;
   auto row_fwd = [&](int slot_row, float2 (&w)[8]) {
     float2* const row = S + slot_row * PITCH;
     Row::forward(w, tr, row, ftw);
@@ -165,23 +202,40 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
   if constexpr (KC) {
     // U's rows first; each lane keeps the U values of its column while K's
     // P0 rows take the region
-    if (has_u) {
-      float a[8], b[8];
-      float2 w[8];
-      load_u(a, b);
-      gate_u(a, b, w);
-      row_fwd(rr, w);
+    {
+      float a[8] = {}, b[8];
+      if (has_u) {
+        load_u(a, b);
+        gate_u(a, b);
+      }
+      if (NORM && norm) {
+        mags.put(0, u_mag(a), tid);
+        mags.sync();
+        eu = mags.get(0);
+      }
+      if (has_u) {
+        float2 w[8];
+        lead_u(a, ra_pow2(-eu), w);
+        row_fwd(rr, w);
+      }
     }
     float2 wr[NR][8];
 #pragma unroll
     for (int q = 0; q < NR; ++q) load_k(q * RPR + rr, wr[q]);
+    if (NORM && norm) {
+      uint32_t m = 0;
+#pragma unroll
+      for (int q = 0; q < NR; ++q) m = ra_umax(m, k_mag(wr[q]));
+      mags.put(1, m, tid);
+    }
     __syncthreads();
+    if (NORM && norm) ek = imax(mags.get(1), ra_exponent(ra_mag(Dv)));
 #pragma unroll
     for (int e = 0; e < E / 2; ++e) wu[e] = cp[(tc + TC * e) * PITCH];
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
-      lead_k(wr[q]);
+      lead_k(wr[q], scale * ra_pow2(-ek));
       row_fwd(q * RPR + rr, wr[q]);
     }
     __syncthreads();
@@ -195,23 +249,45 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
       float2 wr[8];
       if constexpr (KH != 2) load_k(rr, wr);
       if constexpr (KH != 1) load_u(a, b);
+      static_assert(!NORM, "two rounds of rows");
       if constexpr (KH != 2) {
-        lead_k(wr);
+        lead_k(wr, 1.f);
         row_fwd(L0 + rr, wr);
       }
       if constexpr (KH != 1) {
-        gate_u(a, b, wr);
+        gate_u(a, b);
+        lead_u(a, 1.f, wr);
         row_fwd(rr, wr);
       }
+    } else if constexpr (NORM) {
+      float a[8] = {}, b[8];
+      float2 w[8] = {};
+      if (has_u) {
+        load_u(a, b);
+        gate_u(a, b);
+      } else {
+        load_k(r, w);
+      }
+      if (NORM && norm) {
+        mags.put(0, u_mag(a), tid);
+        mags.put(1, k_mag(w), tid);
+        mags.sync();
+        eu = mags.get(0);
+        ek = imax(mags.get(1), ra_exponent(ra_mag(Dv)));
+      }
+      if (has_u) lead_u(a, ra_pow2(-eu), w);
+      else lead_k(w, scale * ra_pow2(-ek));
+      row_fwd(rr, w);
     } else if (KH == 0 || (KH == 1) == !has_u) {
       float2 w[8];
       if (!has_u) {
         load_k(r, w);
-        lead_k(w);
+        lead_k(w, 1.f);
       } else {
         float a[8], b[8];
         load_u(a, b);
-        gate_u(a, b, w);
+        gate_u(a, b);
+        lead_u(a, 1.f, w);
       }
       row_fwd(rr, w);
     }
@@ -245,7 +321,7 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
 #pragma unroll
   for (int e = E / 2; e < E; ++e) wu[e] = czero();
   Col::template run<false>(wu, tc, cp, ctw);
-  const float Ds = scale * ld1(Dp + c);
+  const float Ds = NORM ? Dv * (scale * ra_pow2(-ek)) : scale * Dv;
 #pragma unroll
   for (int e = 0; e < E; ++e) wu[e] = gated_product(wu[e], wk[e], Ds);
   // the outer gate and the inverse rows' twiddles arrive meanwhile
@@ -269,6 +345,7 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
 #pragma unroll
   for (int e = 0; e < 8; ++e) w[e] = row[tr + Row::off(e)];
   Row::inverse(w, tr, row, itw);
+  if (NORM && norm) ra_ldexp(w, eu + ek);
 #pragma unroll
   for (int e = 0; e < 8; ++e)
     if (im.in(r, tr + TR * e)) st1(y + base + rb + TR * e, G.g1(g[e]) * Row::re(w[e], e));
@@ -282,7 +359,8 @@ template <int P0, int N, bool KC, typename TS, bool RAG>
 __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves_per_eu(2)))
     bwd2d_ra(const TS* __restrict__ x1, const TS* __restrict__ x2, const TS* __restrict__ v,
              const TS* __restrict__ k, const TS* __restrict__ Dp, const TS* __restrict__ gy, TS* __restrict__ gx1,
-             TS* __restrict__ gx2, TS* __restrict__ gv, TS* __restrict__ gk, float* __restrict__ partial, int C, int M0, int M1) {
+             TS* __restrict__ gx2, TS* __restrict__ gv, TS* __restrict__ gk, float* __restrict__ partial, int C, int M0, int M1,
+             bool norm) {
   using F = Ra2D<P0, N>;
   using Row = typename F::Row;
   using Col = typename F::Col;
@@ -292,6 +370,11 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
   constexpr float scale = 1.f / ((float)P0 * (float)N);
   __shared__ float2 S[P0 * PITCH];
   __shared__ float red[imax(1, NT / 64)];
+  constexpr int W = NT / 64;
+  __shared__ uint32_t magw[RAG ? 3 * W : 1];
+  RaMags<W, 3> mags;  // norm: |u|, |h|, |k|
+  mags.s = magw;
+  int eu = 0, eh = 0, ek = 0;
   const int img = blockIdx.x;
   const int c = img % C;
   const size_t base = (size_t)img * im.points();
@@ -326,12 +409,29 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
       xe[e] = im.ld(x2 + base, rb + TR * e, in);
     }
     float hu = 0.f;
+    if (RAG && norm) {
+      uint32_t mu = 0, mh = 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        mu = ra_umax(mu, ra_mag(xa[e] * xv[e]));
+        mh = ra_umax(mh, ra_mag(xg[e] * xe[e]));
+      }
+      mags.put(0, mu, tid);
+      mags.put(1, mh, tid);
+      mags.sync();
+      eu = mags.get(0);
+      eh = mags.get(1);
+    }
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
       const bool ish = q * RPR + rr >= L0;
+      const float s = ra_pow2(ish ? -eh : -eu);
       float2 w[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) w[e] = Row::lead(ish ? xg[e] * xe[e] : xa[e] * xv[e], e);
+      for (int e = 0; e < 8; ++e) {
+        const float x = ish ? xg[e] * xe[e] : xa[e] * xv[e];
+        w[e] = Row::lead(RAG ? x * s : x, e);
+      }
       row_fwd(q * RPR + rr, w);
     }
     if (rr < L0) {
@@ -345,15 +445,23 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
   // K's rows are fetched while the columns of U and H are read
   constexpr int NK = KC ? NR : 1;  // rounds of K's rows
   float2 wr[NK][8];
+  uint32_t mk = 0;
 #pragma unroll
   for (int q = 0; q < NK; ++q) {
     const int g0 = q * RPR + rr;
     if (KC || g0 < L0) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) wr[q][e] = im.template kernel_point<KC>(kl, g0, tr + TR * e, scale);
+      for (int e = 0; e < 8; ++e) {
+        wr[q][e] = im.template kernel_point<KC>(kl, g0, tr + TR * e, RAG ? 1.f : scale);
+        if constexpr (RAG) mk = ra_umax(mk, ra_umax(ra_mag(wr[q][e].x), ra_mag(wr[q][e].y)));
+      }
     }
   }
+  const float Dv = ld1(Dp + c);
+  if (RAG && norm) mags.put(2, mk, tid);
   __syncthreads();
+  if (RAG && norm) ek = imax(mags.get(2), ra_exponent(ra_mag(Dv)));
+  const float ks = scale * ra_pow2(-ek);
   if (tid == 0) {
     float s = 0.f;
 #pragma unroll
@@ -373,7 +481,10 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
     const int g0 = q * RPR + rr;
     if (KC || g0 < L0) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) wr[q][e] = KC ? Row::lead(wr[q][e], e) : Row::lead(wr[q][e].x, e);
+      for (int e = 0; e < 8; ++e) {
+        if constexpr (RAG) wr[q][e] = c_scale(wr[q][e], ks);
+        wr[q][e] = KC ? Row::lead(wr[q][e], e) : Row::lead(wr[q][e].x, e);
+      }
       row_fwd(g0, wr[q]);
     }
   }
@@ -388,7 +499,7 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
   Col::template run<false>(wu, tc, cp, ctw);
   Col::template run<false>(wh, tc, cp, ctw);
   {
-    const float Ds = scale * ld1(Dp + c);
+    const float Ds = Dv * ks;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const float2 kd = make_float2(wk[e].x + Ds, wk[e].y);
@@ -418,6 +529,7 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
 #pragma unroll
     for (int e = 0; e < 8; ++e) w[e] = row[tr + Row::off(e)];
     Row::inverse(w, tr, row, itw);
+    if (RAG && norm) ra_ldexp(w, (isgu ? eh : eu) + ek);
     if (isgu) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -449,6 +561,7 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
 #pragma unroll
       for (int e = 0; e < 8; ++e) w[e] = row[tr + Row::off(e)];
       Row::inverse(w, tr, row, itw);
+      if (RAG && norm) ra_ldexp(w, eu + eh);
       if constexpr (!KC) {
 #pragma unroll
         for (int e = 0; e < 8; ++e)
@@ -467,12 +580,13 @@ __global__ void __launch_bounds__((Ra2D<P0, N>::NT)) __attribute__((amdgpu_waves
 }
 
 template <int P0, int N, typename TS, bool RAG>
-hipError_t launch_fwd_t(const FftConvArgs& a, hipStream_t s) {
+hipError_t launch_fwd_t(const FftConvArgs& a, bool norm, hipStream_t s) {
   constexpr int NT = Ra2D<P0, N>::NT;
+  if (norm && !kRa2Norm<P0, N, RAG>) return hipErrorInvalidValue;  // no shape of the mixed plan
 #define HY_RA(KC, ACT, KH, GRID)                                                                               \
   hipLaunchKernelGGL((conv2d_ra<P0, N, KC, TS, ACT, KH, RAG>), dim3((unsigned)(GRID)), dim3(NT), 0, s,              \
                      (const TS*)a.x1, (const TS*)a.x2, (const TS*)a.v, (const TS*)a.k, (const TS*)a.D,         \
-                     (TS*)a.y, (int)a.C, a.kC, a.act_in, a.khat, (int)a.L[0], (int)a.L[1], a.periodic)
+                     (TS*)a.y, (int)a.C, a.kC, a.act_in, a.khat, (int)a.L[0], (int)a.L[1], a.periodic, norm)
   if (a.centered || a.periodic) {
     if (a.act) HY_RA(true, true, 0, a.lines);
     else HY_RA(true, false, 0, a.lines);
@@ -489,13 +603,13 @@ hipError_t launch_fwd_t(const FftConvArgs& a, hipStream_t s) {
 }
 
 template <int P0, int N, typename TS, bool RAG>
-hipError_t launch_bwd_t(const FftConvBwdArgs& b, hipStream_t s) {
+hipError_t launch_bwd_t(const FftConvBwdArgs& b, bool norm, hipStream_t s) {
   const FftConvArgs& a = b.f;
   constexpr int NT = Ra2D<P0, N>::NT;
 #define HY_RA(KC)                                                                                                 \
   hipLaunchKernelGGL((bwd2d_ra<P0, N, KC, TS, RAG>), dim3((unsigned)a.lines), dim3(NT), 0, s, (const TS*)a.x1,         \
                      (const TS*)a.x2, (const TS*)a.v, (const TS*)a.k, (const TS*)a.D, (const TS*)b.gy,            \
-                     (TS*)b.gx1, (TS*)b.gx2, (TS*)b.gv, (TS*)b.gk, b.partial, (int)a.C, (int)a.L[0], (int)a.L[1])
+                     (TS*)b.gx1, (TS*)b.gx2, (TS*)b.gv, (TS*)b.gk, b.partial, (int)a.C, (int)a.L[0], (int)a.L[1], norm)
   if (a.centered) HY_RA(true);
   else HY_RA(false);
 #undef HY_RA
@@ -531,25 +645,25 @@ bool ra2d_ragged(const FftConvArgs& a) {
   return false;
 }
 
-hipError_t launch_ra2d(const FftConvArgs& a, hipStream_t s) {
+hipError_t launch_ra2d(const FftConvArgs& a, bool norm, hipStream_t s) {
 #define HY_CASE(p0, p1)                                                                                        \
   if (a.P[0] == p0 && a.P[1] == p1) {                                                                          \
     if (a.rl)                                                                                                  \
-      return a.bf16 ? launch_fwd_t<p0, p1 / 2, uint16_t, true>(a, s) : launch_fwd_t<p0, p1 / 2, float, true>(a, s); \
-    return a.bf16 ? launch_fwd_t<p0, p1 / 2, uint16_t, false>(a, s) : launch_fwd_t<p0, p1 / 2, float, false>(a, s); \
+      return a.bf16 ? launch_fwd_t<p0, p1 / 2, uint16_t, true>(a, norm, s) : launch_fwd_t<p0, p1 / 2, float, true>(a, norm, s); \
+    return a.bf16 ? launch_fwd_t<p0, p1 / 2, uint16_t, false>(a, norm, s) : launch_fwd_t<p0, p1 / 2, float, false>(a, norm, s); \
   }
   HY_RA2D_SIZES(HY_CASE)
 #undef HY_CASE
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_ra2d_backward(const FftConvBwdArgs& b, hipStream_t s) {
+hipError_t launch_ra2d_backward(const FftConvBwdArgs& b, bool norm, hipStream_t s) {
   const FftConvArgs& a = b.f;
 #define HY_CASE(p0, p1)                                                                                        \
   if (a.P[0] == p0 && a.P[1] == p1) {                                                                          \
     if (a.rl)                                                                                                  \
-      return a.bf16 ? launch_bwd_t<p0, p1 / 2, uint16_t, true>(b, s) : launch_bwd_t<p0, p1 / 2, float, true>(b, s); \
-    return a.bf16 ? launch_bwd_t<p0, p1 / 2, uint16_t, false>(b, s) : launch_bwd_t<p0, p1 / 2, float, false>(b, s); \
+      return a.bf16 ? launch_bwd_t<p0, p1 / 2, uint16_t, true>(b, norm, s) : launch_bwd_t<p0, p1 / 2, float, true>(b, norm, s); \
+    return a.bf16 ? launch_bwd_t<p0, p1 / 2, uint16_t, false>(b, norm, s) : launch_bwd_t<p0, p1 / 2, float, false>(b, norm, s); \
   }
   HY_RA2D_SIZES(HY_CASE)
 #undef HY_CASE

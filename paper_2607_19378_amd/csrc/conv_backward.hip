@@ -541,7 +541,7 @@ hipError_t launch_typed(const FftConvBwdArgs& b, hipStream_t s) {
     HY_BWD1D_SIZES(HY_CASE)
 #undef HY_CASE
   } else if (ra2d_supported(a)) {
-    e = launch_ra2d_backward(b, s);
+    e = launch_ra2d_backward(b, false, s);
   } else if (a.ndim == 2) {
 #define HY_CASE(p0, p1)                                                                                          \
   if (a.P[0] == p0 && a.P[1] == p1)                                                                              \

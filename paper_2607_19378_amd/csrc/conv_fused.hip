@@ -954,7 +954,7 @@ size_t fused2d_khat_bytes(const FftConvArgs& a) {
 }
 
 hipError_t launch_fused2d(const FftConvArgs& a, hipStream_t s) {
-  if (ra2d_supported(a)) return launch_ra2d(a, s);
+  if (ra2d_supported(a)) return launch_ra2d(a, false, s);
 #define HY_CASE(p0, p1) if (a.P[0] == p0 && a.P[1] == p1) return launch_2d_fused_p<p0, p1>(a, s);
   HY_FUSED2D_SIZES(HY_CASE)
 #undef HY_CASE

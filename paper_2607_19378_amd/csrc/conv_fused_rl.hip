@@ -399,7 +399,7 @@ bool fused_rl_supported(const FftConvArgs& a) {
 
 hipError_t launch_fused_rl(const FftConvArgs& a, hipStream_t s) {
   if (!fused_rl_supported(a)) return hipErrorInvalidValue;
-  if (ra2d_ragged(a)) return launch_ra2d(a, s);  // circular 8 x 256 x 57 x 40, fp32: 257 -> 69 us
+  if (ra2d_ragged(a)) return launch_ra2d(a, false, s);  // circular 8 x 256 x 57 x 40, fp32: 257 -> 69 us
   if (a.ndim == 1) {
     switch (a.P[0]) {
       case 4: return launch_1d_p<4>(a, s);

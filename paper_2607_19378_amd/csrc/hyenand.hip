@@ -605,7 +605,7 @@ hipError_t run_ra_line(const FftConvArgs& a, hipStream_t s) {
 // over side streams for the multi-pass plans.
 hipError_t launch_plan(const FftConvArgs& a, Plan p, size_t per, hipStream_t s) {
   switch (p) {
-    case PLAN_FUSED1D: return ra1d_supported(a) ? launch_ra1d(a, s) : launch_fused1d(a, s);
+    case PLAN_FUSED1D: return ra1d_supported(a) ? launch_ra1d(a, false, s) : launch_fused1d(a, s);
     case PLAN_FUSED2D: return launch_fused2d(a, s);
     case PLAN_EMBED:  // forward() embeds the other shapes itself
     case PLAN_MULTIPASS:
@@ -623,12 +623,12 @@ hipError_t launch_plan(const FftConvArgs& a, Plan p, size_t per, hipStream_t s) 
       return run_chunked(a, per, s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
         return launch_fourstep(a, l0, nl, ws, st);
       });
-    case PLAN_FUSED_RL: return ra1d_supported(a) ? launch_ra1d(a, s) : launch_fused_rl(a, s);
+    case PLAN_FUSED_RL: return ra1d_supported(a) ? launch_ra1d(a, false, s) : launch_fused_rl(a, s);
     case PLAN_MIXED:
       // not circular images, whose mixed-radix transforms have no padding (8 x 256
       // x 28 x 28, fp32: 21.3 us)
-      if (ra2d_ragged(a) && !a.periodic && !mixed_forced()) return launch_ra2d(a, s);
-      return mixed_line_on_ra1d(a) ? launch_ra1d(a, s) : launch_mixed(a, s);
+      if (ra2d_ragged(a) && !a.periodic && !mixed_forced()) return launch_ra2d(a, true, s);
+      return mixed_line_on_ra1d(a) ? launch_ra1d(a, true, s) : launch_mixed(a, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -996,10 +996,10 @@ hyenand_status hyenand_fftconv_backward(const void* x1, const void* x2, const vo
   hipError_t err = hipSuccess;
   clear_pending_error();
   if (bwd_runs_ra1d(a, p)) {
-    err = launch_ra1d_backward(b, s);
+    err = launch_ra1d_backward(b, p == BWD_MIXED, s);
     if (err == hipSuccess) err = launch_backward_reduce(b, 1, s);
   } else if (ra2d_ragged(a) && !a.periodic && !(p == BWD_MIXED && mixed_forced())) {  // sums as above
-    err = launch_ra2d_backward(b, s);
+    err = launch_ra2d_backward(b, p == BWD_MIXED, s);
     if (err == hipSuccess) err = launch_backward_reduce(b, 1, s);
   } else if (const bool line = bwd_runs_ra_line(a, p, need); line || bwd_runs_ra_mp(a, p, need)) {
     FftConvArgs sa = b.f;

@@ -60,10 +60,11 @@ hipError_t launch_fused2d(const FftConvArgs& a, hipStream_t s);
 size_t fused2d_khat_bytes(const FftConvArgs& a);
 // single-pass 2D kernels of the linear and centered modes (conv2d_ra.hip),
 // forward and backward; launch_fused2d and launch_backward take them where
-// they are supported
+// they are supported.  norm: u, k and h of a line scaled by powers of two, for
+// the calls that the mixed-radix kernels, which do so, would take
 bool ra2d_supported(const FftConvArgs& a);
 bool ra2d_ragged(const FftConvArgs& a);  // extents that are no powers of two (backward: not of the circular mode)
-hipError_t launch_ra2d(const FftConvArgs& a, hipStream_t s);
+hipError_t launch_ra2d(const FftConvArgs& a, bool norm, hipStream_t s);
 
 // single pass for grid extents that are not powers of two on power-of-two
 // transforms (P_d = the smallest power of two >= 2 L_d - 1; a circular axis
@@ -101,7 +102,7 @@ hipError_t launch_ra_mp(const FftConvArgs& a, int64_t line0, int64_t nl, void* w
 // non-circular lines on right-angle transforms, of any length (conv1d_ra.hip):
 // up to 8192 points in one pass, beyond in three
 bool ra1d_supported(const FftConvArgs& a);
-hipError_t launch_ra1d(const FftConvArgs& a, hipStream_t s);
+hipError_t launch_ra1d(const FftConvArgs& a, bool norm, hipStream_t s);  // norm as in launch_ra2d
 bool ra_line_supported(const FftConvArgs& a);
 size_t ra_line_bytes_per_line(const FftConvArgs& a, bool backward);
 hipError_t launch_ra_line(const FftConvArgs& a, int64_t line0, int64_t nl, void* ws, hipStream_t s);
@@ -117,7 +118,7 @@ struct FftConvBwdArgs {
 // and h fit in LDS); one float of partial per line; launches the gD reduction
 bool fused_backward_supported(const FftConvArgs& a);
 hipError_t launch_backward(const FftConvBwdArgs& b, hipStream_t s);
-hipError_t launch_ra2d_backward(const FftConvBwdArgs& b, hipStream_t s);  // without the gD reduction
+hipError_t launch_ra2d_backward(const FftConvBwdArgs& b, bool norm, hipStream_t s);  // without the gD reduction
 // multi-pass 2D/3D and four-step 1D: one call per chunk of lines [line0,
 // line0 + nl) with their three spectra in ws; partial holds the given number
 // of sums per line; launch_backward_reduce adds them into gD afterwards
@@ -136,7 +137,7 @@ hipError_t launch_ra_mp_backward(const FftConvBwdArgs& b, int64_t line0, int64_t
 // 1D on right-angle transforms (conv1d_ra.hip): single pass up to 8192 points
 // (one float of partial per line, without the gD reduction), or three passes
 bool ra1d_backward_supported(const FftConvArgs& a);
-hipError_t launch_ra1d_backward(const FftConvBwdArgs& b, hipStream_t s);
+hipError_t launch_ra1d_backward(const FftConvBwdArgs& b, bool norm, hipStream_t s);
 hipError_t launch_ra_line_backward(const FftConvBwdArgs& b, int64_t line0, int64_t nl, void* ws, hipStream_t s);
 // mixed-radix single pass (conv_mixed.hip) on the forward's transform grid,
 // grids of up to about 3000 points; one float of partial per line

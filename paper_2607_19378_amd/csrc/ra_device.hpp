@@ -34,6 +34,72 @@
 namespace hyenand {
 namespace {
 
+// ---------------------------------------------------------------------------
+// Magnitudes of a line.  The sums of a transform leave fp32's range where the
+// inputs come near its ends (196 values of 1e37, a kernel of 1e-36 under the
+// normalisation of 1 / N), although u k does not.  The mixed-radix kernels scale
+// u, k and h of a line, exactly, by powers of two to magnitudes near 1 and undo
+// it at the store; in their place these kernels do too (norm).  Everywhere else
+// it would cost without need: 6 to 17 % of 28^2 to 57 x 40 images, 8 % of 64
+// lines of 3000 points.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t ra_umax(uint32_t a, uint32_t b) { return a > b ? a : b; }
+// the bits of |x|, ordered like the values; NaN above all
+__device__ __forceinline__ uint32_t ra_mag(float x) { return __float_as_uint(fabsf(x)); }
+// largest of a wavefront (every lane active), in every lane: maxima over rows of
+// 16 lanes, then across the rows
+__device__ __forceinline__ uint32_t ra_wave_max(uint32_t m) {
+#define HY_DPP(ctrl, rows) m = ra_umax(m, (uint32_t)__builtin_amdgcn_update_dpp((int)m, (int)m, ctrl, rows, 0xf, false))
+  HY_DPP(0x111, 0xf);  // row_shr:1, 2, 4, 8
+  HY_DPP(0x112, 0xf);
+  HY_DPP(0x114, 0xf);
+  HY_DPP(0x118, 0xf);
+  HY_DPP(0x142, 0xa);  // row_bcast:15, 31
+  HY_DPP(0x143, 0xc);
+#undef HY_DPP
+  return (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
+}
+// Exponent e of the magnitude with bits b: b 2^-e in [1/2, 1), 0 for 0, infinity
+// and NaN; within [-100, 112], so that 2^-e and 2^-e / 2^14 are normal numbers
+// (what that leaves unscaled is within 2^16 of 1).
+__device__ __forceinline__ int ra_exponent(uint32_t b) {
+  const int e = __builtin_amdgcn_frexp_expf(__uint_as_float(b));
+  return e < -100 ? -100 : (e > 112 ? 112 : e);
+}
+template <int E>
+__device__ __forceinline__ void ra_ldexp(float2 (&w)[E], int e) {
+#pragma unroll
+  for (int i = 0; i < E; ++i) w[i] = make_float2(ldexpf(w[i].x, e), ldexpf(w[i].y, e));
+}
+__device__ __forceinline__ float ra_pow2(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
+// The exponents of NS signals' largest magnitudes over a workgroup of W
+// wavefronts: put (every lane, its magnitude), a barrier of the workgroup, get.
+// A single wavefront needs neither LDS nor the barrier.
+template <int W, int NS>
+struct RaMags {
+  uint32_t one[NS];
+  uint32_t* s;  // NS W words of LDS
+  __device__ __forceinline__ void put(int i, uint32_t m, int tid) {
+    m = ra_wave_max(m);
+    if constexpr (W == 1) one[i] = m;
+    else if ((tid & 63) == 0) s[i * W + (tid >> 6)] = m;
+  }
+  __device__ __forceinline__ void sync() const {
+    if constexpr (W > 1) __syncthreads();
+  }
+  __device__ __forceinline__ int get(int i) const {
+    uint32_t b;
+    if constexpr (W == 1) {
+      b = one[i];
+    } else {
+      b = s[i * W];
+#pragma unroll
+      for (int j = 1; j < W; ++j) b = ra_umax(b, s[i * W + j]);
+    }
+    return __builtin_amdgcn_readfirstlane(ra_exponent(b));
+  }
+};
+
 // Orders this wavefront's LDS accesses for the compiler; the hardware
 // performs them in order.
 __device__ __forceinline__ void wave_sync() {

@@ -74,3 +74,35 @@ def test_operator(L, mode):
     torch.cuda.synchronize()
     ref = oracle.operator(*[a.astype(np.float64) for a in (q, kin, vin, k, D, wi, wo)], pad_mode=mode)
     assert rel_l2(from_device(y), ref) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("u,k", [(1e37, 1e-30), (1e30, 1e-36)])
+@pytest.mark.parametrize("L,mode,B", [(300, "circular", 1), (3000, "circular", 1), (3000, "circular", 300),
+                                      (1000, "linear", 1), (700, "centered", 1), (300, "linear", 1)])
+def test_magnitudes_near_the_range(L, mode, B, u, k):
+    """Lines of the mixed plan (circular forward, non-circular backward) scale u, h and k by powers of two: sums of u
+    that leave fp32's range, and kernels that the normalisation of the inverse would make subnormal, change no line's
+    relative error (few and many lines: 8 and 16 points per lane)."""
+    import torch
+    from paper_2607_19378_amd import hyenand as H
+    rng = np.random.default_rng(L)
+    shape = (B, 2, L)
+    x1 = np.abs(rng.standard_normal(shape)) * u  # one sign: the DC bin is the sum of all
+    x2, v, gy = rng.standard_normal(shape), np.ones(shape), 1e-4 * rng.standard_normal(shape)
+    kern = rng.standard_normal(oracle.kernel_shape(shape, mode)) * k
+    D = rng.standard_normal(2) * k
+    arrays = [W.quantise(a, "f32") for a in (x1, x2, v, kern, D, gy)]
+    dev = [to_device(a, "f32") for a in arrays]
+    log(f"ra1d range {L} {mode} {B} {u:g} {k:g}")
+    f = [a.astype(np.float64) for a in arrays]
+    if mode == "circular":  # the oracle's circular FFT takes powers of two: numpy's serves here
+        assert H.plan_name(shape, mode, "f32") == "mixed1d"
+        y = from_device(H.fftconv(*dev[:5], pad_mode=mode))
+        ux = f[0] * f[2]
+        ref = f[1] * (np.fft.irfft(np.fft.rfft(ux) * np.fft.rfft(f[3]), n=L) + f[4][None, :, None] * ux)
+        assert per_line_worst(y, ref, 2 * B) <= TOL["f32"]
+        return
+    got = H.backward(*dev, pad_mode=mode)
+    torch.cuda.synchronize()
+    for name, g, r in zip(("gx1", "gx2", "gv", "gk"), got, oracle.backward_direct(*f, mode)):
+        assert per_line_worst(from_device(g), r, 2 * B) <= TOL["f32"], name

@@ -79,3 +79,32 @@ def test_lines_of_different_scales(mode):
     inp.k *= np.float32(1e-4)
     inp.D *= np.float32(1e-4)
     assert per_line_worst(run_gpu(inp), oracle.conv_fft(*inp.as_f64(), mode), 4) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("u,k", [(1e37, 1e-30), (1e30, 1e-36)])
+@pytest.mark.parametrize("grid,mode,forward", [((14, 14), "linear", True), ((14, 14), "centered", True),
+                                               ((17, 28), "centered", True), ((22, 22), "linear", True),
+                                               ((28, 28), "centered", False)])
+def test_magnitudes_near_the_range(grid, mode, forward, u, k, dtype):
+    """Images of the mixed plan (28 x 28: its backward) scale u, h and k by powers of two: sums of u that leave fp32's
+    range, and kernels that the normalisation of the inverse would make subnormal, change no line's relative error."""
+    import torch
+    from paper_2607_19378_amd import hyenand as H
+    rng = np.random.default_rng(31 + sum(grid))
+    shape = (1, 3) + grid
+    x1 = np.abs(rng.standard_normal(shape)) * u  # one sign: the DC bin is the sum of all
+    x2, v, gy = rng.standard_normal(shape), np.ones(shape), 1e-3 * rng.standard_normal(shape)
+    kern = rng.standard_normal(oracle.kernel_shape(shape, mode)) * k
+    D = rng.standard_normal(3) * k
+    arrays = [W.quantise(a, dtype) for a in (x1, x2, v, kern, D, gy)]
+    dev = [to_device(a, dtype) for a in arrays]
+    log(f"ra2d range {grid} {mode} {dtype} {u:g} {k:g}")
+    assert (H.plan_name(shape, mode, dtype) == "mixed2d") == forward
+    y = H.fftconv(*dev[:5], pad_mode=mode)
+    got = H.backward(*dev, pad_mode=mode)
+    torch.cuda.synchronize()
+    f = [W.storage_to_f64(a, dtype) for a in arrays]
+    assert not forward or per_line_worst(from_device(y), oracle.conv_fft(*f[:5], mode), 3) <= TOL[dtype]
+    for name, g, r in zip(("gx1", "gx2", "gv", "gk"), got, oracle.backward_direct(*f, mode)):
+        assert per_line_worst(from_device(g), r, 3) <= TOL[dtype], name

@@ -40,3 +40,18 @@ def test_lines_fit():
         assert 2 * n * 8 <= H.workspace_min(shape, mode, "f32"), (L, mode)
         sums = (min(64, -(-L // 8192)) * 4 + 255) // 256 * 256
         assert sums + 3 * n * 8 <= H.backward_workspace_min(shape, mode, "f32"), (L, mode)
+
+
+def test_scaled_lines_have_kernels():
+    """The right-angle kernels that take the mixed plan's calls scale u, k and h by powers of two; the kernels built
+    without that (images beyond 32 x 32 points, non-circular lines, lines beyond 4096, backward beyond 2048 points) must
+    not be reached by the plan."""
+    for n0, n1 in itertools.product(range(17, 65), repeat=2):
+        if max(n0, n1) > 32 and not (n0 & (n0 - 1) == 0 and n1 & (n1 - 1) == 0):
+            for mode in ("linear", "centered"):
+                assert H.plan_name((2, 3, n0, n1), mode, "f32") == "fused2d_any", (n0, n1, mode)
+    for L in list(range(257, 4097, 7)) + [4099, 5000, 8191]:
+        assert L & (L - 1) == 0 or H.plan_name((2, 3, L), "linear", "f32") == "fused1d_any", L
+        assert L <= 4096 or H.plan_name((2, 3, L), "circular", "f32") == "fused1d_any", L
+    for L in range(2049, 8192, 11):  # embedded, whose least workspace is more than the sums of six lines
+        assert H.backward_workspace_min((2, 3, L), "linear", "f32") > 256, L
