@@ -4,7 +4,9 @@ Tables (all values exp(-2 pi i j / n) rounded once to float32):
   kTwCoarse[j] = exp(-2 pi i j / 4096),  j < 4096
   kTwFine[j]   = exp(-2 pi i j / 2^24),  j < 4096
   kCos32/kSin32[j] = cos/sin(2 pi j / 32), j < 32 (radix-<=32 butterfly constants)
-  kCos64/kSin64[j] = cos/sin(2 pi j / 64), j < 16 (shifted radix-16 passes)
+  kTwDelta[j]  = exp(-2 pi i j / 32768) - 1,  j < 1024 (weights near 1, to full relative accuracy)
+  kCos64/kSin64[j] = cos/sin(2 pi j / 64), j < 16 (shifted radix-16 passes), and
+    kCos64Lo/kSin64Lo[j] what their rounding leaves
   kPassTw_<log2 NS>_<log2 R>: for every Stockham pass shape (NS, R) with
     NS * R <= 8192, the twiddles exp(-2 pi i jm r / (NS R)) laid out
     [r - 1][jm] (r in 1..R-1, jm in 0..NS-1), so lanes holding consecutive jm
@@ -48,6 +50,11 @@ def main():
              "#pragma once",
              table("kTwCoarse", 4096, 4096),
              table("kTwFine", 1 << 24, 4096)]
+    rows = []
+    for j in range(1024):
+        a = 2.0 * math.pi * j / 32768
+        rows.append(f"  {{{lit(-2.0 * math.sin(a / 2) ** 2)}, {lit(-math.sin(a))}}},")
+    parts.append("static __device__ const float2 kTwDelta[1024] = {\n" + "\n".join(rows) + "\n};")
     # Stockham pass tables: one array per pass shape, so that a translation
     # unit holds only the shapes its kernels use
     parts.append("template <int LNS, int LR>\n__device__ __forceinline__ const float2* pass_table();")
@@ -75,6 +82,9 @@ def main():
     sin64 = ", ".join(lit(math.sin(2 * math.pi * j / 64)) for j in range(16))
     parts.append(f"constexpr float kCos64[16] = {{{cos64}}};")
     parts.append(f"constexpr float kSin64[16] = {{{sin64}}};")
+    for name, fn in (("kCos64Lo", math.cos), ("kSin64Lo", math.sin)):
+        lo = ", ".join(lit(fn(2 * math.pi * j / 64) - f32(fn(2 * math.pi * j / 64))) for j in range(16))
+        parts.append(f"constexpr float {name}[16] = {{{lo}}};")
     text = "\n".join(parts) + "\n"
     tmp = path + ".tmp"
     with open(tmp, "w") as f:
