@@ -5,8 +5,8 @@ Tables (all values exp(-2 pi i j / n) rounded once to float32):
   kTwFine[j]   = exp(-2 pi i j / 2^24),  j < 4096
   kCos32/kSin32[j] = cos/sin(2 pi j / 32), j < 32 (radix-<=32 butterfly constants)
   kTwDelta[j]  = exp(-2 pi i j / 32768) - 1,  j < 1024 (weights near 1, to full relative accuracy)
-  kCos64/kSin64[j] = cos/sin(2 pi j / 64), j < 16 (shifted radix-16 passes), and
-    kCos64Lo/kSin64Lo[j] what their rounding leaves
+  kCos64/kSin64[j] = cos/sin(2 pi j / 64), j < 16 (shifted radix-16 passes)
+  kCos32Lo, kSin32Lo, kCos64Lo, kSin64Lo: what the rounding of those leaves
   kPassTw_<log2 NS>_<log2 R>: for every Stockham pass shape (NS, R) with
     NS * R <= 8192, the twiddles exp(-2 pi i jm r / (NS R)) laid out
     [r - 1][jm] (r in 1..R-1, jm in 0..NS-1), so lanes holding consecutive jm
@@ -82,9 +82,10 @@ def main():
     sin64 = ", ".join(lit(math.sin(2 * math.pi * j / 64)) for j in range(16))
     parts.append(f"constexpr float kCos64[16] = {{{cos64}}};")
     parts.append(f"constexpr float kSin64[16] = {{{sin64}}};")
-    for name, fn in (("kCos64Lo", math.cos), ("kSin64Lo", math.sin)):
-        lo = ", ".join(lit(fn(2 * math.pi * j / 64) - f32(fn(2 * math.pi * j / 64))) for j in range(16))
-        parts.append(f"constexpr float {name}[16] = {{{lo}}};")
+    for name, fn, n, count in (("kCos32Lo", math.cos, 32, 32), ("kSin32Lo", math.sin, 32, 32),
+                               ("kCos64Lo", math.cos, 64, 16), ("kSin64Lo", math.sin, 64, 16)):
+        exact = [fn(2 * math.pi * j / n) for j in range(count)]
+        parts.append(f"constexpr float {name}[{count}] = {{{', '.join(lit(x - f32(x)) for x in exact)}}};")
     text = "\n".join(parts) + "\n"
     tmp = path + ".tmp"
     with open(tmp, "w") as f:
