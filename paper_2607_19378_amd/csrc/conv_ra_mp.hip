@@ -15,6 +15,9 @@
 // planes of zeros, no padding bins.  A ragged grid costs its transform grid's
 // columns, not its copies: the embedded plan moved five (backward nine)
 // tensors on the padded grid and transformed all of it.
+#include <stdlib.h>
+#include <string.h>
+
 #include "multipass.hpp"
 #include "ra_mp.hpp"
 
@@ -347,8 +350,9 @@ RaGeom ra_geom(const FftConvArgs& a) {
   g.LL = (int)a.L[last];
   g.N = imax(16, (int)(a.P[last] / 2));
   // (rows of 8 points or less: the slab passes' 32-point rows would not fit in
-  // the workspace that is asked for)
-  g.slab = a.ndim == 3 && a.P[last] >= 32 && ra_slab_takes(g.P1, imax(32, g.N));
+  // the workspace that is asked for; HYENAND_SLAB=0 keeps to the passes per axis)
+  const char* const slab = getenv("HYENAND_SLAB");
+  g.slab = a.ndim == 3 && a.P[last] >= 32 && ra_slab_takes(g.P1, imax(32, g.N)) && !(slab && strcmp(slab, "0") == 0);
   if (g.slab) g.N = imax(32, g.N);
   g.kmode = a.periodic ? RA_PERIODIC : (a.centered ? RA_CENTERED : RA_LINEAR);
   g.KP = g.kmode == RA_LINEAR ? g.L0 : 2 * g.L0 - 1;

@@ -56,6 +56,29 @@ def test_backward(grid, mode, dtype):
         assert rel_l2(from_device(g), r) <= TOL[dtype], name
 
 
+@pytest.mark.parametrize("grid,mode", [((4, 128, 128), "linear"), ((3, 40, 100), "centered"), ((5, 48, 48), "centered"),
+                                       ((4, 33, 20), "linear"), ((4, 20, 60), "circular")])
+def test_slab_and_axis_passes_agree(monkeypatch, grid, mode):
+    """HYENAND_SLAB=0 takes the rows and axis-1 passes in place of the slab ones (two foldings, one, 32-point rows):
+    other bits, the same values, forward and backward."""
+    import torch
+    from paper_2607_19378_amd import hyenand as H
+    inp = W.random_case(1, 2, grid, mode, "f32", seed=70 + sum(grid))
+    gy = np.random.default_rng(9).standard_normal(inp.workload.shape).astype(np.float32)
+    dev = [to_device(a, "f32") for a in (inp.x1, inp.x2, inp.v, inp.k, inp.D, gy)]
+    out = {}
+    for slab in ("1", "0"):
+        monkeypatch.setenv("HYENAND_SLAB", slab)
+        log(f"ra_mp slab {slab} {grid} {mode}")
+        res = [H.fftconv(*dev[:5], pad_mode=mode)]
+        if mode != "circular":  # embedded
+            res += H.backward(*dev, pad_mode=mode)[:4]
+        torch.cuda.synchronize()
+        out[slab] = [from_device(t) for t in res]
+    for a, b in zip(out["1"], out["0"]):
+        assert not np.array_equal(a, b) and rel_l2(a, b) <= 1e-6
+
+
 # relative L2 error (1e-7) of y and gk with the packed real transforms, which the right-angle rows replaced, on the
 # inputs of test_rounding
 PACKED = {((64, 64), "linear"): (1.767, 2.535), ((64, 64), "centered"): (2.159, 2.521),
