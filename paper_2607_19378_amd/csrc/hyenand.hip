@@ -200,8 +200,7 @@ size_t bytes_per_line(const FftConvArgs& a, Plan p) {
 // or equal on the MI355X for 512^2, 2^20 and 128^3 lines against 1, 3 and 4,
 // at 160 to 640 MiB budgets).  The recommended workspace is S such chunks;
 // HYENAND_WS_TARGET_MB sets the budget and HYENAND_CHUNK_STREAMS fixes S.
-size_t ws_target_bytes() {
-  size_t target = (size_t)160 << 20;
+size_t ws_target_bytes(size_t target = (size_t)160 << 20) {
   if (const char* e = getenv("HYENAND_WS_TARGET_MB")) {
     long mb = strtol(e, nullptr, 10);
     if (mb > 0) target = (size_t)mb << 20;
@@ -226,27 +225,37 @@ struct ChunkPlan {
   int streams;      // 1: everything on the caller's stream
 };
 
-// wide: one stream and chunks of up to 640 MiB, for the passes of ragged grids
-// (conv_ra_mp.hip), whose callers hold a workspace of that order anyway.  Their
-// lines are short (about 1 to 10 MB of spectra) and a launch tail costs more
-// than the cache saves: 4 x 64 images of 200 x 150 329 -> 291 us, 2 x 32
-// volumes of 48^3 497 -> 474 us.  Power-of-two grids keep the rule above (one
-// line of 128^3 points is 67 MB: 3378 us, wide 3994 us).
-// Calls of up to 32 MiB of spectra run on one stream too: a second one, with
-// the events that tie it to the caller's, costs about 70 us whatever the call
+// Ragged grids (a.rl), whose callers hold a workspace of five tensors anyway:
+//  * short lines (up to 8 MiB of spectra a line in 2D, 2 MiB in 1D and 3D) run on
+//    one stream in chunks of up to 640 MiB: a launch tail then costs more than the
+//    cache saves.  Against two streams and 160 MiB: 4 x 64 images of 200 x 150 314
+//    -> 280 us, 2 x 64 of 500 x 500 904 -> 867 (backward, 8.2 MB a line, 2364 ->
+//    2254), 4 x 64 of 250 x 250 411 -> 368;
+//  * longer ones run on two streams, which hide the launch tails that one stream
+//    has, in 3D with 320 MiB, since a chunk of 160 may be one line, whose launches
+//    leave CUs idle.  Against one stream and 640 MiB (2 x 160 in brackets): 32
+//    volumes of 120^3, centered, 2996 -> 2750 us [2750], backward 6395 -> 5712
+//    [5695]; 64 of 80^3 3512 -> 3267 [3679]; 32 of 100^3 1607 -> 1515 [1614]; 64 lines of
+//    300001 points, 2 x 160, backward 1127 -> 982.
+// Power-of-two grids: two streams, 160 MiB (one line of 128^3 points is 67 MB: 3373
+// us; one stream, 640 MiB 3923).
+// Calls of up to 32 MiB of spectra run on one stream whatever the grid: a second
+// one, with the events that tie it to the caller's, costs about 70 us a call
 // (48 images of 8 x 32 87 -> 24 us, 128 of 128 x 32 69 -> 20, of 128 x 128, at
 // the limit, 71 -> 42; 32 lines of 16384 points 68 -> 23; circular, 32 images of
 // 256 x 64 71 -> 25).
-ChunkPlan plan_chunks(int64_t lines, size_t per, size_t ws_bytes, bool wide) {
+ChunkPlan plan_chunks(const FftConvArgs& a, size_t per, bool ragged) {
   ChunkPlan c;
-  const int64_t fit = (int64_t)(ws_bytes / per);  // >= 1, checked by the caller
+  const int64_t lines = a.lines, fit = (int64_t)(a.ws_bytes / per);  // >= 1, checked by the caller
   const bool set = getenv("HYENAND_WS_TARGET_MB") || getenv("HYENAND_CHUNK_STREAMS");
-  wide = (wide || (size_t)lines * per <= (size_t)32 << 20) && !set;
+  const bool brief = ragged && per <= (size_t)(a.ndim == 2 ? 8 : 2) << 20;
+  const bool wide = (brief || (size_t)lines * per <= (size_t)32 << 20) && !set;
   const int want = wide ? 1 : chunk_streams();
   c.streams = want;
   if (c.streams > fit) c.streams = (int)fit;
   if (c.streams > lines) c.streams = (int)lines;
-  int64_t target = (int64_t)((wide ? (size_t)640 << 20 : ws_target_bytes()) / (size_t)want / per);
+  const size_t budget = wide ? (size_t)640 << 20 : ws_target_bytes((size_t)(ragged && a.ndim == 3 ? 320 : 160) << 20);
+  int64_t target = (int64_t)(budget / (size_t)want / per);
   if (target < 1) target = 1;
   int64_t chunk = fit / c.streams;
   if (chunk > target) chunk = target;
@@ -351,8 +360,8 @@ hipError_t side_set(hipStream_t caller, SideSet** out) {
 // the caller's stream, chunk j runs on side stream j % S with workspace part
 // j % S, and the caller's stream waits for all S before any later work.
 template <class Launch>
-hipError_t run_chunked(const FftConvArgs& a, size_t per, hipStream_t caller, Launch launch, bool wide = false) {
-  const ChunkPlan c = plan_chunks(a.lines, per, a.ws_bytes, wide);
+hipError_t run_chunked(const FftConvArgs& a, size_t per, hipStream_t caller, Launch launch, bool ragged = false) {
+  const ChunkPlan c = plan_chunks(a, per, ragged);
   if (c.streams == 1) {
     for (int64_t j = 0; j < c.nchunks; ++j) {
       const int64_t line0 = j * c.chunk;
