@@ -348,7 +348,8 @@ struct RaLine {
 };
 
 // a tile of TL adjacent columns of N1 points: as wide as two tiles fit in a CU
-// (runs of TL values of the tensors), 512 lanes
+// (runs of TL values of the tensors), 64 lanes (N1 up to 16), 128, 256 or 512 (from
+// N1 = 128 on)
 template <int N1>
 struct RaColsCfg {
   static constexpr int tl(int cap) { return cap > 1 && N1 * (cap + 1) * 8 > 76 * 1024 ? tl(cap / 2) : cap; }

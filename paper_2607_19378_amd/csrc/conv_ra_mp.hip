@@ -48,7 +48,7 @@ __global__ void __launch_bounds__(kRaNT)
   using Cf = RaRowsCfg<N>;
   using Row = typename Cf::Row;
   constexpr int E = Row::E, T = Row::T;
-  __shared__ float2 S[Cf::RB * Row::PITCH];
+  __shared__ __align__(16) float2 S[Cf::RB * Row::PITCH];  // 16-byte accesses of rows
   const int tid = threadIdx.x, lane = tid & 63;
   const int rr = tid / T, t = tid % T;
   float2* const row = S + rr * Row::PITCH;
@@ -130,7 +130,7 @@ __global__ void __launch_bounds__(kRaNT)
   using Cf = RaRowsCfg<N>;
   using Row = typename Cf::Row;
   constexpr int E = Row::E, T = Row::T;
-  __shared__ float2 S[Cf::RB * Row::PITCH];
+  __shared__ __align__(16) float2 S[Cf::RB * Row::PITCH];  // 16-byte accesses of rows
   const int tid = threadIdx.x, lane = tid & 63;
   const int rr = tid / T, t = tid % T;
   float2* const row = S + rr * Row::PITCH;

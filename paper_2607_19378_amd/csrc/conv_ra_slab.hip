@@ -62,7 +62,7 @@ __global__ void __launch_bounds__((SlabFwd<P1, N>::NT)) __attribute__((amdgpu_wa
   using Col = typename S_::Col;
   constexpr int F = S_::F, PH = S_::PH, PITCH = Row::PITCH, TR = Row::T, ER = Row::E, E = Col::E, TC = Col::T;
   constexpr int RPR = S_::RPR, NC = S_::NC;
-  __shared__ float2 S[PH * PITCH];
+  __shared__ __align__(16) float2 S[PH * PITCH];  // 16-byte accesses of rows
   const unsigned planes = FULL ? g.KP : g.L0;
   unsigned bid = blockIdx.x;
   const int p = F > 1 ? (int)(bid % F) : 0;
@@ -196,7 +196,7 @@ __global__ void __launch_bounds__((SlabInv<P1, N>::NT)) __attribute__((amdgpu_wa
   using Col = typename S_::Col;
   constexpr int PH = S_::PH, PITCH = Row::PITCH, TR = Row::T, ER = Row::E, E = Col::E, TC = Col::T, RPR = S_::RPR;
   constexpr int F = slab_foldings(N);
-  __shared__ float2 S[PH * PITCH];
+  __shared__ __align__(16) float2 S[PH * PITCH];  // 16-byte accesses of rows
   const bool dbl = OUT == RA_GK && g.kmode != RA_LINEAR;
   const unsigned planes = OUT == RA_GK ? g.KP : g.L0;
   unsigned bid = blockIdx.x;

@@ -136,9 +136,11 @@ __device__ __forceinline__ void ra_st(uint16_t* p, const float (&v)[8]) {
   *reinterpret_cast<uint4*>(p) =
       make_uint4(bf16_pack(v[0], v[1]), bf16_pack(v[2], v[3]), bf16_pack(v[4], v[5]), bf16_pack(v[6], v[7]));
 }
+// s and the rows in it are 16-byte aligned (the callers' arrays are declared so).
 // values x w (w null: x) of nrows rows from x and w on
 template <int PITCH, int RW, int NMAX, typename TS>
 __device__ __forceinline__ void ra_rows_in(const TS* x, const TS* w, int nrows, int LL, float* s, int lane) {
+  static_assert(PITCH * sizeof(float2) % 16 == 0, "rows at 16-byte offsets");
   constexpr int V = RaVec<TS>::V, ITER = (RW * NMAX / V + 63) / 64;
   const unsigned vr = (unsigned)LL / V, total = (unsigned)nrows * vr;
   wave_sync();
@@ -166,6 +168,7 @@ __device__ __forceinline__ void ra_rows_in(const TS* x, const TS* w, int nrows, 
 template <int PITCH, int RW, int NMAX, bool ACT, typename TS>
 __device__ __forceinline__ void ra_rows_out(RaOut out, const TS* p, const TS* q, TS* o, TS* o2, int nrows, int LL,
                                             const float* s, int lane) {
+  static_assert(PITCH * sizeof(float2) % 16 == 0, "rows at 16-byte offsets");
   constexpr int V = RaVec<TS>::V, ITER = (RW * NMAX / V + 63) / 64;
   const unsigned vr = (unsigned)LL / V, total = (unsigned)nrows * vr;
   wave_sync();
