@@ -16,30 +16,75 @@ def _ra_bytes(grid, mode, backward):
     return ((2 if backward else 1) * grid[0] + kp) * p1 * n * 8
 
 
+def _sums(grid, lines):
+    """The gD sums of h u: up to 64 parts of 8192 points a line, in a 256-byte block."""
+    data = 1
+    for n in grid:
+        data *= n
+    return (lines * min(64, -(-data // 8192)) * 4 + 255) // 256 * 256
+
+
 def test_power_of_two_grids_fit(monkeypatch):
+    """With one line and with many: the gD sums, which come before the spectra, grow with the lines.  Backward shapes
+    whose least workspace is one float per line run in a single pass and are left out."""
     monkeypatch.setenv("HYENAND_PLAN", "multipass")
     sizes = [2, 4, 8, 16, 32, 64, 128, 256, 512]
     grids = [g for nd in (2, 3) for g in itertools.product(sizes, repeat=nd)]
-    for grid, mode in itertools.product(grids, ("linear", "centered")):
-        shape = (1, 1) + grid
-        assert H.plan_name(shape, mode, "f32")[:6] in ("multip", "slab3d"), (grid, mode)
+    multipass = 0
+    for grid, mode, lines in itertools.product(grids, ("linear", "centered"), (1, 4095)):
+        shape = (1, lines) + grid
+        try:
+            name = H.plan_name(shape, mode, "f32")
+        except H.HyenandError as e:  # 4095 lines of the largest grids
+            assert e.status == H.ERR_UNSUPPORTED and lines > 1
+            continue
+        assert name[:6] in ("multip", "slab3d"), (grid, mode)
         assert _ra_bytes(grid, mode, False) <= H.workspace_min(shape, mode, "f32"), (grid, mode)
-        data = 1
-        for n in grid:
-            data *= n
-        sums = (min(64, -(-data // 8192)) * 4 + 255) // 256 * 256
-        assert sums + _ra_bytes(grid, mode, True) <= H.backward_workspace_min(shape, mode, "f32") or max(grid[:2]) <= 64 \
-            and len(grid) == 2, (grid, mode)
+        try:
+            least = H.backward_workspace_min(shape, mode, "f32")
+        except H.HyenandError as e:  # the centered mode's copies of 2^31 elements
+            assert e.status == H.ERR_UNSUPPORTED and lines > 1
+            continue
+        if least > (lines * 4 + 255) // 256 * 256:
+            multipass += 1
+            assert _sums(grid, lines) + _ra_bytes(grid, mode, True) <= least, (grid, mode, lines)
+    assert multipass > 1000
+
+
+def test_other_extents_fit():
+    """Ragged grids beyond the single-pass kernels, down to the narrowest rows, where the right-angle rows keep 16
+    values; and no shape of that plan is left without passes: a row of N values is no longer than the circular
+    problem's half row, and 3 L0 - 1 planes are at most its 2 P0."""
+    sizes = [3, 5, 7, 9, 17, 31, 33, 63, 65, 129, 200, 511]
+    seen = 0
+    for nd in (2, 3):
+        for grid, mode, lines in itertools.product(itertools.product(sizes, repeat=nd), ("linear", "centered", "circular"),
+                                                   (1, 21)):
+            try:
+                name = H.plan_name((1, lines) + grid, mode, "bf16")
+            except H.HyenandError as e:  # more than 2^31 points on the transform grid
+                assert e.status == H.ERR_UNSUPPORTED and lines * (4 * max(grid)) ** nd > 1 << 31
+                continue
+            if not name.startswith("embedded"):
+                continue
+            seen += 1
+            p = [1 << (2 * n - 2).bit_length() for n in grid]
+            n, p1 = max(16, p[-1] // 2), p[1] if nd == 3 else 1
+            if nd == 3 and p[-1] >= 32 and 32 <= p1 <= 256 and max(32, n) <= 128:
+                n = max(32, n)
+            planes = 2 * grid[0] if mode == "linear" else 3 * grid[0] - 1
+            assert planes * p1 * n * 8 <= H.workspace_min((1, lines) + grid, mode, "bf16"), (grid, mode)
+    assert seen > 1000
 
 
 def test_lines_fit():
     """Three-pass lines: two (backward three) spectra of N = P / 2 points, and the sums of h u."""
-    for L, mode in itertools.product((16384, 20000, 65537, 300001, 1 << 20, 1 << 21), ("linear", "centered")):
+    for L, mode, lines in itertools.product((16384, 20000, 65537, 300001, 1 << 20, 1 << 21), ("linear", "centered"),
+                                            (1, 300)):
         n = 1 << (2 * L - 2).bit_length() - 1
-        shape = (1, 1, L)
+        shape = (1, lines, L)
         assert 2 * n * 8 <= H.workspace_min(shape, mode, "f32"), (L, mode)
-        sums = (min(64, -(-L // 8192)) * 4 + 255) // 256 * 256
-        assert sums + 3 * n * 8 <= H.backward_workspace_min(shape, mode, "f32"), (L, mode)
+        assert _sums((L,), lines) + 3 * n * 8 <= H.backward_workspace_min(shape, mode, "f32"), (L, mode)
 
 
 def test_scaled_lines_have_kernels():
