@@ -114,15 +114,14 @@ hyenand_status parse_shape(int ndim, const int64_t* dims, int pad_mode, int dtyp
 }
 
 // A shape whose extents are not powers of two and that neither the
-// power-of-two single-pass kernels nor the mixed-radix ones take holds the
-// workspace of the embedded route and runs the right-angle passes in it
-// (runs_ra_mp, runs_ra_line); where those do not fit it is
-// embedded in its transform grid (P_d >= 2 L_d - 1, a power of two): on that
-// grid the call is the circular convolution of the zero-padded
-// inputs and of k placed at its displacements (conv_embed.hip), so x1, x2, v
-// and k are embedded, the circular plan of the grid runs, and y is extracted.
-// The workspace holds the five embedded tensors (x1, x2, v, k, y; each
-// 256-byte aligned) and then the circular plan's own.
+// power-of-two single-pass kernels nor the mixed-radix ones take (PLAN_EMBED)
+// runs the right-angle passes (runs_ra_mp, runs_ra_line).  It reports the
+// workspace of the circular problem on its transform grid (P_d >= 2 L_d - 1, a
+// power of two) with five tensors on that grid (x1, x2, v, k, y; each 256-byte
+// aligned), which is what these calls have always asked for; the passes'
+// spectra are a part of it: they have at most 2 L_0 - 1 <= P_0 planes of k and
+// L_0 of u, P_1 rows and P_last / 2 values a row, the circular problem's two
+// half spectra P_0 planes each.
 struct GridProblem {
   FftConvArgs e;  // the circular problem on the transform grid
   int nd;
@@ -145,7 +144,7 @@ bool grid_problem(const FftConvArgs& a, GridProblem* m) {
 
 Plan choose_plan(const FftConvArgs& a);
 
-// the circular plan of the grid problem of an embedded forward
+// the circular plan of the grid problem
 Plan embedded_inner_plan(const FftConvArgs& a, GridProblem* m) {
   if (!grid_problem(a, m)) return PLAN_NONE;
   const Plan p = choose_plan(m->e);
@@ -180,14 +179,14 @@ Plan choose_plan(const FftConvArgs& a) {
 
 size_t bytes_per_line(const FftConvArgs& a, Plan p);
 
-// workspace of an embedded forward: the five tensors, then the inner plan's
-// least (or recommended) workspace
+// workspace reported for PLAN_EMBED: the five tensors, then the circular
+// plan's least (or recommended) workspace
 size_t embed_fwd_ws(const FftConvArgs& a, bool recommended);
 
 size_t bytes_per_line(const FftConvArgs& a, Plan p) {
   if (p == PLAN_MULTIPASS) return multipass_bytes_per_line(a);
   if (p == PLAN_FOURSTEP) return fourstep_bytes_per_line(a);
-  if (p == PLAN_EMBED) return embed_fwd_ws(a, false);  // the least workspace of the whole call
+  if (p == PLAN_EMBED) return embed_fwd_ws(a, false);
   return 0;
 }
 
@@ -616,14 +615,14 @@ hipError_t launch_plan(const FftConvArgs& a, Plan p, size_t per, hipStream_t s) 
   switch (p) {
     case PLAN_FUSED1D: return ra1d_supported(a) ? launch_ra1d(a, false, s) : launch_fused1d(a, s);
     case PLAN_FUSED2D: return launch_fused2d(a, s);
-    case PLAN_EMBED:  // forward() embeds the other shapes itself
+    case PLAN_EMBED:
     case PLAN_MULTIPASS:
       if (runs_ra_mp(a, p))
         return run_chunked(a, ra_mp_bytes_per_line(a, false), s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
           return launch_ra_mp(a, l0, nl, ws, st);
         }, a.rl);
       if (runs_ra_line(a, p)) return run_ra_line(a, s);
-      if (p == PLAN_EMBED) return hipErrorInvalidValue;
+      if (p == PLAN_EMBED) return hipErrorInvalidValue;  // none: see GridProblem
       return run_chunked(a, per, s, [&a](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
         return launch_multipass(a, l0, nl, ws, st);
       });
@@ -722,22 +721,6 @@ hyenand_status forward(const void* x1, const void* x2, const void* v, const void
   a.ws_bytes = workspace_bytes;
   a.khat = use_khat ? (float2*)workspace : nullptr;
   clear_pending_error();
-  if (p == PLAN_EMBED && !runs_ra_mp(a, p) && !runs_ra_line(a, p)) {
-    // x1, x2, v, k into the transform grid, the circular plan there, y back
-    GridProblem m;
-    embedded_inner_plan(a, &m);
-    char* w = (char*)workspace;
-    void* const e[4] = {w, w + m.tensor, w + 2 * m.tensor, w + 3 * m.tensor};
-    void* const ey = w + 4 * m.tensor;
-    hipError_t err = launch_embed_fwd(a, e, (hipStream_t)stream);
-    if (err != hipSuccess) return fail(HYENAND_ERR_HIP, "HIP error %d: %s", (int)err, hipGetErrorString(err));
-    const hyenand_status inner = forward(e[0], e[1], e[2], e[3], D, ey, m.nd, m.dims, HYENAND_PAD_CIRCULAR, dtype,
-                                         w + 5 * m.tensor, workspace_bytes - 5 * m.tensor, stream, false);
-    if (inner != HYENAND_OK) return inner;
-    err = launch_extract_y(a, ey, y, (hipStream_t)stream);
-    if (err != hipSuccess) return fail(HYENAND_ERR_HIP, "HIP error %d: %s", (int)err, hipGetErrorString(err));
-    return HYENAND_OK;
-  }
   const hipError_t err = launch_plan(a, p, per, (hipStream_t)stream);
   if (err != hipSuccess) return fail(HYENAND_ERR_HIP, "HIP error %d: %s", (int)err, hipGetErrorString(err));
   return HYENAND_OK;
