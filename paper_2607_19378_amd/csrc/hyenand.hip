@@ -243,21 +243,31 @@ struct ChunkPlan {
 // (48 images of 8 x 32 87 -> 24 us, 128 of 128 x 32 69 -> 20, of 128 x 128, at
 // the limit, 71 -> 42; 32 lines of 16384 points 68 -> 23; circular, 32 images of
 // 256 x 64 71 -> 25).
+struct ChunkRule {
+  int streams;
+  int64_t lines;  // per chunk, where the workspace holds them
+};
+ChunkRule chunk_rule(const FftConvArgs& a, size_t per, bool ragged) {
+  const bool set = getenv("HYENAND_WS_TARGET_MB") || getenv("HYENAND_CHUNK_STREAMS");
+  const bool brief = ragged && per <= (size_t)(a.ndim == 2 ? 8 : 2) << 20;
+  const bool wide = (brief || (size_t)a.lines * per <= (size_t)32 << 20) && !set;
+  const size_t budget = wide ? (size_t)640 << 20 : ws_target_bytes((size_t)(ragged && a.ndim == 3 ? 320 : 160) << 20);
+  ChunkRule r;
+  r.streams = wide ? 1 : chunk_streams();
+  r.lines = (int64_t)(budget / (size_t)r.streams / per);
+  if (r.lines < 1) r.lines = 1;
+  return r;
+}
+
 ChunkPlan plan_chunks(const FftConvArgs& a, size_t per, bool ragged) {
   ChunkPlan c;
   const int64_t lines = a.lines, fit = (int64_t)(a.ws_bytes / per);  // >= 1, checked by the caller
-  const bool set = getenv("HYENAND_WS_TARGET_MB") || getenv("HYENAND_CHUNK_STREAMS");
-  const bool brief = ragged && per <= (size_t)(a.ndim == 2 ? 8 : 2) << 20;
-  const bool wide = (brief || (size_t)lines * per <= (size_t)32 << 20) && !set;
-  const int want = wide ? 1 : chunk_streams();
-  c.streams = want;
+  const ChunkRule rule = chunk_rule(a, per, ragged);
+  c.streams = rule.streams;
   if (c.streams > fit) c.streams = (int)fit;
   if (c.streams > lines) c.streams = (int)lines;
-  const size_t budget = wide ? (size_t)640 << 20 : ws_target_bytes((size_t)(ragged && a.ndim == 3 ? 320 : 160) << 20);
-  int64_t target = (int64_t)(budget / (size_t)want / per);
-  if (target < 1) target = 1;
   int64_t chunk = fit / c.streams;
-  if (chunk > target) chunk = target;
+  if (chunk > rule.lines) chunk = rule.lines;
   if (chunk > lines) chunk = lines;
   c.nchunks = (lines + chunk - 1) / chunk;
   c.chunk = (lines + c.nchunks - 1) / c.nchunks;  // balanced
@@ -405,14 +415,15 @@ hipError_t run_chunked(const FftConvArgs& a, size_t per, hipStream_t caller, Lau
 //
 // Extents that are not powers of two run the mixed-radix single pass
 // (BWD_MIXED, conv_mixed.hip) where their grid fits, and the right-angle kernels
-// instead where those take them.  Those beyond it and the centred mode on the
-// other power-of-two extents (BWD_EMBED) report the workspace of the embedded
-// route; the circular mode takes it, the others run the right-angle kernels.
-// Embedded: the circular backward on the transform grid (P_d >= 2 L_d - 1, a power of two): the five
-// inputs are embedded in that grid and the four gradient
-// tensors extracted from it (conv_embed.hip); gD comes out directly.  Their
-// workspace holds the nine embedded tensors (each 256-byte aligned) and then
-// the circular backward's own.
+// instead where those take them.  Those beyond it, and the centred mode on the
+// other power-of-two extents (BWD_EMBED), run the right-angle kernels, in one or
+// several passes, with a workspace of their own sums and spectra; what those do
+// not take is embedded: the circular mode, and centred lines of up to 256
+// points.  Embedded: the circular backward on the transform grid (P_d >=
+// 2 L_d - 1, a power of two): the five inputs are embedded in that grid and the
+// four gradient tensors extracted from it (conv_embed.hip); gD comes out
+// directly.  The workspace then holds the nine embedded tensors (each 256-byte
+// aligned) and the circular backward's own.
 enum BwdPlan { BWD_NONE = 0, BWD_FUSED, BWD_MULTIPASS, BWD_FOURSTEP, BWD_MIXED, BWD_EMBED };
 
 BwdPlan choose_bwd_plan(const FftConvArgs& a);
@@ -492,25 +503,54 @@ size_t bwd_recommended_spectra(const FftConvArgs& a, BwdPlan p) {
   return (size_t)n * per;
 }
 
-// as runs_ra_mp, for the backward: sums and spectra within the plan's least workspace
-bool bwd_runs_ra_mp(const FftConvArgs& a, BwdPlan p, size_t least) {
-  return (p == BWD_MULTIPASS || p == BWD_EMBED) && ra_mp_backward_supported(a) &&
-         ra_partial_bytes(a) + ra_mp_bytes_per_line(a, true) <= least;
-}
-
-bool bwd_runs_ra_line(const FftConvArgs& a, BwdPlan p, size_t least) {
-  return (p == BWD_FOURSTEP || p == BWD_EMBED) && ra_line_supported(a) && !a.periodic &&
-         ra_partial_bytes(a) + ra_line_bytes_per_line(a, true) <= least;
-}
 bool mixed_forced() {
   const char* force = getenv("HYENAND_PLAN");
   return force && strcmp(force, "mixed") == 0;
 }
 
-// one float per line of workspace, which every plan has (HYENAND_PLAN=mixed
-// keeps lines on the mixed-radix kernels)
+// The backward on right angles.  In one pass lines of 257 to 8192 points and images
+// (HYENAND_PLAN=mixed keeps those of the mixed plan on the mixed-radix kernels), with
+// one float per line of workspace.
 bool bwd_runs_ra1d(const FftConvArgs& a, BwdPlan p) {
   return p != BWD_NONE && !(p == BWD_MIXED && mixed_forced()) && ra1d_backward_supported(a);
+}
+bool bwd_runs_ra2d(const FftConvArgs& a, BwdPlan p) {
+  return p != BWD_NONE && !(p == BWD_MIXED && mixed_forced()) && ra2d_ragged(a) && !a.periodic;
+}
+// In several passes the others: the sums, then the spectra of a chunk of lines.
+bool bwd_ra_line(const FftConvArgs& a) { return ra_line_supported(a) && !a.periodic; }
+bool bwd_ra_passes(const FftConvArgs& a) { return bwd_ra_line(a) || ra_mp_backward_supported(a); }
+size_t bwd_ra_bytes_per_line(const FftConvArgs& a) {
+  return bwd_ra_line(a) ? ra_line_bytes_per_line(a, true) : ra_mp_bytes_per_line(a, true);
+}
+
+struct BwdWorkspace {
+  size_t least, recommended;
+};
+BwdWorkspace bwd_workspace(const FftConvArgs& a, BwdPlan p) {
+  if (p == BWD_EMBED) {
+    if (bwd_runs_ra1d(a, p) || bwd_runs_ra2d(a, p)) {
+      const size_t sums = bwd_partial_bytes(a, BWD_FUSED);
+      return {sums, sums};
+    }
+    if (bwd_ra_passes(a)) {
+      const size_t sums = ra_partial_bytes(a), per = bwd_ra_bytes_per_line(a);
+      const ChunkRule r = chunk_rule(a, per, a.rl);
+      return {sums + per, sums + (size_t)std::min(a.lines, r.lines * r.streams) * per};
+    }
+    Embedded m;
+    embedded_problem(a, &m);
+    const size_t fixed = 9 * m.tensor + bwd_partial_bytes(m.e, m.p);
+    return {fixed + bwd_bytes_per_line(m.e, m.p), fixed + bwd_recommended_spectra(m.e, m.p)};
+  }
+  const size_t sums = bwd_partial_bytes(a, p);
+  return {sums + bwd_bytes_per_line(a, p), sums + bwd_recommended_spectra(a, p)};
+}
+// (power-of-two grids keep the workspace of their circular plan, which holds the
+// right-angle passes' sums and spectra)
+bool bwd_runs_ra_passes(const FftConvArgs& a, BwdPlan p, size_t least) {
+  return (p == BWD_MULTIPASS || p == BWD_FOURSTEP || p == BWD_EMBED) && bwd_ra_passes(a) &&
+         ra_partial_bytes(a) + bwd_ra_bytes_per_line(a) <= least;
 }
 
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
@@ -894,13 +934,7 @@ hyenand_status hyenand_fftconv_backward_workspace_size(int ndim, const int64_t* 
   if (st != HYENAND_OK) return st;
   const BwdPlan p = choose_bwd_plan(a);
   if (p == BWD_NONE) return fail(HYENAND_ERR_UNSUPPORTED, "no backward plan for this shape");
-  if (p == BWD_EMBED) {
-    Embedded m;
-    embedded_problem(a, &m);
-    *bytes_out = 9 * m.tensor + bwd_partial_bytes(m.e, m.p) + bwd_recommended_spectra(m.e, m.p);
-    return HYENAND_OK;
-  }
-  *bytes_out = bwd_partial_bytes(a, p) + bwd_recommended_spectra(a, p);
+  *bytes_out = bwd_workspace(a, p).recommended;
   return HYENAND_OK;
 }
 
@@ -912,13 +946,7 @@ hyenand_status hyenand_fftconv_backward_workspace_min(int ndim, const int64_t* d
   if (st != HYENAND_OK) return st;
   const BwdPlan p = choose_bwd_plan(a);
   if (p == BWD_NONE) return fail(HYENAND_ERR_UNSUPPORTED, "no backward plan for this shape");
-  if (p == BWD_EMBED) {
-    Embedded m;
-    embedded_problem(a, &m);
-    *bytes_out = 9 * m.tensor + bwd_partial_bytes(m.e, m.p) + bwd_bytes_per_line(m.e, m.p);
-    return HYENAND_OK;
-  }
-  *bytes_out = bwd_partial_bytes(a, p) + bwd_bytes_per_line(a, p);
+  *bytes_out = bwd_workspace(a, p).least;
   return HYENAND_OK;
 }
 
@@ -963,11 +991,7 @@ hyenand_status hyenand_fftconv_backward(const void* x1, const void* x2, const vo
   }
   const BwdPlan p = choose_bwd_plan(a);
   if (p == BWD_NONE) return fail(HYENAND_ERR_UNSUPPORTED, "no backward plan for this shape");
-  Embedded m;
-  if (p == BWD_EMBED) embedded_problem(a, &m);
-  const size_t pbytes = p == BWD_EMBED ? 0 : bwd_partial_bytes(a, p);
-  const size_t need = p == BWD_EMBED ? 9 * m.tensor + bwd_partial_bytes(m.e, m.p) + bwd_bytes_per_line(m.e, m.p)
-                                     : pbytes + bwd_bytes_per_line(a, p);
+  const size_t need = bwd_workspace(a, p).least;
   if (!workspace || workspace_bytes < need)
     return fail(HYENAND_ERR_WORKSPACE_TOO_SMALL, "backward needs at least %zu workspace bytes, got %zu", need,
                 workspace ? workspace_bytes : (size_t)0);
@@ -990,24 +1014,26 @@ hyenand_status hyenand_fftconv_backward(const void* x1, const void* x2, const vo
   if (bwd_runs_ra1d(a, p)) {
     err = launch_ra1d_backward(b, p == BWD_MIXED, s);
     if (err == hipSuccess) err = launch_backward_reduce(b, 1, s);
-  } else if (ra2d_ragged(a) && !a.periodic && !(p == BWD_MIXED && mixed_forced())) {  // sums as above
+  } else if (bwd_runs_ra2d(a, p)) {
     err = launch_ra2d_backward(b, p == BWD_MIXED, s);
     if (err == hipSuccess) err = launch_backward_reduce(b, 1, s);
-  } else if (const bool line = bwd_runs_ra_line(a, p, need); line || bwd_runs_ra_mp(a, p, need)) {
+  } else if (bwd_runs_ra_passes(a, p, need)) {
     FftConvArgs sa = b.f;
     const size_t rb = ra_partial_bytes(a);
     sa.ws = (char*)workspace + rb;
     sa.ws_bytes = workspace_bytes - rb;
+    const bool line = bwd_ra_line(a);
     err = launch_ra_mp_hu(b, b.partial, s);
-    const size_t bytes = line ? ra_line_bytes_per_line(a, true) : ra_mp_bytes_per_line(a, true);
     if (err == hipSuccess)
-      err = run_chunked(sa, bytes, s,
+      err = run_chunked(sa, bwd_ra_bytes_per_line(a), s,
                         [&b, line](int64_t l0, int64_t nl, void* ws, hipStream_t st) {
                           return line ? launch_ra_line_backward(b, l0, nl, ws, st)
                                       : launch_ra_mp_backward(b, l0, nl, ws, st);
                         }, a.rl);
     if (err == hipSuccess) err = launch_backward_reduce(b, ra_mp_partials_per_line(a), s);
   } else if (p == BWD_EMBED) {
+    Embedded m;
+    embedded_problem(a, &m);
     char* w = (char*)workspace;
     void* e[9];
     for (int i = 0; i < 9; ++i) e[i] = w + i * m.tensor;
@@ -1028,6 +1054,7 @@ hyenand_status hyenand_fftconv_backward(const void* x1, const void* x2, const vo
   } else {
     // the spectra of each chunk follow the gD sums in the workspace
     FftConvArgs sa = b.f;
+    const size_t pbytes = bwd_partial_bytes(a, p);
     sa.ws = (char*)workspace + pbytes;
     sa.ws_bytes = workspace_bytes - pbytes;
     const size_t per = bwd_bytes_per_line(a, p);

@@ -89,7 +89,7 @@ def test_lines_fit():
 
 def test_scaled_lines_have_kernels():
     """The right-angle kernels that take the mixed plan's calls scale u, k and h by powers of two; the kernels built
-    without that (images beyond 32 x 32 points, non-circular lines, lines beyond 4096, backward beyond 2048 points) must
+    without that (images beyond 32 x 32 points, non-circular lines, lines beyond 4096) must
     not be reached by the plan."""
     for n0, n1 in itertools.product(range(17, 65), repeat=2):
         if max(n0, n1) > 32 and not (n0 & (n0 - 1) == 0 and n1 & (n1 - 1) == 0):
@@ -98,5 +98,22 @@ def test_scaled_lines_have_kernels():
     for L in list(range(257, 4097, 7)) + [4099, 5000, 8191]:
         assert L & (L - 1) == 0 or H.plan_name((2, 3, L), "linear", "f32") == "fused1d_any", L
         assert L <= 4096 or H.plan_name((2, 3, L), "circular", "f32") == "fused1d_any", L
-    for L in range(2049, 8192, 11):  # embedded, whose least workspace is more than the sums of six lines
-        assert H.backward_workspace_min((2, 3, L), "linear", "f32") > 256, L
+
+
+def test_backward_asks_for_what_it_uses():
+    """Centered and ragged backward calls on right angles hold the gD sums, and in several passes their spectra: no
+    copies on the transform grid (4 x 64 volumes of 48^3 asked for 19.5 GB of them)."""
+    for shape, mode in (((4, 64, 48, 48, 48), "centered"), ((4, 64, 200, 150), "centered"), ((2, 64, 500, 500), "linear"),
+                        ((1, 64, 300001), "linear"), ((8, 64, 128, 128), "centered"), ((1, 64, 1 << 20), "centered")):
+        lines, grid = shape[0] * shape[1], shape[2:]
+        if len(grid) == 1:
+            per = 3 * (1 << (2 * grid[0] - 2).bit_length() - 1) * 8
+        else:
+            p = [1 << (2 * n - 2).bit_length() for n in grid]
+            planes = 2 * grid[0] + (grid[0] if mode == "linear" else 2 * grid[0] - 1)
+            per = planes * (p[1] if len(grid) == 3 else 1) * (p[-1] // 2) * 8
+        least, size = (f(shape, mode, "bf16") for f in (H.backward_workspace_min, H.backward_workspace_size))
+        assert least == _sums(grid, lines) + per, (shape, mode)
+        assert least <= size <= _sums(grid, lines) + max(640 << 20, 2 * per), (shape, mode)
+    for shape, mode in (((8, 64, 5000), "linear"), ((8, 64, 57, 40), "centered"), ((8, 64, 8192), "centered")):
+        assert H.backward_workspace_min(shape, mode, "f32") == H.backward_workspace_size(shape, mode, "f32") == 8 * 64 * 4
