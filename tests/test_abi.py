@@ -61,8 +61,8 @@ def test_invalid_arguments(L):
     assert call(L, (1, 0, 16)) == H.ERR_INVALID_ARGUMENT
     assert call(L, (1, 1, 16), mode=3) == H.ERR_INVALID_ARGUMENT
     assert call(L, (1, 1, 16), dtype=5) == H.ERR_INVALID_ARGUMENT
-    # extents that are not powers of two beyond the single-pass kernels run
-    # embedded in their transform grid, which needs a workspace
+    # extents that are not powers of two beyond the single-pass kernels ask for
+    # copies on their transform grid and the circular plan's workspace
     assert call(L, (1, 1, 10000), mode=1) == H.ERR_WORKSPACE_TOO_SMALL
     assert call(L, (1, 1, 20, 20, 20), mode=1) == H.ERR_WORKSPACE_TOO_SMALL  # 8000 points: no mixed radix
     assert call(L, (1, 1, 300, 300)) == H.ERR_WORKSPACE_TOO_SMALL  # a 1024 x 1024 grid
@@ -127,8 +127,9 @@ def test_workspace_queries_are_host_only():
     assert H.plan_name((2, 4, 14, 16), "linear", "bf16") == "mixed2d"
     assert H.plan_name((2, 4, 24, 40), "linear", "f32") == "fused2d_any"   # 48 x 80 against 64 x 128
     assert H.workspace_size((2, 4, 14, 14), "linear", "f32") == 0
-    # beyond the single pass: embedded in the 256 x 256 grid; five embedded
-    # tensors of 256^2 floats, then the circular multi-pass plan's workspace
+    # beyond the single pass: the workspace of five tensors of 256^2 floats on
+    # the transform grid and of the circular multi-pass plan there (the passes
+    # that run use a part of it)
     assert H.plan_name((1, 1, 100, 100), "linear", "f32") == "embedded2d"
     assert H.plan_name((1, 2, 48, 48, 48), "centered", "bf16") == "embedded3d"
     assert H.workspace_min((1, 1, 100, 100), "linear", "f32") == (
@@ -227,8 +228,8 @@ def test_backward_workspace_size(L):
 
 def test_centered_mode_queries():
     """pad_mode 2: the transform grid of the linear mode, a workspace that
-    holds U (L0 rows) and a centered K (P0 rows) per line; the backward runs
-    embedded in the transform grid."""
+    holds U (L0 rows) and a centered K (P0 rows) per line; the backward of
+    lines of up to 256 points runs embedded in the transform grid."""
     assert H.plan_name((8, 256, 64, 64), "centered", "f32") == "fused2d"
     assert H.plan_name((1, 64, 4096), "centered", "f32") == "fused1d"
     assert H.plan_name((1, 4, 1 << 20), "centered", "bf16") == "fourstep1d"

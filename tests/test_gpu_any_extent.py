@@ -1,7 +1,8 @@
-"""Grid extents that are not powers of two: the single-pass kernels transform
-on the smallest power of two >= 2L - 1 and crop L points (linear and centered
-modes; the circular mode as the centred convolution of the periodically
-repeated kernel); parity with the fp64 oracle (which takes any extent) on 1D
+"""Grid extents that are not powers of two, off the mixed-radix kernels: the
+single-pass kernels transform on the smallest power of two >= 2L - 1 (or, on
+right angles, half as many complex points) and crop L points (linear and
+centered modes; the circular mode as the centred convolution of the
+periodically repeated kernel), larger grids in several passes; parity with the fp64 oracle (which takes any extent) on 1D
 and 2D grids, fp32 and bf16, one kernel per channel and the HyenaND
 operator.  These tests keep the library off the mixed-radix kernels
 (HYENAND_PLAN=nomixed), which tests/test_gpu_mixed_radix.py covers."""
@@ -132,6 +133,7 @@ def test_operator(grid, mode):
 def test_embedded_plans(shape, mode, dtype):
     """Shapes beyond the single-pass kernels (long 1D lines, large 2D images,
     every 3D grid, e.g. the 48^3 volumes of the medical-imaging experiments):
-    x1, x2, v, k embedded in the transform grid, the circular plan there."""
+    the plan whose workspace is that of copies on the transform grid; the
+    right-angle passes run in it, without copies."""
     plan = _check("embedded", shape[0], shape[1], shape[2:], mode, dtype, 70 + sum(shape))
     assert plan.startswith("embedded")

@@ -1,10 +1,10 @@
 """Backward of the centred mode and of grid extents that are not powers of
-two, every pad mode (hyenand_fftconv_backward running the circular backward
-on the transform grid of the embedded tensors) against the oracle's direct-sum backward, every
-gradient, fp32 and bf16, 1D/2D/3D, and each circular plan underneath (single
-pass, multi-pass, four-step).  The mixed-radix backward, which takes most
-of these shapes by default, is kept off here (HYENAND_PLAN=nomixed;
-tests/test_gpu_backward_mixed.py covers it)."""
+two, every pad mode, off the mixed-radix kernels (HYENAND_PLAN=nomixed;
+tests/test_gpu_backward_mixed.py covers those): the circular backward on the
+transform grid of the embedded tensors (circular mode, and centred lines of up
+to 256 points) with each circular plan underneath, and the right-angle kernels
+(the rest), against the oracle's direct-sum backward, every gradient, fp32 and
+bf16, 1D/2D/3D."""
 import os
 
 import numpy as np
@@ -77,15 +77,23 @@ def test_circular_other_extents(shape, dtype):
     _check(shape, "circular", dtype, 41 + sum(shape))
 
 
-def test_centered_long_line_four_step():
-    """2^14 points centred: a 2^15-point circular four-step backward underneath."""
-    from paper_2607_19378_amd import hyenand as H
-    assert H.plan_name((1, 2, 1 << 15), "circular", "f32") == "fourstep1d"
+def test_centered_long_line():
+    """2^14 points centred: the three-pass right-angle lines."""
     _check((1, 2, 1 << 14), "centered", "f32", 31)
 
 
-def test_centered_image_multipass():
-    """64 x 64 centred: the 128 x 128 circular grid runs the multi-pass backward."""
+def test_circular_long_line_four_step():
+    """12000 points: a 2^15-point circular four-step backward underneath the embedded copies."""
+    from paper_2607_19378_amd import hyenand as H
+    assert H.plan_name((1, 2, 1 << 15), "circular", "f32") == "fourstep1d"
+    assert H.backward_workspace_min((1, 2, 12000), "circular", "f32") > 9 * 2 * (1 << 15) * 4
+    _check((1, 2, 12000), "circular", "f32", 33)
+
+
+def test_circular_image_multipass():
+    """60 x 50: the 128 x 128 circular grid runs the multi-pass backward underneath the embedded copies."""
     from paper_2607_19378_amd import hyenand as H
     assert H.backward_workspace_min((1, 2, 128, 128), "circular", "f32") > 256
-    _check((1, 2, 64, 64), "centered", "f32", 32)
+    assert H.backward_workspace_min((1, 2, 60, 50), "circular", "f32") > 9 * 2 * 128 * 128 * 4
+    _check((1, 2, 60, 50), "circular", "f32", 32)
+    _check((1, 2, 64, 64), "centered", "f32", 32)  # in one pass on right angles

@@ -2,7 +2,9 @@
 single pass for extents that are not powers of two): every gradient against
 the oracle's direct-sum backward, whole tensors and the worst line, every
 pad mode, fp32 and bf16, 1D/2D/3D, odd line counts, several pairs per
-workgroup, every radix family, and inputs of very different scales."""
+workgroup, every radix family, and inputs of very different scales.  They
+run under HYENAND_PLAN=mixed: by default lines and images of the non-circular
+modes take the right-angle kernels (tests/test_gpu_ra1d.py, test_gpu_ra2d.py)."""
 import os
 
 import numpy as np
@@ -61,7 +63,7 @@ def _check(shape, mode, dtype, seed, scales=None, kscale=1.0, **env):
         x1, gy = x1 * s, gy * s[::-1]
     x1, x2, v, gy, k, D = (W.quantise(a, dtype) for a in (x1, x2, v, gy, k, D))
     dev = [to_device(a, dtype) for a in (x1, x2, v, k, D, gy)]
-    with _env(**env):
+    with _env(HYENAND_PLAN="mixed", **env):
         assert H.backward_workspace_min(shape, mode, dtype) == _mixed_workspace(shape), "not the mixed-radix plan"
         outs = H.backward(*dev, pad_mode=mode)
         torch.cuda.synchronize()

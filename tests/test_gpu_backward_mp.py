@@ -96,3 +96,24 @@ def test_backward_workspace_sizes_bitwise(shape, mode, dtype):
     for other in runs[1:]:
         for a, b in zip(runs[0], other):
             assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("shape,mode,dtype", [((1, 7, 128, 256), "linear", "f32"), ((1, 7, 100, 70), "centered", "bf16"),
+                                              ((1, 7, 256, 128), "circular", "f32"), ((1, 7, 20000), "linear", "f32"),
+                                              ((1, 7, 32768), "circular", "bf16")])
+def test_backward_side_streams_bitwise(monkeypatch, shape, mode, dtype):
+    """Seven lines in chunks of one, on the caller's stream alone and over two and three side streams: the same bits."""
+    from paper_2607_19378_amd import hyenand as H
+    B, C, grid = shape[0], shape[1], shape[2:]
+    inp = W.random_case(B, C, grid, mode, dtype, seed=43)
+    gy = _gy(shape, dtype, 44)
+    log(f"[bwd-streams] {shape} {mode} {dtype}")
+    wmin = H.backward_workspace_min(shape, mode, dtype)
+    assert wmin > 256, "a single-pass plan, without chunks"
+    runs = []
+    for streams in ("1", "2", "3"):
+        monkeypatch.setenv("HYENAND_CHUNK_STREAMS", streams)
+        runs.append([from_device(g) for g in _gpu_backward(inp, gy, 3 * wmin)])
+    for other in runs[1:]:
+        for a, b in zip(runs[0], other):
+            assert np.array_equal(a, b)

@@ -98,8 +98,8 @@ def test_chunked_workspace_matches_full():
         assert rel_l2(y3, oracle_ref(inp)) <= TOL["f32"]
 
 
-@pytest.mark.parametrize("grid,mode,dtype", [((64, 32), "circular", "f32"), ((8, 8, 16), "linear", "bf16"),
-                                             ((16384,), "linear", "f32")])
+@pytest.mark.parametrize("grid,mode,dtype", [((256, 128), "circular", "f32"), ((8, 8, 16), "linear", "bf16"),
+                                             ((16384,), "linear", "f32"), ((100, 70), "centered", "f32")])
 def test_side_streams_match_caller_stream(monkeypatch, grid, mode, dtype):
     """Chunks rotating over two or three side streams (7 lines, 3 lines of
     workspace: chunks of one line each) give bitwise the result of every
@@ -111,6 +111,7 @@ def test_side_streams_match_caller_stream(monkeypatch, grid, mode, dtype):
     inp = W.random_case(1, 7, grid, mode, dtype, seed=33)
     w = inp.workload
     wmin = H.workspace_min(w.shape, w.pad_mode, w.dtype)
+    assert wmin > 0, "a single-pass plan, without chunks"
     dev = [to_device(a, w.dtype) for a in (inp.x1, inp.x2, inp.v, inp.k, inp.D)]
     ws = torch.empty(3 * wmin, dtype=torch.uint8, device="cuda")
     outs = []
@@ -131,14 +132,19 @@ def test_side_streams_match_caller_stream(monkeypatch, grid, mode, dtype):
     assert rel_l2(a, oracle_ref(inp)) <= TOL[dtype]
 
 
-def test_graph_capture_with_side_streams():
+@pytest.mark.parametrize("grid,mode,name", [((256, 128), "circular", "multipass2d"), ((128, 256), "linear", "multipass2d"),
+                                            ((32768,), "linear", "fourstep1d")])
+def test_graph_capture_with_side_streams(monkeypatch, grid, mode, name):
     """A multi-pass call captured into a graph (chunks on two side streams)
-    replays to the eager result, three times, with eager calls in between."""
+    replays to the eager result, three times, with eager calls in between.
+    (By themselves calls this small stay on the caller's stream.)"""
     import torch
     from paper_2607_19378_amd import hyenand as H
     from gpu_util import to_device
-    inp = W.random_case(1, 5, (64, 32), "circular", "f32", seed=44)
+    monkeypatch.setenv("HYENAND_CHUNK_STREAMS", "2")
+    inp = W.random_case(1, 5, grid, mode, "f32", seed=44)
     w = inp.workload
+    assert plan(inp) == name
     wmin = H.workspace_min(w.shape, w.pad_mode, w.dtype)
     dev = [to_device(a, w.dtype) for a in (inp.x1, inp.x2, inp.v, inp.k, inp.D)]
     ws = torch.empty(2 * wmin, dtype=torch.uint8, device="cuda")
@@ -186,8 +192,9 @@ def test_maximum_extents(grid, mode, dtype):
     check_full(inp, f"max {grid} {mode}")
 
 
-def test_other_stream_outside_its_context():
-    """fftconv(stream=s) called while another stream is current: the binding
+def test_other_stream_outside_its_context(monkeypatch):
+    """fftconv(stream=s) called while another stream is current (its chunks on
+    two side streams of the library): the binding
     allocates y and the workspace on the current stream and hands them to s.
     Allocations made on the current stream right after the call (before s
     finishes) must not take their memory: y matches a call on the current
@@ -195,6 +202,7 @@ def test_other_stream_outside_its_context():
     import torch
     from paper_2607_19378_amd import hyenand as H
     from gpu_util import to_device
+    monkeypatch.setenv("HYENAND_CHUNK_STREAMS", "2")
     inp = W.random_case(2, 6, (256, 128), "circular", "f32", seed=45)
     w = inp.workload
     assert plan(inp) == "multipass2d"
@@ -215,14 +223,15 @@ def test_other_stream_outside_its_context():
             assert bool((f == float(rep + j)).all())
 
 
-def test_host_threads_each_with_own_side_streams():
+def test_host_threads_each_with_own_side_streams(monkeypatch):
     """Four host threads call multi-pass plans at once, each on a stream of
-    its own (ctypes releases the GIL inside the library, so the calls overlap
+    its own and with two side streams (ctypes releases the GIL inside the library, so the calls overlap
     on the host); every result matches the single-thread one bitwise."""
     import threading
     import torch
     from paper_2607_19378_amd import hyenand as H
     from gpu_util import to_device
+    monkeypatch.setenv("HYENAND_CHUNK_STREAMS", "2")  # calls this small would stay on their stream
     cases = []
     for j, (grid, mode) in enumerate((((256, 128), "circular"), ((32768,), "linear"), ((8, 16, 8), "linear"),
                                       ((128, 256), "linear"))):
