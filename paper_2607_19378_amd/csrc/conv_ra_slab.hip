@@ -50,11 +50,23 @@ __device__ __forceinline__ int slab_bin(int col) {
   return col / CW * (P1 * CW) + col % CW;
 }
 
+// Wavefronts per SIMD asked for (the VGPR cap: 6 is 80, 4 is 128).  Planes of up to
+// 128 axis-1 bins fit several times in the LDS of a CU, and 6 wavefronts of them hide
+// more latency than 4.  Not where rows have 65 to 128 points, in the inverse and in a
+// kernel's planes (FULL): their points (two foldings or both halves) do not fit in 80
+// VGPRs, and 7 to 66 spilled (at 128 at most 5, in gk).  32 volumes of 64 x 64 x 128,
+// centered, bf16: 6 for all 960 us, 4 in those inverses 875, in both 737; backward
+// 1740, 1581, 1415.  P1 = 256 needs 1024 lanes, so 4, and spills 2 to 9.
+template <int P1, int N>
+constexpr int slab_waves(bool many) {
+  return P1 <= 128 && !(many && N > 64) ? 6 : 4;
+}
+
 // FULL: a kernel on the double grid (signal 0), planes of 2 L0 - 1
 // displacements; else the gated signals and, w null, linear kernels.
 // Workgroups: (line, plane, signal, folding).
 template <int P1, int N, bool FULL, typename TS, bool ACT>
-__global__ void __launch_bounds__((SlabFwd<P1, N>::NT)) __attribute__((amdgpu_waves_per_eu(P1 <= 128 ? 6 : 4)))
+__global__ void __launch_bounds__((SlabFwd<P1, N>::NT)) __attribute__((amdgpu_waves_per_eu(slab_waves<P1, N>(FULL))))
     ra_slab_fwd(RaSignals sg, float2* __restrict__ ws, RaGeom g, int64_t line0, int64_t per, int kC, int vec, ActIn ain,
                 int C) {
   using S_ = SlabFwd<P1, N>;
@@ -188,7 +200,7 @@ __global__ void __launch_bounds__((SlabFwd<P1, N>::NT)) __attribute__((amdgpu_wa
 // Workgroups: (line, plane), for a gk on the double grid (line, plane, half of
 // axis 1).
 template <int P1, int N, RaOut OUT, typename TS, bool ACT>
-__global__ void __launch_bounds__((SlabInv<P1, N>::NT)) __attribute__((amdgpu_waves_per_eu(P1 <= 128 ? 6 : 4)))
+__global__ void __launch_bounds__((SlabInv<P1, N>::NT)) __attribute__((amdgpu_waves_per_eu(slab_waves<P1, N>(true))))
     ra_slab_inv(const float2* __restrict__ ws, const TS* __restrict__ p, const TS* __restrict__ q,
                 TS* __restrict__ o1, TS* __restrict__ o2, RaGeom g, int64_t line0, int64_t per, int vec) {
   using S_ = SlabInv<P1, N>;
