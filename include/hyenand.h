@@ -97,11 +97,12 @@ typedef enum { HYENAND_DTYPE_F32 = 0, HYENAND_DTYPE_BF16 = 1, HYENAND_DTYPE_MAX_
  *                   L_d - 1, which makes it a non-circular one): in one pass
  *                   per line for 1D up to L = 8192 and 2D up to 128-point
  *                   transforms per axis; beyond that in several passes over
- *                   the points of the grid.  The workspace queries keep the
- *                   size of the embedded route there (five tensors on the
- *                   power-of-two transform grid, and the circular plan's own
- *                   workspace; at most 2^31 elements per embedded
- *                   tensor).  The operator takes the single-pass shapes only.
+ *                   the points of the grid.  The workspace queries report
+ *                   five tensors on the power-of-two transform grid there,
+ *                   and the circular plan's workspace on it, of which the
+ *                   passes use a part (at most 2^31 elements on that grid
+ *                   over all lines).  The operator takes the single-pass
+ *                   shapes only.
  * pad_mode        : hyenand_pad_mode.
  * dtype           : hyenand_dtype.
  * workspace       : device scratch of workspace_bytes (16-byte aligned), owned
@@ -119,10 +120,13 @@ typedef enum { HYENAND_DTYPE_F32 = 0, HYENAND_DTYPE_BF16 = 1, HYENAND_DTYPE_MAX_
  * must not share a workspace.  Results are deterministic (no atomics) and do
  * not depend on the workspace size.
  *
- * The multi-pass plans (the ones with a nonzero workspace) fork onto two or
- * three side streams of the library that wait for `stream` and that `stream`
- * waits for before anything enqueued after the call; a graph captured on
- * `stream` therefore takes them in.  Each host thread has its own side
+ * The multi-pass plans (the ones with a nonzero workspace) run calls of up to
+ * 32 MiB of spectra, and the short lines of extents that are not powers of two,
+ * on `stream` alone.  Others fork onto two side streams of the library that
+ * wait for `stream` and that `stream` waits for before anything enqueued after
+ * the call; a graph captured on `stream` therefore takes them in.  (The
+ * environment's HYENAND_CHUNK_STREAMS, 1 to 4, sets the number for every call,
+ * HYENAND_WS_TARGET_MB the spectra in flight.)  Each host thread has its own side
  * streams and fork/join events per device (default priority, created on the
  * thread's first multi-pass call there, kept until the process ends), so
  * calls from several threads run concurrently and a capture on one thread
@@ -257,9 +261,11 @@ hyenand_status hyenand_fftconv_workspace_min(int ndim, const int64_t* dims, hyen
                                              hyenand_dtype dtype, size_t* bytes_out);
 
 /* Name of the plan the call would use ("fused1d", "fused2d", "multipass2d",
- * "multipass3d", "fourstep1d"; for extents that are not powers of two
- * "mixed1d/2d/3d", "fused1d_any", "fused2d_any" or "embedded1d/2d/3d"), written
- * NUL-terminated into buf (at most n bytes).  Pure host function. */
+ * "multipass3d", "slab3d", "fourstep1d"; for extents that are not powers of two
+ * "mixed1d/2d/3d", "fused1d_any", "fused2d_any" or "embedded1d/2d/3d"; a name
+ * stands for the shape's workspace and limits, and its kernels may be others, as
+ * those of "embedded" shapes, which copy nothing), written NUL-terminated into
+ * buf (at most n bytes).  Pure host function. */
 hyenand_status hyenand_fftconv_plan_name(int ndim, const int64_t* dims, hyenand_pad_mode pad_mode, hyenand_dtype dtype,
                                          char* buf, size_t n);
 
@@ -292,16 +298,19 @@ hyenand_status hyenand_fftconv_plan_name(int ndim, const int64_t* dims, hyenand_
  *
  * Centred mode (k and gk [B, C, 2 L1 - 1, ...], gu[j] = sum_n k[n - j +
  * (L - 1)] h[n] + D h[j], gk[i] = sum_n h[n] u[n - i + (L - 1)]) and
- * extents that are not powers of two.  Lines of up to 8192 points and images of
- * 9 to 64 points per axis (16 beside 64 excepted) run in one pass, larger grids
- * in several over the points of the grid; other extents also on the forward's
- * mixed-radix grid where it fits (about 3000 transform points per image; the
- * workspace holds the gD sums only).  The circular mode on other extents beyond
- * that grid is embedded: the library copies x1, x2, v, gy and k into the
- * transform grid (a power of two >= 2 L_d - 1 per axis), runs the circular
- * backward there and extracts the gradients.  The workspace of these shapes, of
- * either kind, holds nine embedded tensors (each B * C * prod P
- * elements of dtype, 256-byte aligned); the workspace queries include them.
+ * extents that are not powers of two.  In the linear and centred modes lines of
+ * 257 to 8192 points and images of 9 to 64 points per axis (up to 16 beside 33 or
+ * more excepted) run in one pass, larger grids in several over the points of the grid
+ * (the workspace holds their sums and the spectra of a chunk of lines); other
+ * extents also on the forward's mixed-radix grid where it fits (about 3000
+ * transform points per image; the workspace holds the gD sums only).  The
+ * circular mode on other extents beyond that grid, and centred lines of up to 256
+ * points, are embedded: the library copies x1, x2, v, gy and k into the transform
+ * grid (a power of two >= 2 L_d - 1 per axis), runs the circular backward there
+ * and extracts the gradients; their workspace holds the nine embedded tensors
+ * (each B * C * prod P elements of dtype, 256-byte aligned) and the circular
+ * backward's.  At most 2^31 elements on that grid over all lines, embedded or
+ * not.
  * Extents that are not powers of two may also be 3D here.
  */
 hyenand_status hyenand_fftconv_backward(const void* x1, const void* x2, const void* v, const void* k,

@@ -19,17 +19,17 @@
 // 8192 points move 0.15 GB in fp32, 30 us at 5.1 TB/s).  The packed
 // real transform on 2 P points, which these replace, untangled its mirror bins
 // through LDS, and the lengths that are no powers of two went through copies
-// embedded in a circular grid.  Forward, 1024 x 8192 points, fp32: 92.9 -> 71.2
-// us; backward, bf16, centered, 1024 x 8192: 919.7 -> 131.2; 1024 x 8000 linear:
-// 806.9 -> 123.9.  One line per workgroup leaves short calls to the latency of
+// embedded in a circular grid.  Forward, 1024 x 8192 points, fp32: 92.9 -> 72.8
+// us; backward, bf16, centered, 1024 x 8192: 919.7 -> 137.5; 1024 x 8000 linear:
+// 806.9 -> 127.9.  One line per workgroup leaves short calls to the latency of
 // the chain: 64 lines of 4096 points 10.5 -> 8.9 us.
 //
 // Three passes: bound by the traffic of the spectra (forward: u and k written
 // and read, y written and read, 48 bytes a point against 8 of the tensors).
-// 256 lines of 2^20 points, bf16, with the filter's own kernel: 3812 -> 3349
-// us; the columns of u and k 57 us, the core 49 and the inverse columns 30 per
-// launch of ten lines, of which two run side by side.  512 lines of 16384
-// points, backward, bf16: 421 -> 321 us; lengths that are no powers of two
+// 256 lines of 2^20 points, bf16, with the filter's own kernel: 3812 -> 3343
+// us, 15.7 GB; the columns of u and k 51 us, the core 44 and the inverse columns 28
+// per launch of five lines, of which two run side by side.  512 lines of 16384
+// points, backward, bf16: 421 -> 275 us; lengths that are no powers of two
 // (embedded copies before) 3.1 to 7 times faster.
 #include "fourstep.hpp"
 #include "ra_mp.hpp"

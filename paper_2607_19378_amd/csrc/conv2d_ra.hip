@@ -10,15 +10,16 @@
 // columns and back (two per image in the linear forward kernel).
 //
 // What bounds them (8 x 256 images of 64 x 64, fp32): the forward kernel issues
-// 25.5 M VALU instructions, 41.5 us, with 47 us of arithmetic without its
-// loads and stores and 33 us of traffic; two images per CU (74 KB of LDS
-// each, 110 VGPRs) overlap the two.  The packed real transforms that these
-// replace issued 29.0 M and met 21 barriers: linear forward 64.7 -> 58.1 us,
-// the operator on centered kernels 165 -> 118 us (bf16), linear backward 220
-// -> 158 us, and centered backward 1566 us (embedded in the circular 128 x 128
-// grid) -> 224 us.  The backward holds three spectra in registers (228 VGPRs):
-// one image per CU, its loads, arithmetic and stores in turn; at 128 VGPRs it
-// spills (360 us).  Keeping a workgroup resident and fetching the next image's
+// 25.5 M VALU instructions, 41.5 us, and moves 168 MB, 33 us at a large copy's 5.1
+// TB/s; two images per CU (74 KB of LDS each, 109 VGPRs) overlap the two.  The
+// packed real transforms that these replace issued 29.8 M and met 21 barriers:
+// linear forward 64.7 -> 56.3 us, the operator on centered kernels 165 -> 118 us
+// (bf16), linear backward 220 -> 147 us, and centered backward 1566 us (embedded in
+// the circular 128 x 128 grid) -> 222 us.  The backward holds three spectra in
+// registers (230 VGPRs): one image per CU, its loads, arithmetic and stores in turn;
+// at 128 VGPRs it spills (360 us).  The forward of ragged extents in 128 x 128
+// transforms spills 8 to 10 of its 128 VGPRs (36 to 44 bytes a lane; 57 x 40, fp32,
+// centered: 60.6 us).  Keeping a workgroup resident and fetching the next image's
 // inputs during the inverse rows spilled too (80 us forward).
 #include "ra_mp.hpp"
 
@@ -633,10 +634,10 @@ bool ra2d_supported(const FftConvArgs& a) {
 // kernels would transform fewer points: those wait at a workgroup barrier for
 // every factor and compute their indexes from run-time radixes.  8 x 256
 // images, fp32, centered, forward and backward: 17 x 17 (four times the points)
-// 30.6 -> 20.4 and 56.7 -> 40.7 us; 28 x 28 62.2 -> 21.4 and 134 -> 45.4; 57 x
-// 40 (packed real transforms, and embedded) 273 -> 64.9 and 1330 -> 168; 16 x
-// 384 of 9 x 9 27.1 -> 15.6 and 55.9 -> 34.4, of 14 x 14 44.3 -> 16.9 and 89.4
-// -> 40.1.
+// 30.6 -> 21.9 and 56.7 -> 41.5 us; 28 x 28 62.2 -> 21.8 and 134 -> 45.3; 57 x
+// 40 (packed real transforms, and embedded) 273 -> 60.6 and 1330 -> 166; 16 x
+// 384 of 9 x 9 27.1 -> 16.4 and 55.9 -> 31.3, of 14 x 14 44.3 -> 17.4 and 89.4
+// -> 38.8.
 bool ra2d_ragged(const FftConvArgs& a) {
   if (a.ndim != 2 || a.circular || !a.rl) return false;
 #define HY_CASE(p0, p1) if (a.P[0] == p0 && a.P[1] == p1) return true;

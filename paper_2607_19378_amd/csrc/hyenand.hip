@@ -637,8 +637,7 @@ namespace {
 
 // Circular lines reach the mixed-radix kernels with a transform of their own L
 // points; a right-angle one of N >= L points is the faster when it is not much
-// longer (1024 lines of 1000 points, N = 1024: 13.0 against 16.3 us, of 3000
-// points, N = 4096: 28.9 against 42.3).
+// longer (1024 lines of 3000 points, N = 4096: 26.6 against 42.3 us).
 bool mixed_line_on_ra1d(const FftConvArgs& a) {
   return ra1d_supported(a) && !mixed_forced() && 5 * (a.P[0] / 2) <= 7 * a.L[0];
 }
@@ -673,8 +672,11 @@ hipError_t launch_plan(const FftConvArgs& a, Plan p, size_t per, hipStream_t s) 
       });
     case PLAN_FUSED_RL: return ra1d_supported(a) ? launch_ra1d(a, false, s) : launch_fused_rl(a, s);
     case PLAN_MIXED:
-      // not circular images, whose mixed-radix transforms have no padding (8 x 256
-      // x 28 x 28, fp32: 21.3 us)
+      // not circular images: with no prime factor above 7 their mixed-radix
+      // transforms have no padding (6144 of 14 x 14, fp32, 15.2 us, right angles
+      // 16.6; of 28 x 28 45 against 54).  The others, and calls of few images, would
+      // be faster on right angles (6144 of 22 x 22 184 against 55 us, 64 of 14 x 14
+      // 9.5 against 5.2) but have not been moved there.
       if (ra2d_ragged(a) && !a.periodic && !mixed_forced()) return launch_ra2d(a, true, s);
       return mixed_line_on_ra1d(a) ? launch_ra1d(a, true, s) : launch_mixed(a, s);
     default: return hipErrorInvalidValue;

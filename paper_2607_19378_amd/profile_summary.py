@@ -49,8 +49,9 @@ def _rows(d: str, suffix: str):
 
 
 def short_name(full: str) -> str:
-    """'void hyenand::(anonymous namespace)::mp_core<512, true>(...)' -> 'mp_core<512, true>'."""
-    n = full.strip('"')
+    """'void hyenand::(anonymous namespace)::mp_core<512, true>(...)' -> 'mp_core<512, true>' (enum arguments of a
+    template, '(hyenand::(anonymous namespace)::RaOut)0', keep their value)."""
+    n = full.strip('"').replace("(anonymous namespace)::", "").replace("hyenand::", "").replace("(RaOut)", "")
     if n.startswith("void "):
         n = n[5:]
     depth, cut = 0, len(n)
