@@ -156,7 +156,7 @@ def synth_summary(a, W, source_hash):
              f"Kernel synthesis (FiLM-modulated SIREN, Hf = {bench.SYNTH_HIDDEN}, J = {bench.SYNTH_LAYERS}, "
              f"Gaussian window) on the kernel grid of {w.description}: {w.B} x {w.C} x {npos} points.  "
              f"Kernel source hash `{source_hash()}`.", "",
-             "Commands (run from /tmp with TMPDIR=/tmp on the MI355X box):", "",
+             "Commands (run from /tmp with TMPDIR=/tmp on the MI355X):", "",
              "```", a.cmd_trace, a.cmd_fetch, a.cmd_write, "```", "",
              "## Kernel durations (rocprofv3 --kernel-trace --stats)", "",
              "| kernel | dispatches | avg us | min us | max us |", "|---|---:|---:|---:|---:|"]
@@ -220,7 +220,7 @@ def modal_summary(a, W, source_hash):
     lines = [f"# modal filter on {w.name}", "",
              f"Modal filter generation, order {bench.MODAL_ORDER}, one filter per channel over the length of "
              f"{w.description}: {w.C} x {L} points.  Kernel source hash `{source_hash()}`.", "",
-             "Commands (run from /tmp with TMPDIR=/tmp on the MI355X box):", "",
+             "Commands (run from /tmp with TMPDIR=/tmp on the MI355X):", "",
              "```", a.cmd_trace, a.cmd_fetch, a.cmd_write, "```", "",
              "## Kernel durations (rocprofv3 --kernel-trace --stats)", "",
              "| kernel | dispatches | avg us | min us | max us |", "|---|---:|---:|---:|---:|"]
@@ -312,7 +312,7 @@ def main(argv=None):
 
     lines = [f"# {plan} on {w.name}", "",
              f"{w.description}.  Plan `{plan}`; kernel source hash `{h}`.", "",
-             "Commands (run from /tmp with TMPDIR=/tmp on the MI355X box; bench.py made "
+             "Commands (run from /tmp with TMPDIR=/tmp on the MI355X; bench.py made "
              f"{a.calls} hyenand_fftconv calls in each, the last {a.steps} timed):", "",
              "```", a.cmd_trace, a.cmd_fetch, a.cmd_write, "```", "",
              "## Kernel durations (rocprofv3 --kernel-trace --stats)", "",
